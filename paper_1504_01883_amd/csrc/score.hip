@@ -3,6 +3,8 @@
 // value names the person).
 //
 // FP32 paths:
+//   * k_score_f32_rows (few rows or few identities, D a multiple of 4): operands
+//     straight to registers, D shared by the waves of a workgroup;
 //   * k_score_f32_split (D a multiple of 32 per split, 16-byte aligned rows):
 //     128 x 128 tiles streamed through LDS, described at the kernel;
 //   * k_score_f32 (any D): v_mfma_f32_16x16x4f32 (D[m][n] += sum_k A[m][k]
@@ -23,6 +25,8 @@ namespace {
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kTile = 64;
+constexpr int kRowsWaves = 8;      // waves of k_score_f32_rows
+constexpr int kRowsMaxSplits = 8;  // its ranges of D at most
 
 // Four consecutive operands d .. d+3 of row `row` (zeros past `nrows` rows or
 // past `d_end`); `ld` is the row stride. kVec: 16-byte aligned rows and
@@ -445,6 +449,167 @@ __global__ __launch_bounds__(256) void k_reduce_argmax(const float *__restrict__
     if (lane == 0) out[n] = arg;
 }
 
+// --- FP32, few feature rows ---------------------------------------------------------
+//
+// Bound by reading W once (a frame's faces: 5 x 1024 x 7552 reads 31 MB of W
+// for 77 MFLOP). A workgroup of 8 wave64 owns 32 identities x 16 kNB feature
+// rows over one of `splits` ranges of the 32-column steps of D; its waves take
+// the steps in turn (step s by wave s % 8) and their sums meet in LDS in wave
+// order. Operands go straight from global memory to registers: of each 128-byte
+// step of a row, lane quarter q = l / 16 holds columns 8 q .. 8 q + 7, and
+// MFMA c (c = 0..7) multiplies column 8 q + c of every quarter, so the eight
+// MFMAs cover the step once for both operands. W is the first operand: a lane
+// then holds four consecutive identities of one feature row. kU steps are
+// loaded before the first of them is multiplied. 5 x 8192 x 7552: 51 us a call,
+// 4.9 TB/s of W (128 x 128 tiles: 167 us); 5 x 1024 x 7552: 15 us, mostly
+// launches (130 us).
+template <int kNB, bool kTail>
+__global__ __launch_bounds__(512) void k_score_f32_rows(
+    const float *__restrict__ X, int32_t N, const float *__restrict__ W,
+    const float *__restrict__ bias, int32_t K, int32_t D, float *__restrict__ S, int32_t splits,
+    float *__restrict__ part, const int32_t *__restrict__ n_dev) {
+    constexpr int kWB = 2, kU = kNB == 4 ? 2 : 4;
+    __shared__ floatx4 red[kRowsWaves][kWB][kNB][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r = lane & 15, q = lane >> 4;
+    const int32_t k0 = blockIdx.x * 16 * kWB, n0 = blockIdx.y * 16 * kNB, sp = blockIdx.z;
+    if (n_dev) N = *n_dev;
+    if (n0 >= N) return;  // uniform
+    const float *wp[kWB], *xp[kNB];
+#pragma unroll
+    for (int i = 0; i < kWB; ++i) wp[i] = W + (size_t)min(k0 + 16 * i + r, K - 1) * D + 8 * q;
+#pragma unroll
+    for (int j = 0; j < kNB; ++j) xp[j] = X + (size_t)min(n0 + 16 * j + r, N - 1) * D + 8 * q;
+    const int32_t steps = (D + 31) >> 5;
+    const int32_t s_end = (int32_t)((int64_t)steps * (sp + 1) / splits);
+    floatx4 acc[kWB][kNB];
+#pragma unroll
+    for (int i = 0; i < kWB; ++i)
+#pragma unroll
+        for (int j = 0; j < kNB; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // Columns 32 s + 8 q .. + 7 of a row (p points at its column 8 q); zeros
+    // past D, a multiple of 4 (kTail: D % 32 != 0). No branch: a guarded load
+    // would be waited for before the next one is issued.
+    auto load8 = [&](const float *p, int32_t s, floatx4 (&v)[2]) {
+        const int32_t d = 32 * s;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int32_t at = d + 8 * q + 4 * h;
+            v[h] = *reinterpret_cast<const floatx4 *>(p + (kTail ? min(at, D - 4) - 8 * q : d + 4 * h));
+            if (kTail && at >= D) v[h] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    for (int32_t s = (int32_t)((int64_t)steps * sp / splits) + wave; s < s_end;
+         s += kRowsWaves * kU) {
+        floatx4 wv[kU][kWB][2], xv[kU][kNB][2];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            // Past the range: any step before D, loaded but not multiplied.
+            const int32_t su = min(s + kRowsWaves * u, s_end - 1);
+#pragma unroll
+            for (int i = 0; i < kWB; ++i) load8(wp[i], su, wv[u][i]);
+#pragma unroll
+            for (int j = 0; j < kNB; ++j) load8(xp[j], su, xv[u][j]);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // every load issued before the first wait
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            if (s + kRowsWaves * u >= s_end) break;  // uniform
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+#pragma unroll
+                for (int i = 0; i < kWB; ++i)
+#pragma unroll
+                    for (int j = 0; j < kNB; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                            wv[u][i][c >> 2][c & 3], xv[u][j][c >> 2][c & 3], acc[i][j], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kWB; ++i)
+#pragma unroll
+        for (int j = 0; j < kNB; ++j) red[wave][i][j][lane] = acc[i][j];
+    __syncthreads();
+    // Lane l of block (i, j): S[n0 + 16 j + l % 16][k0 + 16 i + 4 (l / 16) + t].
+    for (int e = threadIdx.x; e < kWB * kNB * 64; e += 64 * kRowsWaves) {
+        const int l = e & 63, j = (e >> 6) % kNB, i = (e >> 6) / kNB;
+        floatx4 v = red[0][i][j][l];
+#pragma unroll
+        for (int w = 1; w < kRowsWaves; ++w) v += red[w][i][j][l];
+        const int32_t n = n0 + 16 * j + (l & 15), k = k0 + 16 * i + 4 * (l >> 4);
+        if (n >= N) continue;
+        float *out = splits > 1 ? part + ((size_t)sp * N + n) * K : S + (size_t)n * K;
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            if (k + t < K) out[k + t] = splits > 1 ? v[t] : v[t] + bias[k + t];
+    }
+}
+
+// One workgroup per row, for few rows: as k_reduce_argmax (splits > 1: the
+// partials summed in split order, the bias added, S written) or k_argmax
+// (splits == 1: S read), with 1024 lanes on a row and every partial of an
+// identity in flight at once. A wave per row (k_argmax, k_reduce_argmax) walks
+// the row in dependent steps of memory latency, which pays only once there are
+// rows enough to fill the GPU with waves.
+__global__ __launch_bounds__(1024) void k_row_argmax(const float *__restrict__ part, int32_t splits,
+                                                     int32_t N, int32_t K,
+                                                     const float *__restrict__ bias,
+                                                     float *__restrict__ S,
+                                                     int32_t *__restrict__ out,
+                                                     const int32_t *__restrict__ n_dev) {
+    __shared__ float sv[16];
+    __shared__ int32_t sa[16];
+    const int32_t n = blockIdx.x;
+    if (n_dev && n >= *n_dev) return;  // uniform
+    const size_t plane = (size_t)N * K, row = (size_t)n * K;
+    float best = -INFINITY;
+    int32_t arg = K;  // larger than any valid index
+    for (int32_t k = threadIdx.x; k < K; k += blockDim.x) {
+        float v;
+        if (splits > 1) {
+            float p[kRowsMaxSplits];
+#pragma unroll
+            for (int q = 0; q < kRowsMaxSplits; ++q)
+                p[q] = part[(size_t)min(q, splits - 1) * plane + row + k];
+            const float bk = bias[k];
+            v = p[0];
+#pragma unroll
+            for (int q = 1; q < kRowsMaxSplits; ++q)
+                if (q < splits) v += p[q];  // uniform
+            v += bk;
+            S[row + k] = v;
+        } else {
+            v = S[row + k];
+        }
+        if (v > best || arg == K) {
+            best = v;
+            arg = k;
+        }
+    }
+    if (!out) return;
+    auto take = [&](float ob, int32_t oa) {
+        if (ob > best || (ob == best && oa < arg)) {
+            best = ob;
+            arg = oa;
+        }
+    };
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        const float ob = __shfl_xor(best, off, 64);
+        const int32_t oa = __shfl_xor(arg, off, 64);
+        take(ob, oa);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        sv[threadIdx.x >> 6] = best;
+        sa[threadIdx.x >> 6] = arg;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < (int)(blockDim.x >> 6); ++w) take(sv[w], sa[w]);
+        out[n] = arg;
+    }
+}
+
 }  // namespace
 
 // Identities per tile of the split kernel. On the 4096 x 256 x 7552 product
@@ -452,7 +617,30 @@ __global__ __launch_bounds__(256) void k_reduce_argmax(const float *__restrict__
 // in 171-176 us.
 constexpr int kSplitTK = 128;
 
+// Products of few rows (at most 32) or of few 64 x 32 blocks (at most one per
+// CU) run k_score_f32_rows: below the line a call's time is W's one pass, above
+// it the blocks' own operand traffic passes that of the 128 x 128 tiles. Whole
+// calls, rows against tiles, D = 7552: 5 x 1024 15 us against 130, 32 x 8192 85
+// against 169, 64 x 8192 (256 blocks) 139 against 171, 128 x 8192 (512) 251
+// against 170, 512 x 1024 (256) 130 against 139, 1024 x 1024 (512) 245 against
+// 150, 1024 x 256 (128) 74 against 132, 2048 x 256 (256) 132 against 135.
+static bool few_rows(int32_t N, int32_t K, int32_t D, int32_t num_cus) {
+    return D % 4 == 0 &&
+           (N <= 32 || (int64_t)((N + 63) / 64) * ((K + 31) / 32) <= (int64_t)num_cus);
+}
+// 16-row blocks of X per workgroup of k_score_f32_rows.
+static int32_t rows_blocks(int32_t N) { return N <= 16 ? 1 : (N <= 32 ? 2 : 4); }
+
 int32_t score_f32_splits(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_t part_elems) {
+    if (few_rows(N, K, D, num_cus)) {
+        // Two workgroups a CU, each wave with at least four 32-column steps.
+        const int32_t nb = 16 * rows_blocks(N);
+        const int64_t groups = (int64_t)((K + 31) / 32) * ((N + nb - 1) / nb);
+        int64_t sp = std::min<int64_t>({(2 * (int64_t)num_cus + groups - 1) / groups, kRowsMaxSplits,
+                                        std::max(1, (D + 31) / 32 / (4 * kRowsWaves)),
+                                        (int64_t)(part_elems / ((size_t)N * (size_t)K))});
+        return (int32_t)std::max<int64_t>(sp, 1);
+    }
     const int64_t tiles = (int64_t)((N + 127) / 128) * ((K + kSplitTK - 1) / kSplitTK);
     int32_t best = 1;
     for (int32_t sp = 2; sp <= 4; sp *= 2) {
@@ -466,16 +654,9 @@ int32_t score_f32_splits(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_
 
 hipError_t launch_score_f32(const float *X, int32_t N, const float *W, const float *b, int32_t K,
                             int32_t D, float *S, int32_t *argmax, hipStream_t s, int32_t splits,
-                            float *part, const int32_t *n_dev) {
+                            float *part, const int32_t *n_dev, bool one_order) {
     if (N <= 0 || K <= 0) return hipSuccess;
     const bool aligned = ((uintptr_t)X % 16 == 0) && ((uintptr_t)W % 16 == 0);
-    // Unsplit products whose tiles fill the CUs in fewer rounds as 128 x 256:
-    // 256 identities per tile (48 KB stages, two-stage ring, one workgroup of
-    // 434 registers a lane per CU), 4/3 the matrix work per copied byte of the
-    // 128 x 128 tile. A round of 128 x 256 tiles takes about 1.91 rounds of
-    // 128 x 128 ones (16384 x 1024 x 7552: 1858 us in 2 rounds against
-    // 1941-1947 in 4), so the wide tile is taken when 1.91 r256 < r128 (on
-    // 5120 x 5120 x 7552, 4 wide rounds against 7: 3.8 ms against 3.45).
     int cus = 256;
     {
         int dev = 0;
@@ -483,6 +664,29 @@ hipError_t launch_score_f32(const float *X, int32_t N, const float *W, const flo
             (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         cus = std::max(cus, 1);
     }
+    if (!one_order && aligned && splits >= 1 && few_rows(N, K, D, cus) && (splits == 1 || part)) {
+        const int32_t nb = rows_blocks(N);
+        const dim3 g((K + 31) / 32, (N + 16 * nb - 1) / (16 * nb), splits);
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, g, dim3(64 * kRowsWaves), 0, s, X, N, W, b, K, D, S, splits,
+                               part, n_dev);
+        };
+        const bool tail = D % 32 != 0;
+        if (nb == 1) tail ? go(k_score_f32_rows<1, true>) : go(k_score_f32_rows<1, false>);
+        else if (nb == 2) tail ? go(k_score_f32_rows<2, true>) : go(k_score_f32_rows<2, false>);
+        else tail ? go(k_score_f32_rows<4, true>) : go(k_score_f32_rows<4, false>);
+        if (splits > 1 || argmax)
+            hipLaunchKernelGGL(k_row_argmax, dim3(N), dim3(K > 512 ? 1024 : 256), 0, s, part, splits, N, K, b, S,
+                               argmax, n_dev);
+        return hipGetLastError();
+    }
+    // Unsplit products whose tiles fill the CUs in fewer rounds as 128 x 256:
+    // 256 identities per tile (48 KB stages, two-stage ring, one workgroup of
+    // 434 registers a lane per CU), 4/3 the matrix work per copied byte of the
+    // 128 x 128 tile. A round of 128 x 256 tiles takes about 1.91 rounds of
+    // 128 x 128 ones (16384 x 1024 x 7552: 1858 us in 2 rounds against
+    // 1941-1947 in 4), so the wide tile is taken when 1.91 r256 < r128 (on
+    // 5120 x 5120 x 7552, 4 wide rounds against 7: 3.8 ms against 3.45).
     const size_t nt = (size_t)((N + 127) / 128);
     const size_t r128 = (nt * (size_t)((K + 127) / 128) + cus - 1) / cus;
     const size_t r256 = (nt * (size_t)((K + 255) / 256) + cus - 1) / cus;

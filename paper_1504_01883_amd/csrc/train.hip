@@ -598,7 +598,7 @@ hipError_t launch_train_gram(const float *X, const int32_t *labels, int32_t N, i
     float *al = alpha ? alpha : G0 + kn;
     const dim3 blk(256), rows((N + 255) / 256);
     hipLaunchKernelGGL(k_gram_zero, rows, blk, 0, s, zeros, N);
-    hipError_t e = launch_score_f32(X, N, X, zeros, N, D, G, nullptr, s, 1, nullptr);
+    hipError_t e = launch_score_f32(X, N, X, zeros, N, D, G, nullptr, s, 1, nullptr, nullptr, true);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_gram_diag, rows, blk, 0, s, G, N, norms);
     hipLaunchKernelGGL(k_gram_sigma, rows, blk, 0, s, norms, N, sigma);
@@ -607,7 +607,8 @@ hipError_t launch_train_gram(const float *X, const int32_t *labels, int32_t N, i
     if (w) {
         hipLaunchKernelGGL(k_gram_alpha_y, dim3((unsigned)((kn + 255) / 256)), blk, 0, s, alpha,
                            labels, N, K, A);
-        if ((e = launch_score_f32(A, K, G, zeros, N, N, G0, nullptr, s, 1, nullptr)) != hipSuccess)
+        if ((e = launch_score_f32(A, K, G, zeros, N, N, G0, nullptr, s, 1, nullptr, nullptr,
+                                  true)) != hipSuccess)
             return e;
     }
     GramArgs a{G, labels, sigma, w ? G0 : nullptr, N, K, C, eps, max_epochs, seed, al, b, epochs};
