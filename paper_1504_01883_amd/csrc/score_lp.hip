@@ -17,12 +17,14 @@
 // to 8192 values are quantised by k_quant_rows_vec in one read (the row held
 // in registers, vector stores), longer ones by k_quant_rows.
 //
-// Large products (N >= 512, K >= 256) run k_score_lp_big (256 x 256 tiles
+// Products of few tiles run k_score_lp_rows (operands straight to registers).
+//
+// Other large products (N >= 512, K >= 256) run k_score_lp_big (256 x 256 tiles
 // through an LDS ring, described there), whose epilogue also reduces each
 // row's best identity over the tile; k_argmax_tiles merges the tiles, so an
 // argmax-only call never writes S.
 //
-// Small products, GEMM: a workgroup of 4 wave64 owns a 256 (n) x 128 (k) tile of S; wave w
+// The others: a workgroup of 4 wave64 owns a 256 (n) x 128 (k) tile of S; wave w
 // owns rows 128 (w & 1) .. +128 and columns 64 (w >> 1) .. +64 as 4 x 2
 // blocks of 32 x 32 (v_mfma_f32_32x32x16_{bf16,f16} or
 // v_mfma_f32_32x32x64_f8f6f4). Per k-stage of 128 bytes per row the
@@ -159,33 +161,41 @@ __global__ __launch_bounds__(256) void k_quant_rows(const float *__restrict__ X,
     }
 }
 
-// One wave per row, four rows per workgroup, for rows of D <= 256 kC values
-// with D % 4 == 0 and 16-byte aligned rows: the row is read once into
+// kRW waves per row (1 or 4), 4 / kRW rows per workgroup, for rows of
+// D <= 256 kRW kC values with D % 4 == 0 and 16-byte aligned rows: the row is read once into
 // registers (float4 per lane and chunk), its amax reduced over the wave, and
 // the converted values stored as one 8-byte (BF16, FP16) or 4-byte (FP8)
 // vector per float4; the pad up to `pitch` is zeroed. Same values and scales
 // as k_quant_rows.
-template <int kMode, int kC>
+template <int kMode, int kC, int kRW>
 __global__ __launch_bounds__(256) void k_quant_rows_vec(const float *__restrict__ X, int32_t rows,
                                                         int32_t D, int32_t pitch,
                                                         uint8_t *__restrict__ out,
                                                         float *__restrict__ scales,
                                                         const int32_t *__restrict__ n_dev) {
-    const int lane = threadIdx.x & 63;
-    const int32_t r = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (r >= (n_dev ? *n_dev : rows)) return;
+    constexpr int kL = 64 * kRW;  // lanes of a row
+    __shared__ float part[4];
+    const int lane = threadIdx.x % kL;
+    const int32_t r = blockIdx.x * (4 / kRW) + threadIdx.x / kL;
+    if (r >= (n_dev ? *n_dev : rows)) return;  // uniform over a row's waves
     const int nq = D >> 2;
     const f32x4 *x = reinterpret_cast<const f32x4 *>(X + (size_t)r * D);
     f32x4 v[kC];
     float amax = 0.0f;
 #pragma unroll
     for (int c = 0; c < kC; ++c) {
-        const int q = c * 64 + lane;
+        const int q = c * kL + lane;
         v[c] = q < nq ? __builtin_nontemporal_load(x + q) : f32x4{0.f, 0.f, 0.f, 0.f};
         amax = fmaxf(amax, fmaxf(fmaxf(fabsf(v[c].x), fabsf(v[c].y)),
                                  fmaxf(fabsf(v[c].z), fabsf(v[c].w))));
     }
     amax = wave_max(amax);
+    if constexpr (kRW > 1) {  // one row a workgroup
+        static_assert(kRW == 4, "the workgroup's waves share one row");
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = amax;
+        __syncthreads();
+        amax = fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
+    }
     uint8_t *o = out + (size_t)r * pitch;
     constexpr int kEB = kMode == LBPF_FP8_E4M3 ? 1 : 2;
     if constexpr (kMode == LBPF_F16X3 || kMode == kF16X3W) {
@@ -204,7 +214,7 @@ __global__ __launch_bounds__(256) void k_quant_rows_vec(const float *__restrict_
         };
 #pragma unroll
         for (int c = 0; c < kC; ++c) {
-            const int q = c * 64 + lane;
+            const int q = c * kL + lane;
             if (q < nq) {
                 uint32_t h0, h1, h2, h3, l0, l1, l2, l3;
                 split(v[c].x, h0, l0);
@@ -218,7 +228,7 @@ __global__ __launch_bounds__(256) void k_quant_rows_vec(const float *__restrict_
             }
         }
         // Zero pad every segment past D (segments are multiples of 128 bytes).
-        for (int q = nq + lane; q < seg / 8; q += 64) {
+        for (int q = nq + lane; q < seg / 8; q += kL) {
             *reinterpret_cast<uint2 *>(o + 8 * q) = uint2{0u, 0u};
             *reinterpret_cast<uint2 *>(o + seg + 8 * q) = uint2{0u, 0u};
             if constexpr (kMode == kF16X3W) *reinterpret_cast<uint2 *>(o + 2 * seg + 8 * q) = uint2{0u, 0u};
@@ -231,7 +241,7 @@ __global__ __launch_bounds__(256) void k_quant_rows_vec(const float *__restrict_
         if (lane == 0) scales[r] = s;
 #pragma unroll
         for (int c = 0; c < kC; ++c) {
-            const int q = c * 64 + lane;
+            const int q = c * kL + lane;
             if (q < nq) {
                 // The packed hardware conversion (OCP e4m3, round to nearest
                 // even). Over every float below 464 in magnitude it gives the
@@ -263,7 +273,7 @@ __global__ __launch_bounds__(256) void k_quant_rows_vec(const float *__restrict_
         };
 #pragma unroll
         for (int c = 0; c < kC; ++c) {
-            const int q = c * 64 + lane;
+            const int q = c * kL + lane;
             if (q < nq) {
                 const uint32_t lo = cvt(v[c].x) | (cvt(v[c].y) << 16);
                 const uint32_t hi = cvt(v[c].z) | (cvt(v[c].w) << 16);
@@ -273,7 +283,7 @@ __global__ __launch_bounds__(256) void k_quant_rows_vec(const float *__restrict_
     }
     // Zero pad: elements D .. pitch / kEB - 1, four at a time (pitch is a
     // multiple of 128 bytes and D of 4).
-    for (int q = nq + lane; q < pitch / (4 * kEB); q += 64) {
+    for (int q = nq + lane; q < pitch / (4 * kEB); q += kL) {
         if constexpr (kEB == 1) *reinterpret_cast<uint32_t *>(o + 4 * q) = 0u;
         else *reinterpret_cast<uint2 *>(o + 8 * q) = uint2{0u, 0u};
     }
@@ -420,6 +430,104 @@ __global__ __launch_bounds__(256) void k_score_lp(const uint8_t *__restrict__ Xq
                 const int32_t n = n0 + wm * 128 + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
                 if (n < N) S[(size_t)n * K + k] = (sx[n] * swk) * acc[i][j][r] + bk;
             }
+    }
+}
+
+// --- GEMM, few tiles -------------------------------------------------------------
+//
+// For products whose 256-wide tiles leave most CUs idle (a serving batch of 256
+// rows x 1024 identities is 4 tiles of 256 x 256, each 118 serial stages). A
+// workgroup of 8 wave64 owns 32 kNB feature rows x 32 kKB identities; its waves
+// take the 64-byte steps of the reduction in turn (step s by wave s % 8), each
+// with its operands straight from global memory in registers, and meet in LDS
+// in wave order. Lane (l % 32, l / 32) of an operand block holds bytes
+// 32 (l / 32) .. + 31 of its row's step, for both operands alike. Bound by the
+// operand traffic between L2 and the CUs: 256 x 1024 in BF16 moves 248 MB in
+// about 25 us, 10 TB/s (198 us on the 256 x 256 tiles); 16 waves a workgroup, or
+// four steps in flight a wave instead of one, change nothing. Weights are the first operand: a lane
+// then holds four consecutive identities of one feature row.
+constexpr int kRowsWaves = 8;
+
+template <int kMode, int kNB, int kKB>
+__global__ __launch_bounds__(64 * kRowsWaves) void k_score_lp_rows(
+    const uint8_t *__restrict__ Xq, const float *__restrict__ sx, int32_t N,
+    const uint8_t *__restrict__ Wq, const float *__restrict__ sw, const float *__restrict__ bias,
+    int32_t K, int32_t pitch, float *__restrict__ S, const int32_t *__restrict__ n_dev,
+    int32_t a_pitch, int32_t a_seg) {
+    __shared__ f32x4 red[kRowsWaves][kNB * kKB * 4][64];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: scalar steps
+    const int fr = lane & 31, fq = lane >> 5;
+    const int32_t n0 = blockIdx.y * 32 * kNB, k0 = blockIdx.x * 32 * kKB;
+    if (n_dev) N = *n_dev;
+    if (n0 >= N) return;  // uniform
+    const uint8_t *xp[kNB], *wp[kKB];
+#pragma unroll
+    for (int i = 0; i < kNB; ++i)
+        xp[i] = Xq + (size_t)min(n0 + 32 * i + fr, N - 1) * a_pitch + 32 * fq;
+#pragma unroll
+    for (int j = 0; j < kKB; ++j)
+        wp[j] = Wq + (size_t)min(k0 + 32 * j + fr, K - 1) * pitch + 32 * fq;
+    f32x16 acc[kNB][kKB];
+#pragma unroll
+    for (int i = 0; i < kNB; ++i)
+#pragma unroll
+        for (int j = 0; j < kKB; ++j) acc[i][j] = f32x16{};
+    const int32_t steps = pitch / 64;
+    for (int32_t s = wave; s < steps; s += kRowsWaves) {
+        const int32_t kb = 64 * s, kba = (a_seg && kb >= a_seg) ? kb - a_seg : kb;
+        u32x4 a[kNB][2], b[kKB][2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int i = 0; i < kNB; ++i)
+                a[i][h] = *reinterpret_cast<const u32x4 *>(xp[i] + kba + 16 * h);
+#pragma unroll
+            for (int j = 0; j < kKB; ++j)
+                b[j][h] = *reinterpret_cast<const u32x4 *>(wp[j] + kb + 16 * h);
+        }
+        constexpr int kSubs = (kMode == LBPF_FP8_E4M3) ? 1 : 2;
+#pragma unroll
+        for (int sub = 0; sub < kSubs; ++sub)
+#pragma unroll
+            for (int i = 0; i < kNB; ++i)
+#pragma unroll
+                for (int j = 0; j < kKB; ++j)
+                    acc[i][j] = mfma_step<kMode>(b[j], a[i], acc[i][j], sub);
+    }
+    // Register 4 g + t of lane l: identity 8 g + 4 (l / 32) + t, row l % 32.
+#pragma unroll
+    for (int i = 0; i < kNB; ++i)
+#pragma unroll
+        for (int j = 0; j < kKB; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                red[wave][(i * kKB + j) * 4 + g][lane] =
+                    f32x4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2],
+                          acc[i][j][4 * g + 3]};
+    __syncthreads();
+    const bool vec = (K & 3) == 0 && ((uintptr_t)S & 15) == 0;
+    for (int e = threadIdx.x; e < kNB * kKB * 4 * 64; e += 64 * kRowsWaves) {
+        const int l = e & 63, c = e >> 6;
+        f32x4 v = red[0][c][l];
+#pragma unroll
+        for (int w = 1; w < kRowsWaves; ++w) v += red[w][c][l];
+        const int32_t n = n0 + 32 * (c / (4 * kKB)) + (l & 31);
+        const int32_t k = k0 + 32 * ((c / 4) % kKB) + 8 * (c & 3) + 4 * (l >> 5);
+        if (n >= N || k >= K) continue;
+        const float sxn = sx[n];
+        float *out = S + (size_t)n * K + k;
+        if (vec) {
+            const f32x4 swk = *reinterpret_cast<const f32x4 *>(sw + k);
+            const f32x4 bk = *reinterpret_cast<const f32x4 *>(bias + k);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) v[t] = (sxn * swk[t]) * v[t] + bk[t];
+            *reinterpret_cast<f32x4 *>(out) = v;
+        } else {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (k + t < K) out[t] = (sxn * sw[k + t]) * v[t] + bias[k + t];
+        }
     }
 }
 
@@ -807,6 +915,10 @@ __global__ __launch_bounds__(256) void k_argmax_tiles(const float *__restrict__ 
 // float4 chunks per lane of the register-resident quantiser: rows up to
 // 8192 values.
 constexpr int kQuantChunks = 32;
+// Up to this many rows a workgroup of four waves quantises each row: a wave per
+// row leaves CUs idle (whole FP8 calls, 256 x 1024: 27.3 us against 29.6; from
+// 2048 rows on the two are level, at 16384 the wave is 1% ahead).
+constexpr int32_t kQuantGroupRows = 1024;
 
 int32_t lp_seg(int32_t D) { return (2 * D + kRowB - 1) / kRowB * kRowB; }
 
@@ -826,32 +938,59 @@ hipError_t launch_quant_rows(const float *X, int32_t rows, int32_t D, int32_t mo
     // Split rows: weight rows hold three segments, feature rows two.
     const int32_t qmode = (mode == LBPF_F16X3 && weights) ? kF16X3W : mode;
     const int32_t pitch = weights ? lp_pitch(D, mode) : lp_pitch_features(D, mode);
-    auto go = [&](auto vec_kernel, auto row_kernel) {
-        if (D % 4 == 0 && D <= 256 * kQuantChunks && ((uintptr_t)X & 15) == 0)
-            hipLaunchKernelGGL(vec_kernel, dim3((rows + 3) / 4), dim3(256), 0, s, X, rows, D,
+    auto go = [&](auto wave_kernel, auto group_kernel, auto row_kernel) {
+        const bool vec = D % 4 == 0 && D <= 256 * kQuantChunks && ((uintptr_t)X & 15) == 0;
+        if (vec && rows > kQuantGroupRows)
+            hipLaunchKernelGGL(wave_kernel, dim3((rows + 3) / 4), dim3(256), 0, s, X, rows, D,
                                pitch, out, scales, n_dev);
+        else if (vec)
+            hipLaunchKernelGGL(group_kernel, dim3(rows), dim3(256), 0, s, X, rows, D, pitch, out,
+                               scales, n_dev);
         else
             hipLaunchKernelGGL(row_kernel, dim3(rows), dim3(256), 0, s, X, rows, D, pitch, out,
                                scales, n_dev);
     };
+    constexpr int kC = kQuantChunks;
     switch (qmode) {
         case LBPF_BF16:
-            go(k_quant_rows_vec<LBPF_BF16, kQuantChunks>, k_quant_rows<LBPF_BF16>);
+            go(k_quant_rows_vec<LBPF_BF16, kC, 1>, k_quant_rows_vec<LBPF_BF16, kC / 4, 4>,
+               k_quant_rows<LBPF_BF16>);
             break;
         case LBPF_FP16:
-            go(k_quant_rows_vec<LBPF_FP16, kQuantChunks>, k_quant_rows<LBPF_FP16>);
+            go(k_quant_rows_vec<LBPF_FP16, kC, 1>, k_quant_rows_vec<LBPF_FP16, kC / 4, 4>,
+               k_quant_rows<LBPF_FP16>);
             break;
         case LBPF_FP8_E4M3:
-            go(k_quant_rows_vec<LBPF_FP8_E4M3, kQuantChunks>, k_quant_rows<LBPF_FP8_E4M3>);
+            go(k_quant_rows_vec<LBPF_FP8_E4M3, kC, 1>, k_quant_rows_vec<LBPF_FP8_E4M3, kC / 4, 4>,
+               k_quant_rows<LBPF_FP8_E4M3>);
             break;
         case LBPF_F16X3:
-            go(k_quant_rows_vec<LBPF_F16X3, kQuantChunks>, k_quant_rows<LBPF_F16X3>);
+            go(k_quant_rows_vec<LBPF_F16X3, kC, 1>, k_quant_rows_vec<LBPF_F16X3, kC / 4, 4>,
+               k_quant_rows<LBPF_F16X3>);
             break;
         default:
-            go(k_quant_rows_vec<kF16X3W, kQuantChunks>, k_quant_rows<kF16X3W>);
+            go(k_quant_rows_vec<kF16X3W, kC, 1>, k_quant_rows_vec<kF16X3W, kC / 4, 4>,
+               k_quant_rows<kF16X3W>);
             break;
     }
     return hipGetLastError();
+}
+
+// Side of k_score_lp_rows' tile for a product, 0 for the 256-wide tile kernels.
+// 32 x 32 tiles up to two per CU of this GPU (and for up to 32 rows, where W is
+// read once anyway), then 64 x 64 tiles up to two per CU, beyond which the
+// 256-wide tiles' lower operand traffic wins. At two tiles of 32 a CU the two
+// sides are level; a pipeline's batch that fills half its rows then runs half
+// of them at once (256 of 512 rows x 1024, BF16: 61 us on the 64 side). Whole calls in us, 32 / 64 / 256-wide
+// tiles, BF16: 256 x 1024 42 / 71 / 176, 512 x 1024 70 / 73 / 210, 1024 x 1024
+// 126 / 78 / 213, 2048 x 1024 (512 tiles of 64) 241 / 143 / 221, 4096 x 1024
+// (1024) 473 / 275 / 242, 32 x 8192 44 / 62 / 161, 256 x 8192 (512) 248 / 132 /
+// 180, 512 x 8192 (1024) 483 / 244 / 217; FP8 512 x 8192 245 / 131 / 125, split
+// FP16 2048 x 1024 672 / 373 / 593 and 4096 x 1024 1340 / 738 / 616.
+static int rows_side(int32_t N, int32_t K) {
+    auto tiles = [&](int64_t t) { return ((N + t - 1) / t) * ((K + t - 1) / t); };
+    if (N <= 32 || tiles(32) <= 512) return 32;
+    return tiles(64) <= 512 ? 64 : 0;
 }
 
 hipError_t launch_score_lp(const uint8_t *Xq, const float *sx, int32_t N, const uint8_t *Wq,
@@ -862,6 +1001,25 @@ hipError_t launch_score_lp(const uint8_t *Xq, const float *sx, int32_t N, const 
     const int32_t pitch = lp_pitch(D, mode);  // reduction bytes per row (weights)
     const int32_t a_pitch = lp_pitch_features(D, mode);
     const int32_t a_seg = mode == LBPF_F16X3 ? lp_seg(D) : 0;
+    const int side = rows_side(N, K);
+    if (side && (S || (size_t)N * (size_t)K <= scratch_elems)) {
+        float *Sout = S ? S : scratch;
+        const dim3 grid((K + side - 1) / side, (N + side - 1) / side);
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, grid, dim3(64 * kRowsWaves), 0, s, Xq, sx, N, Wq, sw, b, K,
+                               pitch, Sout, n_dev, a_pitch, a_seg);
+        };
+        if (mode == LBPF_BF16)
+            side == 32 ? go(k_score_lp_rows<LBPF_BF16, 1, 1>) : go(k_score_lp_rows<LBPF_BF16, 2, 2>);
+        else if (mode == LBPF_FP8_E4M3)
+            side == 32 ? go(k_score_lp_rows<LBPF_FP8_E4M3, 1, 1>)
+                     : go(k_score_lp_rows<LBPF_FP8_E4M3, 2, 2>);
+        else  // FP16 and split FP16
+            side == 32 ? go(k_score_lp_rows<LBPF_FP16, 1, 1>) : go(k_score_lp_rows<LBPF_FP16, 2, 2>);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess || !argmax) return e;
+        return launch_argmax(Sout, N, K, argmax, s, n_dev);
+    }
     if (N >= 2 * kBigT && K >= kBigT) {
         // Large products: 256 x 256 tiles fed through the LDS ring, the
         // argmax taken in the epilogue (per tile) when its pairs fit the
@@ -886,7 +1044,7 @@ hipError_t launch_score_lp(const uint8_t *Xq, const float *sx, int32_t N, const 
                            argmax, n_dev);
         return hipGetLastError();
     }
-    // Small products. Without S the scores go through the scratch, in row
+    // Few rows or identities. Without S the scores go through the scratch, in row
     // blocks that fit it (one block when the row count is on the device).
     int32_t blk = N;
     if (!S) {
