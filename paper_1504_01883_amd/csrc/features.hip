@@ -16,19 +16,22 @@
 // Kernels:
 //   k_features_fast       -- the default configuration (uniform-59 bins, both
 //                            channels, window 1..255 mm), one workgroup per
-//                            crop. Crops up to 256 px wide take the lane path
-//                            below; wider crops (and crops whose median lies
-//                            within the window of 0) the per-pixel loop,
-//                            inside the same launch.
+//                            crop. Crops up to 256 px wide in one panel of the
+//                            lane path below, wider ones in several; crops
+//                            whose median lies within the window of 0 pixel by
+//                            pixel, inside the same launch.
 //   k_features_persistent -- the same per crop, a fixed grid taking crops
 //                            from a self-resetting work queue (ragged batches).
-//   k_features_generic    -- every other configuration (256 bins, one
-//                            channel, mask off, wide windows).
+//   k_split_*             -- the same configuration, several workgroups per
+//                            crop, for few or large crops.
+//   k_features_any        -- every other configuration (256 bins, one channel,
+//                            mask off, wide windows, coarse grids).
 //
 // Default configuration, per crop:
 //   * Median: the four waves each estimate it from 64 pixels of a 16 x 16
 //     sampling grid; one pass over the crop then histograms the 64 mm window
-//     centred on the combined estimate (1 mm bins, LDS atomics) and counts
+//     (where several workgroups share a crop, a wider one if the estimates
+//     disagree) around the combined estimate (1 mm bins, LDS atomics) and counts
 //     non-zero pixels and pixels above the window's start in packed 16-bit
 //     registers; when the median falls in the window the histogram gives
 //     it, otherwise an exact two-level radix select (high byte, then low
@@ -78,22 +81,6 @@ __device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a),
                                                                   __builtin_bit_cast(u16x2, b)));
 }
-__device__ __forceinline__ uint32_t ld_u32(const void *p) {
-    uint32_t v;
-    __builtin_memcpy(&v, p, 4);
-    return v;
-}
-__device__ __forceinline__ uint2 ld_u64(const void *p) {
-    uint2 v;
-    __builtin_memcpy(&v, p, 8);
-    return v;
-}
-__device__ __forceinline__ uint4 ld_u128(const void *p) {
-    uint4 v;
-    __builtin_memcpy(&v, p, 16);
-    return v;
-}
-
 __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v, int lane) {
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
@@ -113,7 +100,7 @@ struct MedianScratch {
     uint32_t hist[256];
     int32_t bin;
     uint32_t rank;
-    uint32_t est[kWaves];  // the waves' median estimates
+    uint32_t est[4];  // median estimates of the first four waves
 };
 
 // On wave 0: find the bin of a 256-bin LDS histogram that holds 0-based rank
@@ -145,78 +132,6 @@ __device__ __forceinline__ void select_bin(MedianScratch &ms, uint32_t rank, int
     }
 }
 
-// Load the 8 depth pixels x0..x0+7 of a row (zeros past the crop's width).
-__device__ __forceinline__ void load8(const uint16_t *row, int x0, int w, uint32_t v[8]) {
-    if (x0 + 8 <= w) {
-        const uint4 q = ld_u128(row + x0);
-        v[0] = q.x & 0xFFFFu; v[1] = q.x >> 16;
-        v[2] = q.y & 0xFFFFu; v[3] = q.y >> 16;
-        v[4] = q.z & 0xFFFFu; v[5] = q.z >> 16;
-        v[6] = q.w & 0xFFFFu; v[7] = q.w >> 16;
-    } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = (x0 + i < w) ? row[x0 + i] : 0u;
-    }
-}
-
-// Exact lower median of the non-zero depth values of the crop, -1 if none.
-// All threads of the block call it.
-__device__ __noinline__ int32_t crop_median(const CropDesc c, MedianScratch &ms) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int cpr = (c.w + 7) >> 3;              // 8-pixel chunks per row (<= 128)
-    const int rows_par = kThreads / cpr;         // rows visited in parallel
-    const int cx = tid % cpr, ry0 = tid / cpr;
-    const bool act = ry0 < rows_par;
-    for (int i = tid; i < 256; i += kThreads) ms.hist[i] = 0;
-    __syncthreads();
-    if (act) {
-        for (int y = ry0; y < c.h; y += rows_par) {
-            uint32_t v[8];
-            load8(c.depth + (size_t)y * c.depth_pitch, 8 * cx, c.w, v);
-            const uint32_t key = (v[3] ? v[3] : v[4]) >> 8;
-            uint32_t same = 0;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) same += (v[i] != 0 && (v[i] >> 8) == key) ? 1u : 0u;
-            if (same) atomicAdd(&ms.hist[key], same);
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (v[i] != 0 && (v[i] >> 8) != key) atomicAdd(&ms.hist[v[i] >> 8], 1u);
-        }
-    }
-    __syncthreads();
-    if (wave == 0) {
-        const uint32_t tot = wave_sum(ms.hist[4 * lane] + ms.hist[4 * lane + 1] +
-                                      ms.hist[4 * lane + 2] + ms.hist[4 * lane + 3]);
-        if (tot > 0) {
-            select_bin(ms, (tot - 1) / 2, lane);
-        } else if (lane == 0) {
-            ms.bin = -1;
-        }
-    }
-    __syncthreads();
-    const int32_t hi = ms.bin;
-    const uint32_t rank_in_hi = ms.rank;
-    if (hi < 0) return -1;
-    __syncthreads();
-    for (int i = tid; i < 256; i += kThreads) ms.hist[i] = 0;
-    __syncthreads();
-    if (act) {
-        for (int y = ry0; y < c.h; y += rows_par) {
-            uint32_t v[8];
-            load8(c.depth + (size_t)y * c.depth_pitch, 8 * cx, c.w, v);
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (v[i] != 0 && (int32_t)(v[i] >> 8) == hi) atomicAdd(&ms.hist[v[i] & 255u], 1u);
-        }
-    }
-    __syncthreads();
-    if (wave == 0) select_bin(ms, rank_in_hi, lane);
-    __syncthreads();
-    const int32_t m = (hi << 8) | ms.bin;
-    __syncthreads();
-    return m;
-}
-
 __device__ __forceinline__ bool centre_in_mask(uint32_t d, int32_t m, int32_t window) {
     if (window <= 0) return true;
     if (m < 0 || d == 0) return false;
@@ -234,41 +149,6 @@ __device__ __forceinline__ uint32_t lbp_code(const T *p, int32_t pitch, int y, i
         code |= (g >= c ? 1u : 0u) << k;
     }
     return code;
-}
-
-// Per-pixel histogram loop for any crop and configuration: each thread takes
-// pixels in row order and increments its bins with LDS atomics.
-// With `packed` (both channels in use) the counters are the fast path's: one
-// word per (cell, bin), grey count in the low half, depth count in the high.
-template <int kNW = kWaves>
-__device__ void lbp_hist_generic(const CropDesc c, const FeatParams &fp, int32_t m,
-                                 const uint8_t *sh_bin, const uint8_t *sh_rowband,
-                                 const uint8_t *sh_colband, uint32_t *sh_hist,
-                                 bool packed = false) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int cells = fp.grid_x * fp.grid_y;
-    const int nb = fp.nbins;
-    for (int y = 1 + wave; y <= c.h - 2; y += kNW) {
-        const int rowcell = sh_rowband[y] * fp.grid_x;
-        for (int x = 1 + lane; x <= c.w - 2; x += 64) {
-            const uint32_t dc = c.depth[(size_t)y * c.depth_pitch + x];
-            if (!centre_in_mask(dc, m, fp.window)) continue;
-            const int cell = rowcell + sh_colband[x];
-            int ch = 0;
-            if (fp.use_grey) {
-                const uint32_t code = lbp_code(c.grey, c.grey_pitch, y, x);
-                atomicAdd(&sh_hist[cell * nb + sh_bin[code]], 1u);
-                ch = 1;
-            }
-            if (fp.use_depth) {
-                const uint32_t code = lbp_code(c.depth, c.depth_pitch, y, x);
-                if (packed)
-                    atomicAdd(&sh_hist[cell * nb + sh_bin[code]], 0x10000u);
-                else
-                    atomicAdd(&sh_hist[(ch * cells + cell) * nb + sh_bin[code]], 1u);
-            }
-        }
-    }
 }
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -346,34 +226,128 @@ __device__ __forceinline__ u32x4 depth_chunk(const CropDesc &c, int y, int x0) {
 
 constexpr int kMedBatch = 8;  // 16-byte chunks in flight per thread
 
-// Width (mm) of the median pass's 1 mm window histogram, centred on the
-// estimate.
+// f(v) for the eight depth pixels v[8] of every chunk of the crop that falls to
+// this thread of kNT (0: no depth, or outside the crop), four chunks in flight.
+template <int kNT, typename F>
+__device__ __forceinline__ void each_chunk(const CropDesc &c, F &&f) {
+    const int cpr = (c.w + 7) >> 3;              // 8-pixel chunks per row (<= 128)
+    const int rows_par = kNT / cpr;              // rows visited in parallel
+    const int cx = threadIdx.x % cpr, ry0 = threadIdx.x / cpr;
+    const int nk = ry0 < rows_par ? max(0, (c.h - ry0 + rows_par - 1) / rows_par) : 0;
+    constexpr int kBatch = 4;  // more would cost the kernels a workgroup per CU (VGPRs)
+    for (int kb = 0; kb < nk; kb += kBatch) {
+        u32x4 buf[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+            buf[u] = depth_chunk(c, ry0 + min(kb + u, nk - 1) * rows_par, 8 * cx);
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            if (kb + u >= nk) break;
+            uint32_t v[8];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                v[2 * i] = buf[u][i] & 0xFFFFu;
+                v[2 * i + 1] = buf[u][i] >> 16;
+            }
+            f(v);
+        }
+    }
+}
+
+// The value of rank `rank` among the crop's depths in [base, base + 2^k), k <= 8.
+// All kNT threads of the block call it.
+template <int kNT>
+__device__ __forceinline__ int32_t median_refine(const CropDesc &c, MedianScratch &ms, int32_t base,
+                                              uint32_t k, uint32_t rank) {
+    for (int i = threadIdx.x; i < 256; i += kNT) ms.hist[i] = 0;
+    __syncthreads();
+    each_chunk<kNT>(c, [&](const uint32_t (&v)[8]) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (v[i] != 0 && v[i] - (uint32_t)base < (1u << k)) atomicAdd(&ms.hist[v[i] - base], 1u);
+    });
+    __syncthreads();
+    if (threadIdx.x < 64) select_bin(ms, rank, threadIdx.x);
+    __syncthreads();
+    const int32_t m = base + ms.bin;
+    __syncthreads();
+    return m;
+}
+
+// Exact lower median of the non-zero depth values of the crop by two 256-bin
+// passes (high byte, then low byte), -1 if none: for the rare crop whose median
+// the window of the estimate misses. All kNT threads of the block call it.
+template <int kNT = kThreads>
+__device__ __noinline__ int32_t crop_median(const CropDesc c, MedianScratch &ms) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int i = tid; i < 256; i += kNT) ms.hist[i] = 0;
+    __syncthreads();
+    each_chunk<kNT>(c, [&](const uint32_t (&v)[8]) {
+        // One atomic for the pixels that share the chunk's middle key.
+        const uint32_t key = (v[3] ? v[3] : v[4]) >> 8;
+        uint32_t same = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) same += (v[i] != 0 && (v[i] >> 8) == key) ? 1u : 0u;
+        if (same) atomicAdd(&ms.hist[key], same);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (v[i] != 0 && (v[i] >> 8) != key) atomicAdd(&ms.hist[v[i] >> 8], 1u);
+    });
+    __syncthreads();
+    if (wave == 0) {
+        const uint32_t tot = wave_sum(ms.hist[4 * lane] + ms.hist[4 * lane + 1] +
+                                      ms.hist[4 * lane + 2] + ms.hist[4 * lane + 3]);
+        if (tot > 0) {
+            select_bin(ms, (tot - 1) / 2, lane);
+        } else if (lane == 0) {
+            ms.bin = -1;
+        }
+    }
+    __syncthreads();
+    const int32_t hi = ms.bin;
+    const uint32_t rank_in_hi = ms.rank;
+    __syncthreads();
+    if (hi < 0) return -1;
+    return median_refine<kNT>(c, ms, hi << 8, 8, rank_in_hi);
+}
+
+// Window of the median pass: bins of 2^k mm from lo on, k = 0 and kMedWin bins
+// centred on the estimate where the four wave estimates agree within kMedAgree
+// mm; else (two surfaces of about equal share, as where boxes overlap) 256 bins
+// that span all four.
 constexpr uint32_t kMedWin = 64;
+constexpr int32_t kMedAgree = 48;
+struct MedWindow {
+    int32_t lo;
+    uint32_t k;
+    bool wide;
+};
 
 // One u16 pair of the median pass: per-half counts of v >= lo (ge2) and of
-// v != 0 (nz2), and the 1 mm window histogram of [lo, lo + kMedWin). one2
-// holds 0x10001 (kept opaque to the compiler, see crop_median_fast).
+// v != 0 (nz2), and the window's histogram. one2 holds 0x10001 (kept opaque to
+// the compiler, see median_rows).
+template <bool kWide>
 __device__ __forceinline__ void median_count(uint32_t q, uint32_t lolo, uint32_t lm1,
-                                             uint32_t one2, uint32_t &ge2, uint32_t &nz2,
+                                             uint32_t one2, uint32_t k, uint32_t &ge2, uint32_t &nz2,
                                              MedianScratch &ms) {
     // v >= lo iff v - (lo - 1) saturates above 0 (lo >= 1, so 0 is not).
     ge2 += pk_min(pk_sub_sat(q, lm1), one2);
     nz2 += pk_min(q, one2);
-    const uint32_t t = pk_sub(q, lolo);  // v - lo; >= kMedWin for v = 0
-    const uint32_t t0 = t & 0xFFFFu, t1 = t >> 16;
-    if (t0 < kMedWin) atomicAdd(&ms.hist[t0], 1u);
-    if (t1 < kMedWin) atomicAdd(&ms.hist[t1], 1u);
+    const uint32_t t = pk_sub(q, lolo);  // v - lo; past the window for v < lo
+    const uint32_t t0 = kWide ? (t & 0xFFFFu) >> k : t & 0xFFFFu, t1 = kWide ? t >> (16 + k) : t >> 16;
+    if (t0 < (kWide ? 256u : kMedWin)) atomicAdd(&ms.hist[t0], 1u);
+    if (t1 < (kWide ? 256u : kMedWin)) atomicAdd(&ms.hist[t1], 1u);
 }
 
 // End of the median pass for a block of kNW waves: totals over the block,
-// then the lower median's rank looked up in the window histogram. Returns
-// the median, -1 when the crop has no depth, -2 when the median lies outside
-// [lo, lo + kMedWin) (the caller then runs the exact radix select). All threads
-// call it; it ends with a barrier.
+// then the lower median's rank looked up in the window histogram. Returns the
+// bin, -1 when the crop has no depth, -2 when the median lies outside the window;
+// ms.rank is its rank within the bin. All threads call it; it ends with a
+// barrier.
 template <int kNW>
 __device__ __forceinline__ int32_t median_finish(MedianScratch &ms, uint32_t *sh_red,
-                                                 uint32_t ge2, uint32_t nz2, int32_t lo) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+                                                 uint32_t ge2, uint32_t nz2) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint32_t nnz = wave_sum((nz2 & 0xFFFFu) + (nz2 >> 16));
     const uint32_t below = nnz - wave_sum((ge2 & 0xFFFFu) + (ge2 >> 16));
     if (lane == 0) {
@@ -399,8 +373,17 @@ __device__ __forceinline__ int32_t median_finish(MedianScratch &ms, uint32_t *sh
     __syncthreads();
     const int32_t bin = ms.bin;
     __syncthreads();
-    (void)tid;
-    return bin >= 0 ? lo + bin : -2;
+    return bin >= 0 ? bin : -2;
+}
+
+// The median from a bin of the window (or -1, -2: see median_finish).
+template <int kNT>
+__device__ __forceinline__ int32_t median_of_bin(const CropDesc &c, MedianScratch &ms,
+                                                 const MedWindow &win, int32_t bin) {
+    if (bin == -1) return -1;
+    if (bin == -2) return crop_median<kNT>(c, ms);
+    const int32_t v = win.lo + (bin << win.k);
+    return win.k == 0 ? v : median_refine<kNT>(c, ms, v, win.k, ms.rank);
 }
 
 // One wave's 64-sample estimate of the median: the lower median of the
@@ -423,24 +406,44 @@ __device__ __forceinline__ uint32_t median_estimate(uint32_t v) {
     return lo;
 }
 
-// Exact lower median of the crop's non-zero depth, -1 if none.
-//  1. Each wave estimates it as the lower median of the non-zero values
-//     among 64 pixels of a 16 x 16 sampling grid (wave w takes the grid rows
-//     w, w + 4, ...); the estimate is the mean of the middle two of the four.
-//  2. One pass over the crop: a 1 mm histogram of the kMedWin values
-//     [lo, lo + kMedWin) centred on the estimate (LDS atomics), and
-//     per-thread counts of the non-zero pixels and of those below the window
-//     (packed 16-bit arithmetic, no atomics).
-//  3. When the median's rank falls inside the window, the window histogram
-//     gives it exactly; otherwise the two-level radix select runs.
-// All threads of the block call it.
-__device__ __forceinline__ int32_t crop_median_fast(const CropDesc &c, MedianScratch &ms,
-                                                   uint32_t *sh_red) {
+// The window from the four wave estimates (the wide one with kWide only: its
+// branch costs the kernels of large batches 1%, and their workgroups overlap
+// the rare radix select). lo >= 1, and lo + (bins << k) <= 65536,
+// so a value below lo (0 among them) wraps past the window.
+template <bool kWide>
+__device__ __forceinline__ MedWindow median_window(const MedianScratch &ms) {
+    const int32_t ea = min(ms.est[0], ms.est[1]), eb = max(ms.est[0], ms.est[1]);
+    const int32_t ec = min(ms.est[2], ms.est[3]), ed = max(ms.est[2], ms.est[3]);
+    const int32_t e0 = min(ea, ec), e3 = max(eb, ed);
+    MedWindow win;
+    win.wide = kWide && e3 - e0 > kMedAgree;
+    win.k = 0;
+    if (!win.wide) {
+        // Centred on the mean of the middle two.
+        win.lo = ((max(ea, ec) + min(eb, ed)) >> 1) - (int32_t)kMedWin / 2;
+        win.lo = min(max(win.lo, 1), 65536 - (int32_t)kMedWin);
+    } else {
+        win.lo = max(e0 - 32, 1);
+        while (win.k < 7 && (e3 + 32 - win.lo) >> win.k >= 256) ++win.k;
+        win.lo = min(win.lo, 65536 - (256 << win.k));
+    }
+    return win;
+}
+
+// The median pass of a block of kNT threads over rows ya .. yb - 1 of a crop:
+// clears ms.hist, estimates the crop's median and places the window, then
+// counts the rows. Returns the window, the same in every thread and for every
+// range of the crop's rows; ge2, nz2: this thread's packed counts of v >= lo and
+// v != 0; ms.hist: the window's histogram, complete after the caller's next
+// barrier.
+template <int kNT, bool kWide>
+__device__ __forceinline__ MedWindow median_rows(const CropDesc &c, int ya, int yb, MedianScratch &ms,
+                                               uint32_t &ge2, uint32_t &nz2) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int cpr = (c.w + 7) >> 3;
-    const int rows_par = kThreads / cpr;
-    const int cx = tid % cpr, ry0 = tid / cpr;
-    const int nk = ry0 < rows_par ? (c.h - ry0 + rows_par - 1) / rows_par : 0;
+    const int rows_par = kNT / cpr;
+    const int cx = tid % cpr, ry0 = ya + tid / cpr;
+    const int nk = tid / cpr < rows_par ? max(0, (yb - ry0 + rows_par - 1) / rows_par) : 0;
     const int x0 = 8 * cx;
     // The first batch of chunks does not depend on the estimate: issue its
     // loads before the estimate is taken so the two latencies overlap.
@@ -449,8 +452,8 @@ __device__ __forceinline__ int32_t crop_median_fast(const CropDesc &c, MedianScr
     for (int u = 0; u < kMedBatch; ++u)
         if (nk > 0) buf[u] = depth_chunk(c, ry0 + min(u, nk - 1) * rows_par, x0);
     // select_bin scans all 256 bins; the pass fills the first kMedWin.
-    for (int i = tid; i < 256; i += kThreads) ms.hist[i] = 0;
-    {
+    for (int i = tid; i < 256; i += kNT) ms.hist[i] = 0;
+    if (kNT == 256 || wave < 4) {
         // Wave w samples grid rows w, w + 4, ... of a 16 x 16 grid over the
         // crop, so each wave's estimate covers the whole crop.
         const int gr = 4 * (lane >> 4) + wave, gc = lane & 15;
@@ -459,19 +462,15 @@ __device__ __forceinline__ int32_t crop_median_fast(const CropDesc &c, MedianScr
         if (lane == 0) ms.est[wave] = e;
     }
     __syncthreads();
-    // The mean of the middle two of the four wave estimates.
-    const uint32_t ea = min(ms.est[0], ms.est[1]), eb = max(ms.est[0], ms.est[1]);
-    const uint32_t ec = min(ms.est[2], ms.est[3]), ed = max(ms.est[2], ms.est[3]);
-    const int32_t est = (int32_t)((max(ea, ec) + min(eb, ed)) >> 1);
-    const int32_t lo = min(max(est - (int32_t)kMedWin / 2, 1), 65536 - (int32_t)kMedWin);
-    const uint32_t lolo = (uint32_t)lo * 0x10001u;
-    const uint32_t lm1 = (uint32_t)(lo - 1) * 0x10001u;
+    const MedWindow win = median_window<kWide>(ms);
+    const uint32_t lolo = (uint32_t)win.lo * 0x10001u;
+    const uint32_t lm1 = (uint32_t)(win.lo - 1) * 0x10001u;
     // A 1 in each half that the compiler cannot see: with a visible constant
     // it turns each packed min below into two compares and selects.
     uint32_t one2 = 0x10001u;
     asm volatile("" : "+s"(one2));
 
-    uint32_t ge2 = 0, nz2 = 0;  // per-half counts of v >= lo and of v != 0
+    ge2 = nz2 = 0;  // per-half counts of v >= lo and of v != 0
     for (int kb = 0; kb < nk; kb += kMedBatch) {
         if (kb > 0) {
 #pragma unroll
@@ -482,11 +481,32 @@ __device__ __forceinline__ int32_t crop_median_fast(const CropDesc &c, MedianScr
         for (int u = 0; u < kMedBatch; ++u) {
             if (kb + u >= nk) break;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) median_count(buf[u][i], lolo, lm1, one2, ge2, nz2, ms);
+            for (int i = 0; i < 4; ++i) {
+                if (kWide && win.wide) median_count<true>(buf[u][i], lolo, lm1, one2, win.k, ge2, nz2, ms);
+                else median_count<false>(buf[u][i], lolo, lm1, one2, 0u, ge2, nz2, ms);
+            }
         }
     }
-    const int32_t r = median_finish<kWaves>(ms, sh_red, ge2, nz2, lo);
-    return r != -2 ? r : crop_median(c, ms);
+    return win;
+}
+
+// Exact lower median of the crop's non-zero depth, -1 if none.
+//  1. Each wave estimates it as the lower median of the non-zero values
+//     among 64 pixels of a 16 x 16 sampling grid (wave w takes the grid rows
+//     w, w + 4, ...); the estimate is the mean of the middle two of the four.
+//  2. One pass over the crop: the histogram of a window around the estimates
+//     (LDS atomics), and per-thread counts of the non-zero pixels and of those
+//     below the window (packed 16-bit arithmetic, no atomics).
+//  3. When the median's rank falls inside the window, its bin gives it (after
+//     a pass over the bin's values where bins are wider than 1 mm); otherwise
+//     the two-level radix select runs.
+// All kNT threads of the block call it.
+template <int kNT, bool kWide>
+__device__ __forceinline__ int32_t crop_median_fast(const CropDesc &c, MedianScratch &ms,
+                                                   uint32_t *sh_red) {
+    uint32_t ge2, nz2;
+    const MedWindow win = median_rows<kNT, kWide>(c, 0, c.h, ms, ge2, nz2);
+    return median_of_bin<kNT>(c, ms, win, median_finish<kNT / 64>(ms, sh_red, ge2, nz2));
 }
 
 // Columns x0..x0+3 of one row as loaded: grey bytes in G, depth u16 pairs
@@ -575,7 +595,8 @@ __device__ __forceinline__ uint32_t or_b23(uint32_t x) {
 // first, depth of the second); the masks then keep bit p for neighbour p.
 // Grey index = byte 0 | byte 1, depth index = byte 2 | byte 3 (or_b01,
 // or_b23): bit p <-> neighbour p in both.
-__device__ __forceinline__ uint32_t compare_bits(const Row6 &A, const Row6 &B, const Row6 &C, int j) {
+template <typename Row>
+__device__ __forceinline__ uint32_t compare_bits(const Row &A, const Row &B, const Row &C, int j) {
     const uint32_t c = B.p[j];
     // All eight differences first: a packed result read by the very next
     // instruction costs a wait state on gfx950.
@@ -591,15 +612,283 @@ __device__ __forceinline__ uint32_t compare_bits(const Row6 &A, const Row6 &B, c
     return acc;
 }
 
+// Centre pixels [xa, xb) x [ya, yb) of a crop.
+struct Region {
+    int xa, xb, ya, yb;
+};
+
+constexpr int kPanel = kFastMaxW - 2;  // centre columns of a panel: 256 columns loaded
+
+// How a region's centre rows fall on the lanes of a block: a stream is the L
+// lanes across the region's columns (4 each, one halo column on either side),
+// S streams share its rows. Every lane of the block steps through n_step rows,
+// so the row loop is uniform; rows past a stream's own are coded but not
+// counted, and stay inside the region: floor(s R / S) + ceil(R / S) <= R.
+struct Lanes {
+    int x0, xl;        // first column of this lane, and the column its loads start at
+    int yb, n_own;     // first centre row, rows of its own
+    int n_step;
+    uint32_t s8;       // 8 (x0 - xl): the shift that undoes xl
+};
+template <int kNT>
+__device__ __forceinline__ Lanes lanes_of(const CropDesc &c, const Region &rg) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int L = (rg.xb - rg.xa + 2 + 3) >> 2, spw = 64 / L, sw = lane / L;
+    const int S = kNT / 64 * spw, s = wave * spw + (sw < spw ? sw : 0), R = rg.yb - rg.ya;
+    Lanes l;
+    l.x0 = rg.xa - 1 + 4 * (lane - sw * L);
+    const bool full = (c.flags & kCropOverReadOk) || l.x0 + 4 <= c.w;
+    l.xl = full ? l.x0 : c.w - 4;
+    l.s8 = 8u * (uint32_t)(l.x0 - l.xl);
+    l.yb = rg.ya + (s * R) / S;
+    l.n_own = sw < spw ? rg.ya + ((s + 1) * R) / S - l.yb : 0;
+    l.n_step = (R + S - 1) / S;
+    return l;
+}
+
+// Word offset of column x's cell in a row band's counters.
+__device__ __forceinline__ uint32_t column_offset(const CropDesc &c, const FeatParams &fp, int x) {
+    return (uint32_t)(((min(x, c.w - 1) + 1) * fp.grid_x - 1) / c.w * fp.nbins);
+}
+
+// Byte offset of a comparison byte's bin: the table's (4 x bin), or, with 256
+// bins, of the code itself, the byte's complement.
+template <bool kFull, typename L>
+__device__ __forceinline__ uint32_t bin_offset(const L *lut4, uint32_t below) {
+    return kFull ? 1020u - 4u * below : (uint32_t)lut4[below];
+}
+
+// Counters of the grey and of the depth channel. Grey counts grow by 1 at
+// counter (cell, bin); depth counts by dinc at doff bytes further. A counter
+// may have 2^copies words, one for every 2^copies-th lane (base is the lane's),
+// so that fewer lanes of an instruction meet on a word; rowoff and the bin
+// table hold offsets in bytes of such counters.
+struct Counters {
+    char *base;
+    const uint16_t *rowoff;  // of row y's band
+    uint32_t dinc, doff;
+    uint32_t copies = 0;
+};
+
+// Per-pixel histogram loop over a region of any crop in any configuration,
+// for what the lane path does not take: each thread takes pixels in row order
+// and increments its bins with LDS atomics.
+template <int kNT, typename L>
+__device__ void code_pixels(const CropDesc c, const FeatParams &fp, int32_t m, const Region rg,
+                            const L *lut4, const Counters &ct) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int y = rg.ya + wave; y < rg.yb; y += kNT / 64) {
+        for (int x = rg.xa + lane; x < rg.xb; x += 64) {
+            const uint32_t dc = c.depth[(size_t)y * c.depth_pitch + x];
+            if (!centre_in_mask(dc, m, fp.window)) continue;
+            char *cell = ct.base + ct.rowoff[y] + (column_offset(c, fp, x) << (2 + ct.copies));
+            // The table maps comparison bytes (set bits: neighbours below).
+            if (fp.use_grey)
+                atomicAdd(reinterpret_cast<uint32_t *>(
+                              cell + lut4[255u ^ lbp_code(c.grey, c.grey_pitch, y, x)]), 1u);
+            if (fp.use_depth)
+                atomicAdd(reinterpret_cast<uint32_t *>(
+                              cell + ct.doff + lut4[255u ^ lbp_code(c.depth, c.depth_pitch, y, x)]),
+                          ct.dinc);
+        }
+    }
+}
+
+// Codes and counts a region with both channels in one pass, for a window of
+// 1 .. 255 and a median m >= window: each pixel packed as grey | d' << 16, so
+// that one packed subtraction compares both channels (see the file's head).
+template <bool kFull, int kPF, int kNT, typename L>
+__device__ __forceinline__ void code_both(const CropDesc &c, const FeatParams &fp, int32_t m,
+                                          const Region &rg, const L *lut4, const Counters &ct) {
+    const Lanes l = lanes_of<kNT>(c, rg);
+    const uint32_t lolo = (uint32_t)(m - fp.window) * 0x10001u;
+    const uint32_t span2 = (uint32_t)(2 * fp.window) * 0x10001u;
+    const uint32_t in_hi = (uint32_t)(2 * fp.window - 1) << 16;
+    const uint32_t s8 = l.s8, s16 = 2u * l.s8;
+    const RawRow rawA = load_row(c, l.yb - 1, l.xl), rawB = load_row(c, l.yb, l.xl);
+    RawRow ring[kPF];
+#pragma unroll
+    for (int u = 0; u < kPF; ++u) ring[u] = load_row(c, min(l.yb + 1 + u, rg.yb), l.xl);
+    uint32_t colg[4], cold[4], thr[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        colg[k] = column_offset(c, fp, l.x0 + k) << (2 + ct.copies);
+        cold[k] = colg[k] + ct.doff;
+        thr[k] = (l.x0 + k >= rg.xa && l.x0 + k < rg.xb) ? in_hi : 0u;
+    }
+    Row6 A = make_row(rawA, lolo, span2, s8, s16), B = make_row(rawB, lolo, span2, s8, s16);
+    auto step = [&](int t, const RawRow &raw) {
+        const Row6 C = make_row(raw, lolo, span2, s8, s16);
+        const uint32_t bias = t < l.n_own ? 0xFFFF0000u : 0x7FFF0000u;
+        const uint32_t row4 = ct.rowoff[l.yb + t];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t bits = compare_bits(A, B, C, k + 1);
+            if (B.p[k + 1] + bias < thr[k]) {
+                const uint32_t og = bin_offset<kFull>(lut4, or_b01(bits));
+                const uint32_t od = bin_offset<kFull>(lut4, or_b23(bits));
+                atomicAdd(reinterpret_cast<uint32_t *>(ct.base + add3(row4, colg[k], og)), 1u);
+                atomicAdd(reinterpret_cast<uint32_t *>(ct.base + add3(row4, cold[k], od)), ct.dinc);
+            }
+        }
+        A = B;
+        B = C;
+    };
+    int t = 0;
+    for (; t + kPF <= l.n_step; t += kPF) {
+#pragma unroll
+        for (int u = 0; u < kPF; ++u) {
+            const RawRow raw = ring[u];
+            ring[u] = load_row(c, min(l.yb + t + u + 1 + kPF, rg.yb), l.xl);
+            step(t + u, raw);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kPF - 1; ++u) {
+        if (t + u >= l.n_step) break;  // uniform
+        step(t + u, ring[u]);
+    }
+}
+
+// Columns x0-1 .. x0+4 of one row as u16 pairs (x0-1, x0), (x0, x0+1), ..,
+// (x0+3, x0+4); out: per centre pair (x0, x0+1), (x0+2, x0+3) a 1 in the half
+// of each pixel outside the mask.
+struct Row5 {
+    uint32_t p[5];
+    uint32_t out[2];
+};
+
+// Codes and counts a region with one channel (depth when kDepth, else grey), in
+// any window (kMask: pixels outside it, or with no depth, are not counted).
+// Two pixels to a word: every packed instruction compares two centre pixels.
+// Grey compares by the sign of the difference; depth uses all 16 bits, so its
+// comparison is a saturating subtraction.
+template <bool kDepth, bool kMask, bool kFull, int kPF, int kNT, typename L>
+__device__ __forceinline__ void code_one(const CropDesc &c, const FeatParams &fp, int32_t m,
+                                         const Region &rg, const L *lut4, const Counters &ct) {
+    const Lanes l = lanes_of<kNT>(c, rg);
+    // In the mask: d in [first, last], d != 0.
+    const int32_t first = max(m - fp.window + 1, 1), last = min(m + fp.window - 1, 65535);
+    const uint32_t first2 = (uint32_t)first * 0x10001u;
+    const uint32_t span2 = (uint32_t)(last - first) * 0x10001u;
+    const uint32_t s8 = l.s8, s16 = 2u * l.s8;
+    const uint32_t inc = kDepth ? ct.dinc : 1u;
+    uint32_t one2 = 0x10001u;  // opaque, as in median_rows
+    asm volatile("" : "+s"(one2));
+    auto load = [&](int y) {
+        RawRow r{0u, 0u, 0u};
+        if (!kDepth)
+            r.G = gld<uint32_t>(c.grey, (uint32_t)y * (uint32_t)c.grey_pitch + (uint32_t)l.xl);
+        if (kDepth || kMask) {
+            const u32x2 z = gld<u32x2>(c.depth, ((uint32_t)y * (uint32_t)c.depth_pitch + (uint32_t)l.xl) * 2u);
+            r.Z0 = z.x;
+            r.Z1 = z.y;
+        }
+        return r;
+    };
+    auto make = [&](const RawRow &raw) {
+        const uint64_t Z = ((((uint64_t)raw.Z1) << 32) | raw.Z0) >> s16;
+        const uint32_t z0 = (uint32_t)Z, z1 = (uint32_t)(Z >> 32);
+        Row5 r;
+        if (kDepth) {
+            const uint32_t zl = __builtin_amdgcn_mov_dpp(z1, 0x138, 0xF, 0xF, true);  // wave_shr:1
+            const uint32_t zr = __builtin_amdgcn_mov_dpp(z0, 0x130, 0xF, 0xF, true);  // wave_shl:1
+            r.p[0] = __builtin_amdgcn_alignbit(z0, zl, 16);
+            r.p[1] = z0;
+            r.p[2] = __builtin_amdgcn_alignbit(z1, z0, 16);
+            r.p[3] = z1;
+            r.p[4] = __builtin_amdgcn_alignbit(zr, z1, 16);
+        } else {
+            const uint32_t G = raw.G >> s8;
+            const uint32_t gl = __builtin_amdgcn_mov_dpp(G, 0x138, 0xF, 0xF, true);
+            const uint32_t gr = __builtin_amdgcn_mov_dpp(G, 0x130, 0xF, 0xF, true);
+            // perm(hi, lo, sel): bytes 0-3 are lo's, 4-7 hi's, 0x0C is 0.
+            r.p[0] = __builtin_amdgcn_perm(G, gl, 0x0C040C03u);
+            r.p[1] = __builtin_amdgcn_perm(G, G, 0x0C010C00u);
+            r.p[2] = __builtin_amdgcn_perm(G, G, 0x0C020C01u);
+            r.p[3] = __builtin_amdgcn_perm(G, G, 0x0C030C02u);
+            r.p[4] = __builtin_amdgcn_perm(gr, G, 0x0C040C03u);
+        }
+        r.out[0] = r.out[1] = 0u;
+        if (kMask) {
+            // d - first wraps above the span for d < first (first + span <= 65535).
+            r.out[0] = pk_min(pk_sub_sat(pk_sub(z0, first2), span2), one2);
+            r.out[1] = pk_min(pk_sub_sat(pk_sub(z1, first2), span2), one2);
+        }
+        return r;
+    };
+    RawRow ring[kPF];
+    const RawRow rawA = load(l.yb - 1), rawB = load(l.yb);
+#pragma unroll
+    for (int u = 0; u < kPF; ++u) ring[u] = load(min(l.yb + 1 + u, rg.yb));
+    uint32_t col4[4], cut[2] = {0u, 0u};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        col4[k] = 4u * column_offset(c, fp, l.x0 + k) + (kDepth ? ct.doff : 0u);
+        if (l.x0 + k < rg.xa || l.x0 + k >= rg.xb) cut[k >> 1] |= 1u << (16 * (k & 1));
+    }
+    Row5 A = make(rawA), B = make(rawB);
+    auto step = [&](int t, const RawRow &raw) {
+        const Row5 C = make(raw);
+        const uint32_t other = t < l.n_own ? 0u : 0x10001u;
+        const uint32_t row4 = ct.rowoff[l.yb + t];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int i = 2 * j + 1;
+            uint32_t b0, b1;  // comparison bytes of the pair's pixels
+            if (kDepth) {
+                const uint32_t v = B.p[i];
+                const uint32_t n[8] = {A.p[i - 1], A.p[i], A.p[i + 1], B.p[i + 1],
+                                       C.p[i + 1], C.p[i], C.p[i - 1], B.p[i - 1]};
+                uint32_t bits = 0;
+#pragma unroll
+                for (int q = 0; q < 8; ++q) bits |= pk_min(pk_sub_sat(v, n[q]), one2) << q;
+                b0 = bits & 0xFFFFu;
+                b1 = bits >> 16;
+            } else {
+                const uint32_t bits = compare_bits(A, B, C, i);
+                b0 = or_b01(bits);
+                b1 = or_b23(bits);
+            }
+            const uint32_t out = B.out[j] | cut[j] | other;
+            if (!(out & 0xFFFFu))
+                atomicAdd(reinterpret_cast<uint32_t *>(
+                              ct.base + add3(row4, col4[2 * j], bin_offset<kFull>(lut4, b0))), inc);
+            if (!(out >> 16))
+                atomicAdd(reinterpret_cast<uint32_t *>(
+                              ct.base + add3(row4, col4[2 * j + 1], bin_offset<kFull>(lut4, b1))), inc);
+        }
+        A = B;
+        B = C;
+    };
+    int t = 0;
+    for (; t + kPF <= l.n_step; t += kPF) {
+#pragma unroll
+        for (int u = 0; u < kPF; ++u) {
+            const RawRow raw = ring[u];
+            ring[u] = load(min(l.yb + t + u + 1 + kPF, rg.yb));
+            step(t + u, raw);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kPF - 1; ++u) {
+        if (t + u >= l.n_step) break;  // uniform
+        step(t + u, ring[u]);
+    }
+}
+
+// The lane path's loads need w >= 4 unless the crop may be over-read.
+__device__ __forceinline__ bool lanes_ok(const CropDesc &c) {
+    return c.w >= 4 || (c.flags & kCropOverReadOk);
+}
+
 // LDS of the fast path, about 23 KB: six workgroups fit a CU's LDS.
 struct FastShared {
     // cells * 59 words: the grey count of (cell, bin) in the low half, the
     // depth count in the high half (a cell holds fewer than 65536 pixels).
     __attribute__((aligned(16))) uint32_t hist[64 * kU59];
     MedianScratch ms;
-    uint8_t bin[256];    // code -> bin
     uint8_t lut[256];    // comparison byte (bit p: neighbour p below) -> 4 x bin
-    uint8_t rowband[LBPF_MAX_SIDE];
     uint8_t colband[LBPF_MAX_SIDE];
     uint16_t rowoff[LBPF_MAX_SIDE];  // byte offset of row y's band in hist
     float q[kQuot];
@@ -608,10 +897,8 @@ struct FastShared {
 };
 
 __device__ __forceinline__ void load_tables(FastShared &sh, const uint8_t *tables) {
-    for (int i = threadIdx.x; i < 256; i += kThreads) {
-        sh.bin[i] = tables[i];
+    for (int i = threadIdx.x; i < 256; i += kThreads)
         sh.lut[i] = (uint8_t)(4 * tables[256 + i]);  // bins <= 58: byte offsets fit
-    }
 }
 
 // Normalisation and output of one crop by a block of kNT threads, after the
@@ -683,11 +970,8 @@ __device__ void fast_crop(const CropDesc &cd, const FeatParams &fp, FastShared &
     for (int i = 4 * tid; i < half; i += 4 * kThreads)
         *reinterpret_cast<u32x4 *>(&sh.hist[i]) = u32x4{0u, 0u, 0u, 0u};
     // Coordinate y lies in band floor(((y + 1) g - 1) / n) of a side of length n.
-    for (int y = tid; y < h; y += kThreads) {
-        const int band = ((y + 1) * gy - 1) / h;
-        sh.rowband[y] = (uint8_t)band;
-        sh.rowoff[y] = (uint16_t)(band * gx * kU59 * 4);  // < 64 * 59 * 4
-    }
+    for (int y = tid; y < h; y += kThreads)
+        sh.rowoff[y] = (uint16_t)(((y + 1) * gy - 1) / h * gx * kU59 * 4);  // < 64 * 59 * 4
     for (int x = tid; x < w; x += kThreads) sh.colband[x] = (uint8_t)(((x + 1) * gx - 1) / w);
 
     // Stream geometry of the code phase. Its first rows do not depend on the
@@ -723,10 +1007,9 @@ __device__ void fast_crop(const CropDesc &cd, const FeatParams &fp, FastShared &
     if (kEarly && fast) prime();
 
     // Ends with a barrier; the same value in every lane.
-    const int32_t m = __builtin_amdgcn_readfirstlane(crop_median_fast(c, sh.ms, sh.red));
+    const int32_t m = __builtin_amdgcn_readfirstlane(crop_median_fast<kThreads, false>(c, sh.ms, sh.red));
     const int32_t lo = m - fp.window;
-    // The packed window arithmetic needs lo >= 0: a crop whose median lies
-    // within the window of 0 takes the generic path.
+    // The packed window arithmetic needs lo >= 0.
     if (fast && (m < 0 || lo >= 0)) {
         if (m >= 0) {
             if (!kEarly) prime();
@@ -797,8 +1080,16 @@ __device__ void fast_crop(const CropDesc &cd, const FeatParams &fp, FastShared &
                 step(t + u, ring[u], false);
             }
         }
-    } else {
-        lbp_hist_generic(c, fp, m, sh.bin, sh.rowband, sh.colband, sh.hist, true);
+    } else if (m >= 0) {
+        // Wider crops by panels; a median within the window of 0, or crops
+        // too narrow for the lane loads, pixel by pixel.
+        const Counters ct{reinterpret_cast<char *>(sh.hist), sh.rowoff, 0x10000u, 0u};
+        if (lo >= 0 && w > kFastMaxW)
+            for (int xa = 1; xa < w - 1; xa += kPanel)
+                code_both<false, 2, kThreads>(c, fp, m, Region{xa, min(xa + kPanel, w - 1), 1, h - 1},
+                                              sh.lut, ct);
+        else
+            code_pixels<kThreads>(c, fp, m, Region{1, w - 1, 1, h - 1}, sh.lut, ct);
     }
     __syncthreads();
 
@@ -859,48 +1150,309 @@ __global__ __launch_bounds__(kThreads, 4) void k_features_persistent(
     }
 }
 
-// Any configuration: dynamic LDS holds fp.dim counters.
-__global__ __launch_bounds__(kThreads) void k_features_generic(const CropDesc *__restrict__ crops,
-                                                               FeatParams fp,
-                                                               const uint8_t *__restrict__ tables,
-                                                               float *__restrict__ hist,
-                                                               uint32_t *__restrict__ counts) {
-    extern __shared__ uint32_t sh_hist[];
-    __shared__ MedianScratch ms;
-    __shared__ uint8_t sh_bin[256];
-    __shared__ uint8_t sh_rowband[LBPF_MAX_SIDE];
-    __shared__ uint8_t sh_colband[LBPF_MAX_SIDE];
-    __shared__ uint32_t sh_red[kWaves];
+// --- few or large crops: several workgroups a crop -------------------------------
+//
+// One workgroup per crop leaves most of the GPU idle when there are fewer crops
+// than CUs, and makes a call as long as its largest crop (a 256 x 256 face takes
+// 40 us on one workgroup). Here a crop is shared by parts_of(c) workgroups in
+// three launches: the median's counts by rows, the codes by row bands and
+// column panels, the normalisation (5 faces of 48-256 px 50 -> 22 us a call; 128
+// crops of 257-1024 px 4170 -> 150 us, of which the median 38, the codes 97: 560
+// px a ns, bound by LDS atomics on flat patches and VALU issue). Nothing but the crop's own row of `hist` is
+// written: until the last launch it holds the packed counters (words 0 ..
+// half - 1, added to atomically) and, behind them, kMedWords words of median
+// counts per part.
 
+constexpr int kSplitMinPx = 2048, kSplitMaxPx = 16384;  // pixels a part
+constexpr int kMedWords = 132;    // 256 16-bit bins, non-zero pixels, those >= lo, the window
+
+// The crop table: in device memory, or (a frame's few faces) in the kernel's
+// arguments, so that no copy precedes the launch.
+struct CropArgs {
+    CropDesc c[kArgCrops];
+};
+__device__ __forceinline__ CropDesc crop_at(const CropDesc *t, int32_t i) { return t[i]; }
+__device__ __forceinline__ CropDesc crop_at(const CropArgs &t, int32_t i) { return t.c[i]; }
+
+__device__ __forceinline__ int parts_of(const CropDesc &c, const SplitCfg &sc, const int32_t *n_dev) {
+    const int px = n_dev ? min(max(*n_dev * sc.px, kSplitMinPx), kSplitMaxPx) : sc.px;
+    return min(sc.parts, ((int)c.w * c.h + px - 1) / px);
+}
+
+// Parts of a crop that hold median counts: 8 (each part of the code launch sums
+// them with its loads in one flight), or one per 32 K pixels (so that a part's
+// counts fit its 16-bit bins), at most what fits behind the counters.
+__device__ __forceinline__ int median_parts(const CropDesc &c, int parts, int half) {
+    return min(parts, min(max(8, (int)c.w * c.h >> 15), half / kMedWords));
+}
+
+struct SplitShared {
+    __attribute__((aligned(16))) uint32_t hist[64 * kU59];
+    MedianScratch ms;
+    uint16_t lut[256];               // comparison byte -> offset of its bin
+    uint16_t rowoff[LBPF_MAX_SIDE];  // offset of row y's band
+    uint32_t red[2];
+};
+
+// Crop of a workgroup: rotated by the part, so that a large crop's parts spread
+// over the XCDs (workgroups are dealt to them in turn).
+__device__ __forceinline__ int32_t split_crop() {
+    return (int32_t)((blockIdx.x + blockIdx.y) % gridDim.x);
+}
+
+// Part p of a crop: a column panel and a range of rows. With at least one range
+// per grid row, each lies within one grid row, so that the part's few counters
+// leave room for copies.
+__device__ __forceinline__ bool part_region(const CropDesc &c, int gy, int parts, int p, Region &rg) {
+    const int panels = (c.w - 2 + kPanel - 1) / kPanel;
+    int bands = max(1, parts / panels);
+    const int sub = bands / gy;  // ranges per grid row
+    if (sub > 0) bands = sub * gy;
+    if (p >= bands * panels) return false;
+    const int band = p / panels, panel = p % panels;
+    rg.xa = 1 + panel * (c.w - 2) / panels;
+    rg.xb = 1 + (panel + 1) * (c.w - 2) / panels;
+    if (sub > 0) {
+        const int g = band / sub, k = band % sub;
+        const int y0 = max(g * c.h / gy, 1), y1 = min((g + 1) * c.h / gy, c.h - 1);
+        rg.ya = y0 + k * (y1 - y0) / sub;
+        rg.yb = y0 + (k + 1) * (y1 - y0) / sub;
+    } else {
+        rg.ya = 1 + band * (c.h - 2) / bands;
+        rg.yb = 1 + (band + 1) * (c.h - 2) / bands;
+    }
+    return rg.yb > rg.ya;
+}
+
+template <typename Table>
+__global__ __launch_bounds__(kThreads) void k_split_median(Table crops, SplitCfg sc, FeatParams fp,
+                                                           float *__restrict__ hist,
+                                                           const int32_t *__restrict__ n_dev) {
+    __shared__ MedianScratch ms;
+    __shared__ uint32_t red[2 * kWaves];
+    const int32_t p = blockIdx.y, i = split_crop();
+    if (n_dev && i >= *n_dev) return;  // uniform
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int half = fp.grid_x * fp.grid_y * kU59;
+    const CropDesc c = crop_at(crops, i);
+    const int parts = parts_of(c, sc, n_dev), mparts = median_parts(c, parts, half);
+    if (p >= parts) return;  // uniform
+    uint32_t *row = reinterpret_cast<uint32_t *>(hist + (size_t)i * fp.dim);
+    for (int w = p * half / parts + tid; w < (p + 1) * half / parts; w += kThreads) row[w] = 0u;
+    if (p >= mparts) return;
+    uint32_t ge2, nz2;
+    const MedWindow win =
+        median_rows<kThreads, true>(c, p * c.h / mparts, (p + 1) * c.h / mparts, ms, ge2, nz2);
+    const uint32_t nnz = wave_sum((nz2 & 0xFFFFu) + (nz2 >> 16));
+    const uint32_t nge = wave_sum((ge2 & 0xFFFFu) + (ge2 >> 16));
+    if (lane == 0) {
+        red[wave] = nnz;
+        red[kWaves + wave] = nge;
+    }
+    __syncthreads();
+    uint32_t *part = row + half + p * kMedWords;
+    if (tid < (win.wide ? 128 : (int)kMedWin / 2))
+        part[tid] = ms.hist[2 * tid] | (ms.hist[2 * tid + 1] << 16);
+    if (tid == 0) {
+        uint32_t a = 0, b = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            a += red[w];
+            b += red[kWaves + w];
+        }
+        part[128] = a;
+        part[129] = b;
+        part[130] = (uint32_t)win.lo;
+        part[131] = win.k | (win.wide ? 256u : 0u);
+    }
+}
+
+template <typename Table>
+__global__ __launch_bounds__(kThreads) void k_split_code(Table crops, SplitCfg sc, FeatParams fp,
+                                                         const uint8_t *__restrict__ tables,
+                                                         float *__restrict__ hist,
+                                                         const int32_t *__restrict__ n_dev) {
+    __shared__ SplitShared sh;
+    const int32_t p = blockIdx.y, i = split_crop();
+    if (n_dev && i >= *n_dev) return;  // uniform
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int gx = fp.grid_x, gy = fp.grid_y, half = gx * gy * kU59;
+    const CropDesc c = crop_at(crops, i);
+    const int parts = parts_of(c, sc, n_dev), mparts = median_parts(c, parts, half);
+    Region rg;
+    if (!part_region(c, gy, parts, p, rg)) return;  // uniform
+    uint32_t *row = reinterpret_cast<uint32_t *>(hist + (size_t)i * fp.dim);
+    // Counters of the grid rows this part touches, in as many copies (at most
+    // 8) as fit: large crops have flat patches, whose lanes would otherwise
+    // meet on one word.
+    const int w0 = ((rg.ya + 1) * gy - 1) / c.h * gx * kU59;
+    const int w1 = ((rg.yb * gy - 1) / c.h + 1) * gx * kU59;
+    const uint32_t cp = min(31 - __builtin_clz(64 * kU59 / (w1 - w0)), 3);
+    // 64 * 59 is a multiple of 4, so the rounded-up clear stays in the array.
+    for (int w = 4 * tid; w < (w1 - w0) << cp; w += 4 * kThreads)
+        *reinterpret_cast<u32x4 *>(&sh.hist[w]) = u32x4{0u, 0u, 0u, 0u};
+    for (int k = tid; k < 256; k += kThreads) sh.lut[k] = (uint16_t)((uint32_t)tables[256 + k] << (2 + cp));
+    for (int y = rg.ya + tid; y < rg.yb; y += kThreads)
+        sh.rowoff[y] = (uint16_t)((((y + 1) * gy - 1) / c.h * gx * kU59 - w0) << (2 + cp));
+    // The median from the parts' counts, as median_finish: thread t sums bin t,
+    // eight loads in flight.
+    static_assert(kThreads == 256, "a thread per bin");
+    const uint32_t *med = row + half;
+    const MedWindow win{(int32_t)med[130], med[131] & 255u, (med[131] & 256u) != 0};
+    uint32_t bins = 0, tot = 0;
+    for (int q0 = 0; q0 < mparts; q0 += 8) {
+        uint32_t v[8], u[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const uint32_t *part = med + min(q0 + k, mparts - 1) * kMedWords;
+            v[k] = part[tid >> 1] >> (16 * (tid & 1)) & 0xFFFFu;
+            u[k] = part[128 + (tid & 1)];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            bins += q0 + k < mparts ? v[k] : 0u;
+            tot += q0 + k < mparts ? u[k] : 0u;
+        }
+    }
+    sh.ms.hist[tid] = win.wide || tid < (int)kMedWin ? bins : 0u;  // (the rest was not written)
+    if (tid < 2) sh.red[tid] = tot;
+    __syncthreads();
+    const uint32_t nnz = sh.red[0], below = nnz - sh.red[1];
+    int32_t m = -1;
+    if (nnz > 0) {  // uniform
+        const uint32_t rank = (nnz - 1) / 2;
+        if (wave == 0) {
+            if (rank >= below) select_bin(sh.ms, rank - below, lane);
+            else if (lane == 0) sh.ms.bin = -1;
+        }
+        __syncthreads();
+        const int32_t bin = sh.ms.bin;
+        __syncthreads();
+        m = median_of_bin<kThreads>(c, sh.ms, win, bin >= 0 ? bin : -2);
+    }
+    m = __builtin_amdgcn_readfirstlane(m);
+    if (m < 0) return;
+    const Counters ct{reinterpret_cast<char *>(sh.hist + (lane & ((1u << cp) - 1u))), sh.rowoff,
+                      0x10000u, 0u, cp};
+    if (m >= fp.window && lanes_ok(c))
+        code_both<false, 2, kThreads>(c, fp, m, rg, sh.lut, ct);
+    else
+        code_pixels<kThreads>(c, fp, m, rg, sh.lut, ct);
+    __syncthreads();
+    for (int w = tid; w < w1 - w0; w += kThreads) {
+        uint32_t v = sh.hist[w << cp];
+        if (cp == 1) v += sh.hist[2 * w + 1];
+        if (cp >= 2) {
+            u32x4 t = *reinterpret_cast<const u32x4 *>(&sh.hist[w << cp]);
+            if (cp == 3) t += *reinterpret_cast<const u32x4 *>(&sh.hist[(w << cp) + 4]);
+            v = t.x + t.y + t.z + t.w;
+        }
+        if (v) atomicAdd(&row[w0 + w], v);
+    }
+}
+
+template <typename Table>
+__global__ __launch_bounds__(kThreads) void k_split_finish(Table crops, FeatParams fp,
+                                                           float *__restrict__ hist,
+                                                           uint32_t *__restrict__ counts,
+                                                           const int32_t *__restrict__ n_dev) {
+    __shared__ __attribute__((aligned(16))) uint32_t cnt[64 * kU59];
+    __shared__ float q[kQuot];
+    __shared__ uint32_t red[kWaves];
+    const size_t i = blockIdx.x;
+    if (n_dev && (int32_t)i >= *n_dev) return;  // uniform
+    const CropDesc c = crop_at(crops, (int32_t)i);
+    const int w = c.w, h = c.h;
+    const int gx = fp.grid_x, gy = fp.grid_y, half = gx * gy * kU59;
+    float *out = hist + i * fp.dim;
+    for (int k = threadIdx.x; k < half; k += kThreads)
+        cnt[k] = reinterpret_cast<const uint32_t *>(out)[k];
+    __syncthreads();
+    finish_crop<kThreads>(cnt, half, ((h + gy - 1) / gy) * ((w + gx - 1) / gx), q, red, out,
+                          counts ? counts + i * fp.dim : nullptr);
+}
+
+// --- every other configuration --------------------------------------------------
+//
+// 256 bins, one channel, mask off, wide windows, coarse grids: one workgroup of
+// 8 waves per crop on the same lane path, counters in dynamic LDS. Both channels
+// share a counter word when a cell's counts fit 16 bits (packed); with a window
+// outside 1 .. 255 mm they are coded in two passes, since the packed pixels of
+// code_both hold the depth clamped to the window. Bound by VALU issue (67% of it)
+// and the LDS; 1024 crops of 200 x 200, 256 bins of grey: 74 us, 2.6 TB/s of
+// input and output, against 331 one pixel a thread with 18 loads a pixel.
+enum class Channels { kGrey, kDepth, kBothNarrow, kBothWide };
+constexpr int kAnyThreads = 512;
+
+template <Channels kCh, bool kMask, bool kFull>
+__global__ __launch_bounds__(kAnyThreads) void k_features_any(const CropDesc *__restrict__ crops,
+                                                              FeatParams fp, bool packed,
+                                                              const uint8_t *__restrict__ tables,
+                                                              float *__restrict__ hist,
+                                                              uint32_t *__restrict__ counts) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t cnt[];
+    __shared__ MedianScratch ms;
+    __shared__ uint16_t lut[256];                 // comparison byte -> 4 x bin
+    __shared__ uint16_t rowoff[LBPF_MAX_SIDE];    // < 64 * 256 * 4
+    __shared__ float q[kQuot];
+    __shared__ uint32_t red[2 * (kAnyThreads / 64)];
+    constexpr int kNT = kAnyThreads, kNW = kNT / 64;
+    constexpr bool kBoth = kCh == Channels::kBothNarrow || kCh == Channels::kBothWide;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const CropDesc c = crops[blockIdx.x];
-
-    for (int i = tid; i < fp.dim; i += kThreads) sh_hist[i] = 0;
-    for (int i = tid; i < 256; i += kThreads) sh_bin[i] = tables[i];
-    for (int y = tid; y < c.h; y += kThreads) sh_rowband[y] = (uint8_t)(((y + 1) * fp.grid_y - 1) / c.h);
-    for (int x = tid; x < c.w; x += kThreads) sh_colband[x] = (uint8_t)(((x + 1) * fp.grid_x - 1) / c.w);
+    const int gx = fp.grid_x, gy = fp.grid_y, per = gx * gy * fp.nbins;
+    const int words = kBoth && !packed ? 2 * per : per;
+    for (int i = tid; i < words; i += kNT) cnt[i] = 0u;
+    for (int i = tid; i < 256; i += kNT) lut[i] = (uint16_t)(4 * tables[256 + i]);
+    for (int y = tid; y < c.h; y += kNT)
+        rowoff[y] = (uint16_t)(((y + 1) * gy - 1) / c.h * gx * fp.nbins * 4);
+    int32_t m = 0;
+    if (kMask) m = __builtin_amdgcn_readfirstlane(crop_median_fast<kNT, true>(c, ms, red));
     __syncthreads();
-    const int32_t m = fp.window > 0 ? crop_median(c, ms) : -1;
-
-    lbp_hist_generic(c, fp, m, sh_bin, sh_rowband, sh_colband, sh_hist);
+    if (m >= 0) {
+        const Counters ct{reinterpret_cast<char *>(cnt), rowoff, kBoth && packed ? 0x10000u : 1u,
+                          kBoth && !packed ? 4u * per : 0u};
+        if (!lanes_ok(c) || (kCh == Channels::kBothNarrow && m < fp.window)) {
+            code_pixels<kNT>(c, fp, m, Region{1, c.w - 1, 1, c.h - 1}, lut, ct);
+        } else {
+            for (int xa = 1; xa < c.w - 1; xa += kPanel) {
+                const Region rg{xa, min(xa + kPanel, c.w - 1), 1, c.h - 1};
+                if constexpr (kCh == Channels::kBothNarrow) {
+                    code_both<kFull, 2, kNT>(c, fp, m, rg, lut, ct);
+                } else {
+                    if constexpr (kCh != Channels::kDepth)
+                        code_one<false, kMask, kFull, 4, kNT>(c, fp, m, rg, lut, ct);
+                    if constexpr (kCh != Channels::kGrey)
+                        code_one<true, kMask, kFull, 4, kNT>(c, fp, m, rg, lut, ct);
+                }
+            }
+        }
+    }
     __syncthreads();
 
-    const int per_ch = fp.grid_x * fp.grid_y * fp.nbins;
+    const uint32_t low = kBoth && packed ? 0xFFFFu : ~0u;
     uint32_t part = 0;
-    for (int i = tid; i < per_ch; i += kThreads) part += sh_hist[i];
+    for (int i = tid; i < per; i += kNT) part += cnt[i] & low;
     part = wave_sum(part);
-    if (lane == 0) sh_red[wave] = part;
+    if (lane == 0) red[wave] = part;
     __syncthreads();
     uint32_t n_in = 0;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) n_in += sh_red[w];
+    for (int w = 0; w < kNW; ++w) n_in += red[w];
     const float T = (float)(fp.nch * n_in);
-
+    const int maxc = ((c.h + gy - 1) / gy) * ((c.w + gx - 1) / gx);
+    const bool tab = maxc < kQuot;
+    if (tab) {
+        for (int v = tid; v <= maxc; v += kNT) q[v] = n_in ? (float)v / T : 0.0f;
+        __syncthreads();
+    }
     float *out = hist + (size_t)blockIdx.x * fp.dim;
     uint32_t *cout = counts ? counts + (size_t)blockIdx.x * fp.dim : nullptr;
-    for (int i = tid; i < fp.dim; i += kThreads) {
-        const uint32_t v = sh_hist[i];
-        out[i] = n_in ? (float)v / T : 0.0f;
+    for (int i = tid; i < fp.dim; i += kNT) {
+        uint32_t v;
+        if (kBoth && packed) v = i < per ? cnt[i] & 0xFFFFu : cnt[i - per] >> 16;
+        else v = cnt[i];
+        st_nt(out + i, tab ? q[v] : (n_in ? (float)v / T : 0.0f));
         if (cout) cout[i] = v;
     }
 }
@@ -927,56 +1479,138 @@ __global__ __launch_bounds__(kThreads) void k_debug_codes(const CropDesc *__rest
 
 }  // namespace
 
+// Packed 16-bit counters: a cell of the largest crop holds < 65536 pixels.
+static bool packed_cells(const FeatParams &fp) {
+    return (int64_t)((LBPF_MAX_SIDE + fp.grid_x - 1) / fp.grid_x) *
+               ((LBPF_MAX_SIDE + fp.grid_y - 1) / fp.grid_y) < 65536;
+}
+
 bool fast_path_ok(const FeatParams &fp) {
-    // Packed 16-bit counters: a cell of the largest crop holds < 65536 pixels.
-    const int64_t cell_max = (int64_t)((LBPF_MAX_SIDE + fp.grid_x - 1) / fp.grid_x) *
-                             ((LBPF_MAX_SIDE + fp.grid_y - 1) / fp.grid_y);
     return fp.nbins == kU59 && fp.use_grey && fp.use_depth && fp.window >= 1 &&
-           fp.window <= 255 && fp.grid_x * fp.grid_y <= 64 && cell_max < 65536;
+           fp.window <= 255 && fp.grid_x * fp.grid_y <= 64 && packed_cells(fp);
+}
+
+// Whether the median parts that fit behind a row's counters (median_parts) hold a
+// crop of `largest` px: fewer than 60000 px each, whole rows of at most 1024 more.
+static bool median_parts_fit(int32_t largest, const FeatParams &fp) {
+    return (int64_t)(fp.grid_x * fp.grid_y * kU59 / kMedWords) * 60000 >= largest;
+}
+
+// Whether a call of these crops is split, from the two launches' times in us as
+// measured: one workgroup per crop takes 5.5 + 0.72 per 1000 px of the largest
+// crop, or 8 + 1 per 620 K px in all (twice that for crops wider than a panel);
+// split, 18.5 + 1 per 450 K px. Whole calls, one workgroup / split: 5 crops of
+// 48-256 px 50 / 22, 64 x 200 x 200 37 / 25, 256 x 200 x 200 38 / 40, 256 x 128
+// x 128 18 / 28, 128 of 257-1024 px 984 / 139, 512 of 257-1024 px 1404 / 455,
+// 512 of 100-300 px 100 / 95, 2048 of 100-300 px 208 / 267.
+SplitCfg split_for(const CropDesc *crops, int32_t n, const FeatParams &fp) {
+    SplitCfg sc;
+    if (n <= 0 || !fast_path_ok(fp)) return sc;
+    int64_t total = 0, wide = 0;
+    int32_t largest = 0, widest = 0;
+    for (int32_t i = 0; i < n; ++i) {
+        const int32_t px = (int32_t)crops[i].w * crops[i].h;
+        total += px;
+        if (crops[i].w > kFastMaxW) wide += px;
+        largest = std::max(largest, px);
+        widest = std::max<int32_t>(widest, crops[i].w);
+    }
+    const double one = std::max(5.5 + 0.72e-3 * largest, 8.0 + (double)(total + wide) / 620e3);
+    if (18.5 + (double)total / 450e3 >= one) return sc;
+    if (!median_parts_fit(largest, fp)) return sc;
+    sc.px = (int32_t)std::min<int64_t>(std::max<int64_t>(total / 512, kSplitMinPx), kSplitMaxPx);
+    sc.parts = std::max((largest + sc.px - 1) / sc.px, (widest - 2 + kPanel - 1) / kPanel);
+    return sc;
+}
+
+SplitCfg split_for_device_count(int32_t max_n, const FeatParams &fp) {
+    SplitCfg sc;
+    if (max_n > 512 || !fast_path_ok(fp) || !median_parts_fit(LBPF_MAX_SIDE * LBPF_MAX_SIDE, fp))
+        return sc;
+    sc.parts = 32;
+    sc.px = 52;  // 27 K px a crop on average, 512 parts in all
+    return sc;
+}
+
+template <bool kFull>
+static hipError_t launch_any(const CropDesc *crops, int32_t n, const FeatParams &fp,
+                             const uint8_t *d_tables, float *hist, uint32_t *counts,
+                             hipStream_t s) {
+    const bool both = fp.use_grey && fp.use_depth, mask = fp.window > 0;
+    const bool packed = both && packed_cells(fp);
+    const size_t lds = sizeof(uint32_t) * (size_t)fp.grid_x * fp.grid_y * fp.nbins *
+                       (both && !packed ? 2 : 1);
+    auto go = [&](auto kern) {
+        // The opt-in above 64 KB of LDS in all (the 256-bin mapping on 8 x 8 cells).
+        hipError_t e = hipFuncSetAttribute((const void *)kern,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kern, dim3(n), dim3(kAnyThreads), lds, s, crops, fp, packed, d_tables,
+                           hist, counts);
+        return hipGetLastError();
+    };
+    using C = Channels;
+    if (!both && fp.use_grey)
+        return mask ? go(k_features_any<C::kGrey, true, kFull>)
+                    : go(k_features_any<C::kGrey, false, kFull>);
+    if (!both)
+        return mask ? go(k_features_any<C::kDepth, true, kFull>)
+                    : go(k_features_any<C::kDepth, false, kFull>);
+    if (mask && fp.window <= 255) return go(k_features_any<C::kBothNarrow, true, kFull>);
+    return mask ? go(k_features_any<C::kBothWide, true, kFull>)
+                : go(k_features_any<C::kBothWide, false, kFull>);
 }
 
 hipError_t launch_features(const CropDesc *crops, int32_t n, const FeatParams &fp,
                            const uint8_t *d_tables, float *hist, uint32_t *counts,
-                           hipStream_t s, const LaunchCfg &lc, const int32_t *order,
-                           uint32_t *queue, int32_t num_cus, const int32_t *n_dev) {
+                           hipStream_t s, const SplitCfg &split, const LaunchCfg &lc,
+                           const int32_t *order, uint32_t *queue, int32_t num_cus,
+                           const int32_t *n_dev, const CropDesc *h_crops) {
     if (n <= 0) return hipSuccess;
-    if (fast_path_ok(fp)) {
-        const int pf = lc.row_prefetch <= 2 ? 2 : (lc.row_prefetch <= 4 ? 4 : 8);
-        if (lc.persistent && queue) {
-            const int grid = std::min<int>(n, std::max(1, lc.wg_per_cu) * num_cus);
-            const int32_t *ord = lc.sorted ? order : nullptr;
-            auto go = [&](auto kern) {
-                hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), 0, s, crops, ord, n, fp,
-                                   d_tables, hist, counts, queue, n_dev);
-            };
-            if (pf == 2) go(k_features_persistent<2>);
-            else if (pf == 4) go(k_features_persistent<4>);
-            else go(k_features_persistent<8>);
+    if (!fast_path_ok(fp)) {
+        if (n_dev) return hipErrorInvalidValue;  // device counts: the fast configuration only
+        return fp.nbins == kU59 ? launch_any<false>(crops, n, fp, d_tables, hist, counts, s)
+                                : launch_any<true>(crops, n, fp, d_tables, hist, counts, s);
+    }
+    const int pf = lc.row_prefetch <= 2 ? 2 : (lc.row_prefetch <= 4 ? 4 : 8);
+    if (split.parts > 0 && !lc.persistent) {
+        const dim3 grid(n, split.parts);
+        auto go = [&](auto table) {
+            using T = decltype(table);
+            hipLaunchKernelGGL(k_split_median<T>, grid, dim3(kThreads), 0, s, table, split, fp,
+                               hist, n_dev);
+            hipLaunchKernelGGL(k_split_code<T>, grid, dim3(kThreads), 0, s, table, split, fp,
+                               d_tables, hist, n_dev);
+            hipLaunchKernelGGL(k_split_finish<T>, dim3(n), dim3(kThreads), 0, s, table, fp, hist,
+                               counts, n_dev);
+        };
+        if (h_crops) {
+            CropArgs args;
+            std::copy(h_crops, h_crops + n, args.c);
+            go(args);
         } else {
-            if (n_dev) return hipErrorInvalidValue;  // device counts: the persistent kernel only
-            auto go = [&](auto kern) {
-                hipLaunchKernelGGL(kern, dim3(n), dim3(kThreads), 0, s, crops, fp, d_tables, hist,
-                                   counts);
-            };
-            if (pf == 2) go(k_features_fast<2>);
-            else if (pf == 4) go(k_features_fast<4>);
-            else go(k_features_fast<8>);
+            go(crops);
         }
-        return hipGetLastError();
+    } else if (lc.persistent && queue) {
+        const int grid = std::min<int>(n, std::max(1, lc.wg_per_cu) * num_cus);
+        const int32_t *ord = lc.sorted ? order : nullptr;
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), 0, s, crops, ord, n, fp,
+                               d_tables, hist, counts, queue, n_dev);
+        };
+        if (pf == 2) go(k_features_persistent<2>);
+        else if (pf == 4) go(k_features_persistent<4>);
+        else go(k_features_persistent<8>);
+    } else {
+        if (n_dev) return hipErrorInvalidValue;  // device counts: not one workgroup per crop
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(n), dim3(kThreads), 0, s, crops, fp, d_tables, hist,
+                               counts);
+        };
+        if (pf == 2) go(k_features_fast<2>);
+        else if (pf == 4) go(k_features_fast<4>);
+        else go(k_features_fast<8>);
     }
-    if (n_dev) return hipErrorInvalidValue;  // device counts: the fast configuration only
-    const size_t shmem = (size_t)fp.dim * sizeof(uint32_t);
-    // Above 64 KiB of dynamic LDS (the 256-bin mapping) the kernel must opt in.
-    static size_t shmem_limit = 64 * 1024;
-    if (shmem > shmem_limit) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_features_generic,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)shmem);
-        if (e != hipSuccess) return e;
-        shmem_limit = shmem;
-    }
-    hipLaunchKernelGGL(k_features_generic, dim3(n), dim3(kThreads), shmem, s, crops, fp,
-                       d_tables, hist, counts);
     return hipGetLastError();
 }
 

@@ -54,13 +54,29 @@ struct LaunchCfg {
     int32_t sorted = 1;        // persistent: take crops largest first
 };
 
+// Several workgroups per crop (few or large crops): at most `parts` a crop, of
+// about `px` pixels each; parts = 0: one workgroup per crop. When the kernels
+// read the crop count on the device, px is per crop of the call.
+struct SplitCfg {
+    int32_t parts = 0, px = 0;
+};
+SplitCfg split_for(const CropDesc *crops, int32_t n, const FeatParams &fp);
+// For a launch of up to max_n crops whose count and sizes are known on the
+// device only: split up to 512 crops, in grids whose rows hold the median parts
+// of the largest crop.
+SplitCfg split_for_device_count(int32_t max_n, const FeatParams &fp);
+
 // Kernel launchers (features.hip). All return hipSuccess or the launch error.
-// order / queue may be null (then the launch is one workgroup per crop).
+// order / queue may be null (then the launch is not persistent). h_crops: the
+// crops on the host, at most kArgCrops, for a split launch that needs no table
+// in device memory (crops may then be null).
+constexpr int kArgCrops = 32;
 hipError_t launch_features(const CropDesc *crops, int32_t n, const FeatParams &fp,
                            const uint8_t *d_tables, float *hist, uint32_t *counts,
-                           hipStream_t s, const LaunchCfg &lc = LaunchCfg(),
+                           hipStream_t s, const SplitCfg &split, const LaunchCfg &lc = LaunchCfg(),
                            const int32_t *order = nullptr, uint32_t *queue = nullptr,
-                           int32_t num_cus = 256, const int32_t *n_dev = nullptr);
+                           int32_t num_cus = 256, const int32_t *n_dev = nullptr,
+                           const CropDesc *h_crops = nullptr);
 hipError_t launch_debug_codes(const CropDesc *crop, const FeatParams &fp, uint8_t *gcodes,
                               uint8_t *dcodes, uint8_t *mask, int32_t w, int32_t h,
                               hipStream_t s);
