@@ -151,15 +151,14 @@ hipError_t launch_track(const int32_t *prev, const int32_t *ps, int32_t P, const
 
 // Scoring (score.hip).
 // FP32 scores. Few rows: a kernel that reads W once, over `splits` ranges of
-// D; else, with D a multiple of 32 * splits and 16-byte aligned operands, the
-// 128 x 128-tile kernel over `splits` ranges (partials in part[splits][N][K],
+// D; else, with D a multiple of 32 and 16-byte aligned operands, the product on
+// the BF16 matrix cores over `splits` ranges (partials in part[splits][N][K],
 // summed with the argmax by a second kernel); otherwise the 64 x 64-tile
-// kernels. splits: from score_f32_splits (1 when the tiles alone fill the
-// GPU); 0 selects the 64 x 64-tile kernels.
+// kernels. splits: from score_f32_splits; 0 selects the 64 x 64-tile kernels.
 int32_t score_f32_splits(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_t part_elems);
 // S is always written; argmax (may be null) gets each row's best identity.
-// one_order: sum the tile kernel's way whatever the sizes (the trainer's Gram
-// products, whose steps follow their last bits).
+// one_order: FP32 MFMA tiles whatever the sizes (the trainer's Gram products,
+// whose steps follow their last bits); n_dev: these or the few-rows kernel.
 hipError_t launch_score_f32(const float *X, int32_t N, const float *W, const float *b,
                             int32_t K, int32_t D, float *S, int32_t *argmax, hipStream_t s,
                             int32_t splits = 0, float *part = nullptr,

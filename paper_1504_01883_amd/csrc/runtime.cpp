@@ -658,19 +658,25 @@ lbpf_status lbpf_score(lbpf_ctx *ctx, const float *hist, int32_t N, const lbpf_w
             rows = kLpChunkRows;
         rows = std::min(rows, kLpChunkRows);
     }
-    // FP32 products too small to fill the GPU with 128 x 128 tiles split D
-    // (partials in the context's scratch).
-    const int32_t splits =
-        w->prec == LBPF_FP32
-            ? score_f32_splits(std::min(rows, N), w->K, w->D, ctx->num_cus, kPartElems)
-            : 1;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(s, &cap), "hipStreamIsCapturing");
+    const bool capturing = cap != hipStreamCaptureStatusNone;
+    // FP32 products too small to fill the GPU with tiles split D. The partials
+    // go to the context's score scratch, or to the smaller one where that holds
+    // the scores (or may, for calls running beside a captured graph).
+    const bool roomy = scores_opt && !capturing;
+    float *part = roomy ? ctx->d_scores : ctx->d_part;
+    const size_t part_elems = roomy ? ctx->scores_elems : kPartElems;
+    auto splits_of = [&](int32_t n) {
+        return w->prec == LBPF_FP32
+                   ? score_f32_splits(n, w->K, w->D, ctx->num_cus, part_elems) : 1;
+    };
+    const int32_t splits = splits_of(std::min(rows, N));
     // Calls that use the context's scratch (reduced precision, argmax without
     // caller scores, split D) are ordered across streams by scratch_ev. Under
     // graph capture the graph's own order applies instead.
     const bool uses_scratch = w->prec != LBPF_FP32 || !scores_opt || splits > 1;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    HIP_TRY(hipStreamIsCapturing(s, &cap), "hipStreamIsCapturing");
-    const bool order = uses_scratch && cap == hipStreamCaptureStatusNone;
+    const bool order = uses_scratch && !capturing;
     if (order) HIP_TRY(hipStreamWaitEvent(s, ctx->scratch_ev, 0), "hipStreamWaitEvent");
     for (int32_t n0 = 0; n0 < N; n0 += rows) {
         const int32_t n = std::min(rows, N - n0);
@@ -688,11 +694,9 @@ lbpf_status lbpf_score(lbpf_ctx *ctx, const float *hist, int32_t N, const lbpf_w
                     "score launch");
             continue;
         }
-        const int32_t sp = n == std::min(rows, N)
-                               ? splits
-                               : score_f32_splits(n, w->K, w->D, ctx->num_cus, kPartElems);
+        const int32_t sp = n == std::min(rows, N) ? splits : splits_of(n);
         HIP_TRY(launch_score_f32(hist + (size_t)n0 * D, n, w->W, w->b, w->K, w->D, S,
-                                 argmax_opt ? argmax_opt + n0 : nullptr, s, sp, ctx->d_part),
+                                 argmax_opt ? argmax_opt + n0 : nullptr, s, sp, part),
                 "score launch");
     }
     if (order) HIP_TRY(hipEventRecord(ctx->scratch_ev, s), "hipEventRecord");

@@ -5,8 +5,10 @@
 // FP32 paths:
 //   * k_score_f32_rows (few rows or few identities, D a multiple of 4): operands
 //     straight to registers, D shared by the waves of a workgroup;
-//   * k_score_f32_split (D a multiple of 32 per split, 16-byte aligned rows):
-//     128 x 128 tiles streamed through LDS, described at the kernel;
+//   * k_score_f32_bf16x3 (D a multiple of 32, 16-byte aligned rows): each value
+//     split exactly into three BF16 parts, six BF16 products, FP32 sums;
+//   * k_score_f32_tiles (the same shapes, for callers that keep one order of
+//     summation, and row counts on the device): FP32 MFMA, tiles through LDS;
 //   * k_score_f32 (any D): v_mfma_f32_16x16x4f32 (D[m][n] += sum_k A[m][k]
 //     B[k][n] over a 16 x 16 x 4 block; lane l supplies A[l % 16][l / 16] and
 //     B[l / 16][l % 16] and receives D[4 (l / 16) + t][l % 16], t = 0..3).
@@ -17,6 +19,7 @@
 #include "lbpf_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace lbpf {
 
@@ -192,6 +195,10 @@ __global__ __launch_bounds__(256) void k_argmax(const float *__restrict__ S, int
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(1))) const void glb_void_t;
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
 
 template <int kVm>
 __device__ __forceinline__ void wait_vm() {
@@ -210,27 +217,23 @@ __device__ __forceinline__ void barrier_lds() {
     asm volatile("" ::: "memory");
 }
 
-// --- FP32, 128 x 128 tiles, split feature dimension --------------------------------
+// --- FP32 MFMA, 128 x 128 or 128 x 256 tiles ---------------------------------------
 //
-// A workgroup of 4 waves owns a 128 x 128 tile of S over one of `splits`
-// equal ranges of the feature dimension; wave w computes the 64 x 64 quarter
-// (rows 64 (w & 1), columns 64 (w >> 1)) as 2 x 2 blocks of 32 x 32 (four
-// independent accumulator chains). 128-byte slices of the 128 X rows and 128
-// W rows stream through a ring of kRingN 32 KB stages (global_load_lds; each
+// For callers that keep one order of summation (the trainer's Gram products,
+// whose coordinate steps follow their last bits) and for row counts read on the
+// device. A workgroup of 4 waves owns a 128 x 128 tile of S; wave w computes the
+// 64 x 64 quarter (rows 64 (w & 1), columns 64 (w >> 1)) as 2 x 2 blocks of 32 x
+// 32 (four independent accumulator chains). 128-byte slices of the 128 X rows and
+// 128 W rows stream through a ring of kRingN 32 KB stages (global_load_lds; each
 // wave copies 32 rows of each; chunk c of row r at position c ^ (r % 8)), and
 // a stage's fragments are read one stage ahead. The barrier per stage orders
 // LDS only (barrier_lds), so the copies of later stages stay in flight.
-// With splits > 1 every workgroup stores its partial tile and k_reduce_argmax,
-// queued after it on the same stream, adds the partials in split order and
-// the bias (and takes the argmax in the same pass). (Reducing inside the kernel would need device-scope fences, which
-// on this GPU write back and invalidate the XCD's L2 under the tiles still
-// streaming through it.)
 
 template <int kRingN, int kTK>
-__global__ __launch_bounds__(256) void k_score_f32_split(
+__global__ __launch_bounds__(256) void k_score_f32_tiles(
     const float *__restrict__ X, int32_t N, const float *__restrict__ W,
-    const float *__restrict__ bias, int32_t K, int32_t D, float *__restrict__ S, int32_t splits,
-    float *__restrict__ part, const int32_t *__restrict__ n_dev) {
+    const float *__restrict__ bias, int32_t K, int32_t D, float *__restrict__ S,
+    const int32_t *__restrict__ n_dev) {
     // Tile: 128 feature rows x kTK identities (kTK = 256, 128 or 64); wave w owns
     // rows 64 (w & 1) .. +64 and identities (kTK / 2) (w >> 1) .. + kTK / 2 as
     // 2 x kJB blocks of 32 x 32.
@@ -242,11 +245,10 @@ __global__ __launch_bounds__(256) void k_score_f32_split(
     __shared__ __attribute__((aligned(1024))) uint8_t lds[kRingN * kStage];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave & 1, wn = wave >> 1;
-    const int32_t n0 = blockIdx.x * kTM, k0 = blockIdx.y * kTK, sp = blockIdx.z;
+    const int32_t n0 = blockIdx.x * kTM, k0 = blockIdx.y * kTK;
     if (n_dev) N = *n_dev;  // the grid covers the most rows; tiles past N leave
     if (n0 >= N) return;    // uniform
-    const int32_t dsp = D / splits, d0 = sp * dsp;
-    const int nst = dsp / (kSlice / 4);
+    const int nst = D / (kSlice / 4);
     auto swz = [](int row, int chunk) { return chunk ^ (row & 7); };
 
     // Copy role: X rows 32 w .. +31 (4 copies of 8 rows) and W rows
@@ -259,7 +261,7 @@ __global__ __launch_bounds__(256) void k_score_f32_split(
         const bool isx = j < 4;
         const int row = isx ? wave * 32 + j * 8 + rr : wave * kWRows + (j - 4) * 8 + rr;
         const int32_t g = isx ? min(n0 + row, N - 1) : min(k0 + row, K - 1);
-        src[j] = (isx ? X : W) + (size_t)g * D + d0 + 4 * swz(row, pos);
+        src[j] = (isx ? X : W) + (size_t)g * D + 4 * swz(row, pos);
         dst[j] = isx ? (wave * 32 + j * 8) * kSlice : kTM * kSlice + (wave * kWRows + (j - 4) * 8) * kSlice;
     }
     // Copy j of stage st into ring slot st % kRingN. Stages past the last one
@@ -381,20 +383,262 @@ __global__ __launch_bounds__(256) void k_score_f32_split(
                 }
         }
     };
-    if (splits == 1) {
-        for_each([&](int i, int j, int r, int32_t n, int32_t k) {
-            S[(size_t)n * K + k] = acc[i][j][r] + bias[k];
-        });
-        return;
-    }
-    const size_t plane = (size_t)N * K;
     for_each([&](int i, int j, int r, int32_t n, int32_t k) {
-        part[(size_t)sp * plane + (size_t)n * K + k] = acc[i][j][r];
+        S[(size_t)n * K + k] = acc[i][j][r] + bias[k];
     });
 }
 
-// Split-D epilogue, one wave per row: S = (((part_0 + part_1) + ...) + b in
-// split order, and (optionally) the row's argmax, ties to the lowest index as
+// --- FP32 on the BF16 matrix cores -------------------------------------------------
+//
+// An FP32 value is the exact sum of three BF16 values: h = bf16(v), m =
+// bf16(v - h), l = v - h - m (8 + 8 + 8 significant bits, each remainder exact
+// in FP32). The product keeps the six terms h h, h m, m h, h l, l h, m m; what it
+// drops (m l, l m, l l) is at most 2^-25 of |x w| with either sign. Six BF16 MFMA
+// take 6 / 16 of the FP32 MFMA's cycles for the same product.
+//
+// The matrix cores truncate as they accumulate, so every kFlush stages the
+// accumulators are added (round to nearest) to a running sum and start again
+// from zero. Error against 64 bits, relative to the condition scale, root mean
+// square, against the FP32 MFMA kernel's, 4096 x 1024 x 7552: histograms
+// against enrolled weights 1.8e-8 / 7.2e-8, uniform against normal values
+// 4.5e-9 / 2.7e-8, positive values 9.6e-8 / 1.3e-6, log-normal values over 10
+// decades 9.5e-8 / 5.1e-7 (kFlush 4 to 16 level, without it 2 to 3 times more).
+//
+// A workgroup of 8 waves owns 64 kWN feature rows x 64 kWK identities (256 x 128
+// or 128 x 256) over one of `splits` ranges of the 32-column stages of D; each
+// wave computes 64 x 64 of them as 2 x 2 blocks of 32 x 32. Per stage each thread
+// loads 24 floats (two stages ahead), splits them and writes the three planes into
+// one of two 72 KB LDS buffers (16-byte chunk c of a row at c ^ ((row / 2) % 4));
+// one plane is read by as many waves as a BF16 product's operand would be, but
+// multiplied twice as often. 16384 x 1024 x 7552 1355 us (FP32 MFMA, 128 x 256
+// tiles: 1850), 4096 x 256 103 (135): 1.12 PFLOP/s of BF16, the matrix cores busy
+// 59% at a clock that falls below 2 GHz under them; waves out of step, raised
+// wave priority during the MFMAs, or VALU work interleaved by scheduling barriers
+// gained nothing (1330-1370 us against 1300 before the check below, 25 us of it).
+//
+// A tile is computed again by FP32 MFMAs on operands straight from memory where
+// the split does not hold: a result is not finite (h rounds to infinity, or m =
+// inf - inf), or so small that BF16's last bit, 2^-133, may count: below 2^-96 of
+// the tile's largest value and not 0, or 0 where that is above 2^30 (D up to 2^14
+// keeps 24 bits then).
+constexpr int kX3Waves = 8, kX3MaxSplits = 16;
+
+__device__ __forceinline__ bool finite_f32(float v) {
+    return fabsf(v) <= 3.402823466e38f;
+}
+
+template <int kWN, int kWK>
+__global__ __launch_bounds__(64 * kX3Waves) void k_score_f32_bf16x3(
+    const float *__restrict__ X, int32_t N, const float *__restrict__ W,
+    const float *__restrict__ bias, int32_t K, int32_t D, float *__restrict__ S, int32_t splits,
+    float *__restrict__ part) {
+    static_assert(kWN * kWK == kX3Waves, "64 x 64 per wave");
+    constexpr int kT = 64 * kX3Waves, kFlush = 8, kTN = 64 * kWN, kTK = 64 * kWK;
+    constexpr int kRows = kTN + kTK;              // X rows, then W rows
+    constexpr int kGroups = kRows * 4 / kT;       // 8-column groups a thread splits
+    static_assert(kRows * 4 % kT == 0, "whole groups");
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[2][3][kRows * 64];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wn = wave % kWN, wk = wave / kWN;
+    // Tile order: consecutive workgroups are dealt round-robin to the 8 XCDs;
+    // each XCD takes a contiguous range of logical tiles, walked in groups of
+    // 4 row tiles x all identity tiles, which share their operands in its L2.
+    const int32_t sp = blockIdx.y;
+    const uint32_t KT = (uint32_t)(K + kTK - 1) / kTK, NT = (uint32_t)(N + kTN - 1) / kTN;
+    const uint32_t nwg = gridDim.x, pid = blockIdx.x;
+    const uint32_t xcd = pid & 7u, per = nwg >> 3, rem = nwg & 7u;
+    const uint32_t L = xcd * per + min(xcd, rem) + (pid >> 3);
+    constexpr uint32_t kGroupN = 4;
+    const uint32_t g = L / (kGroupN * KT), i_g = L - g * (kGroupN * KT);
+    const uint32_t gn = min(kGroupN, NT - g * kGroupN);
+    const int32_t n0 = (int32_t)(g * kGroupN + i_g % gn) * kTN;
+    const int32_t k0 = (int32_t)(i_g / gn) * kTK;
+    const int32_t stages = D >> 5;
+    const int32_t st0 = (int32_t)((int64_t)stages * sp / splits);
+    const int32_t st1 = (int32_t)((int64_t)stages * (sp + 1) / splits);
+
+    auto swz = [](int row, int chunk) { return chunk ^ ((row >> 1) & 3); };
+    const float *src[kGroups];
+    int dst[kGroups];
+#pragma unroll
+    for (int i = 0; i < kGroups; ++i) {
+        // Rows past the matrices' ends re-read the last one (not stored).
+        const int row = (i * kT + tid) >> 2, c = tid & 3;
+        const float *base = row < kTN ? X + (size_t)min(n0 + row, N - 1) * D
+                                        : W + (size_t)min(k0 + row - kTN, K - 1) * D;
+        src[i] = base + 8 * c;
+        dst[i] = row * 64 + 16 * swz(row, c);
+    }
+    floatx4 raw[kGroups][2];
+    auto load = [&](int32_t st) {
+#pragma unroll
+        for (int i = 0; i < kGroups; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                raw[i][h] = *reinterpret_cast<const floatx4 *>(src[i] + 32 * st + 4 * h);
+    };
+    const int fr = lane & 31, fq = lane >> 5;
+    floatx16 acc[2][2], sum[2][2];  // [identity block][row block]
+
+    float top[kGroups] = {};  // largest |v|
+    auto store = [&](int b) {
+#pragma unroll
+        for (int i = 0; i < kGroups; ++i) {
+            uintx4 hv, mv, lv;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const floatx2 v = {raw[i][e >> 1][2 * (e & 1)], raw[i][e >> 1][2 * (e & 1) + 1]};
+                asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(top[i]) : "v"(v[0]), "v"(v[1]));
+                // Two a conversion; the pair's halves are floats as they are.
+                auto pack = [](floatx2 f) {
+                    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
+                };
+                auto rest = [](floatx2 f, uint32_t h) {
+                    return floatx2{f[0] - __uint_as_float(h << 16),
+                                   f[1] - __uint_as_float(h & 0xffff0000u)};
+                };
+                hv[e] = pack(v);
+                const floatx2 r = rest(v, hv[e]);
+                mv[e] = pack(r);
+                lv[e] = pack(rest(r, mv[e]));
+            }
+            *reinterpret_cast<uintx4 *>(&lds[b][0][dst[i]]) = hv;
+            *reinterpret_cast<uintx4 *>(&lds[b][1][dst[i]]) = mv;
+            *reinterpret_cast<uintx4 *>(&lds[b][2][dst[i]]) = lv;
+        }
+    };
+    auto stage = [&](int b) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            bf16x8 x[2][3], w[2][3];
+#pragma unroll
+            for (int q = 2; q >= 0; --q)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int rx = wn * 64 + 32 * i + fr, rw = kTN + wk * 64 + 32 * i + fr;
+                    const int c = 2 * s + fq;
+                    x[i][q] = *reinterpret_cast<const bf16x8 *>(&lds[b][q][rx * 64 + 16 * swz(rx, c)]);
+                    w[i][q] = *reinterpret_cast<const bf16x8 *>(&lds[b][q][rw * 64 + 16 * swz(rw, c)]);
+                }
+            constexpr int qw[6] = {2, 0, 1, 1, 0, 0}, qx[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+            for (int t = 0; t < 6; ++t)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+                        acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            w[j][qw[t]], x[i][qx[t]], acc[j][i], 0, 0, 0);
+        }
+    };
+    auto flush = [&](bool first) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                if (first) sum[j][i] = floatx16{};
+                else sum[j][i] += acc[j][i];
+                acc[j][i] = floatx16{};
+            }
+    };
+    flush(true);
+    load(st0);
+    store(0);
+    if (st0 + 1 < st1) load(st0 + 1);
+    __syncthreads();
+    for (int32_t st = st0; st < st1; ++st) {
+        const int b = (st - st0) & 1;
+        if (st + 1 < st1) store(b ^ 1);
+        if (st + 2 < st1) load(st + 2);
+        stage(b);
+        if ((st - st0) % kFlush == kFlush - 1) flush(false);
+        __syncthreads();
+    }
+    flush(false);
+
+    // A split value is off by 2^-134 at most, so a result by 2^-134 D max |v|.
+    uint32_t *most = reinterpret_cast<uint32_t *>(&lds[0][0][0]);
+    float mine = top[0];
+#pragma unroll
+    for (int i = 1; i < kGroups; ++i) mine = fmaxf(mine, top[i]);
+    if (tid == 0) *most = 0;
+    __syncthreads();
+    atomicMax(most, __float_as_uint(mine));
+    __syncthreads();
+    const float all = __uint_as_float(*most);
+    const float small = all * 0x1p-96f, none = all > 0x1p30f ? -1.0f : 0.0f;
+    bool again = false;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float v = fabsf(sum[j][i][r]);
+                again |= !finite_f32(v) || (v < small && v > none);
+            }
+    if (__syncthreads_or(again)) {
+        const float *px[2], *pw[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            px[i] = X + (size_t)min(n0 + wn * 64 + 32 * i + fr, N - 1) * D + 4 * fq;
+            pw[i] = W + (size_t)min(k0 + wk * 64 + 32 * i + fr, K - 1) * D + 4 * fq;
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) sum[j][i] = floatx16{};
+        // MFMA c covers columns c and 4 + c of eight.
+        for (int32_t d = 32 * st0; d < 32 * st1; d += 8) {
+            floatx4 x[2], w[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                x[i] = *reinterpret_cast<const floatx4 *>(px[i] + d);
+                w[i] = *reinterpret_cast<const floatx4 *>(pw[i] + d);
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+                        sum[j][i] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[j][c], x[i][c],
+                                                                         sum[j][i], 0, 0, 0);
+        }
+    }
+    // Register 4 q + t of lane l: identity 8 q + 4 (l / 32) + t, row l % 32.
+    float *out = sp > 0 ? part + (size_t)(sp - 1) * N * K : S;
+    const bool vec = (K & 3) == 0 && ((uintptr_t)out & 15) == 0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int32_t n = n0 + wn * 64 + 32 * i + fr;
+        if (n >= N) continue;
+        float *row = out + (size_t)n * K;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int32_t k = k0 + wk * 64 + 32 * j + 8 * q + 4 * fq;
+                floatx4 v;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    v[t] = sum[j][i][4 * q + t];
+                    if (splits == 1 && k + t < K) v[t] += bias[k + t];
+                }
+                if (vec && k + 3 < K) {
+                    *reinterpret_cast<floatx4 *>(row + k) = v;
+                } else {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        if (k + t < K) row[k + t] = v[t];
+                }
+            }
+    }
+}
+
+// Split-D epilogue, one wave per row: S = (((S + part_0) + part_1) + ...) + b in
+// split order (the first range's sums are in S, the others' in part), and (optionally) the row's argmax, ties to the lowest index as
 // in k_argmax.
 // kVec: K a multiple of 4 and 16-byte aligned rows, so each lane takes four
 // consecutive identities per step as float4.
@@ -402,7 +646,7 @@ template <bool kVec>
 __global__ __launch_bounds__(256) void k_reduce_argmax(const float *__restrict__ part,
                                                        int32_t splits, int32_t N, int32_t K,
                                                        const float *__restrict__ bias,
-                                                       float *__restrict__ S,
+                                                       float *S,
                                                        int32_t *__restrict__ out) {
     const int lane = threadIdx.x & 63;
     const int32_t n = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -412,8 +656,8 @@ __global__ __launch_bounds__(256) void k_reduce_argmax(const float *__restrict__
     int32_t arg = K;
     if constexpr (kVec) {
         for (int32_t k = 4 * lane; k < K; k += 256) {
-            floatx4 v = *reinterpret_cast<const floatx4 *>(part + row + k);
-            for (int q = 1; q < splits; ++q)
+            floatx4 v = *reinterpret_cast<const floatx4 *>(S + row + k);
+            for (int q = 0; q < splits - 1; ++q)
                 v += *reinterpret_cast<const floatx4 *>(part + (size_t)q * plane + row + k);
             v += *reinterpret_cast<const floatx4 *>(bias + k);
             *reinterpret_cast<floatx4 *>(S + row + k) = v;
@@ -426,8 +670,8 @@ __global__ __launch_bounds__(256) void k_reduce_argmax(const float *__restrict__
         }
     } else {
         for (int32_t k = lane; k < K; k += 64) {
-            float v = part[row + k];
-            for (int q = 1; q < splits; ++q) v += part[(size_t)q * plane + row + k];
+            float v = S[row + k];
+            for (int q = 0; q < splits - 1; ++q) v += part[(size_t)q * plane + row + k];
             v += bias[k];
             S[row + k] = v;
             if (v > best || arg == K) {
@@ -612,27 +856,44 @@ __global__ __launch_bounds__(1024) void k_row_argmax(const float *__restrict__ p
 
 }  // namespace
 
-// Identities per tile of the split kernel. On the 4096 x 256 x 7552 product
-// 128 (64 tiles, D split in 4) ran in 164 us and 64 (128 tiles, D split in 2)
-// in 171-176 us.
-constexpr int kSplitTK = 128;
-
-// Products of few rows (at most 32) or of few 64 x 32 blocks (at most one per
-// CU) run k_score_f32_rows: below the line a call's time is W's one pass, above
-// it the blocks' own operand traffic passes that of the 128 x 128 tiles. Whole
-// calls, rows against tiles, D = 7552: 5 x 1024 15 us against 130, 32 x 8192 85
-// against 169, 64 x 8192 (256 blocks) 139 against 171, 128 x 8192 (512) 251
-// against 170, 512 x 1024 (256) 130 against 139, 1024 x 1024 (512) 245 against
-// 150, 1024 x 256 (128) 74 against 132, 2048 x 256 (256) 132 against 135.
-static bool few_rows(int32_t N, int32_t K, int32_t D, int32_t num_cus) {
-    return D % 4 == 0 &&
-           (N <= 32 || (int64_t)((N + 63) / 64) * ((K + 31) / 32) <= (int64_t)num_cus);
+// Products of few rows (at most 32) or of few 64 x 32 blocks run
+// k_score_f32_rows: below the line a call's time is W's one pass, above it the
+// blocks' own operand traffic passes that of the tiles. Where k_score_f32_bf16x3
+// serves the others (x3), up to 3 blocks per 8 CUs, else one per CU. Whole calls
+// in us, rows / x3 / FP32 tiles, D = 7552: 5 x 1024 15 / 63 / 130, 32 x 8192 80 /
+// 190 / 169, 128 x 1024 (64 blocks) 47 / 65 / 134, 512 x 256 (64) 47 / 53 / 131,
+// 256 x 1024 (128) 72 / 68 / 135, 1024 x 256 (128) 73 / 57 / 132, 512 x 1024 (256)
+// 130 / 73 / 139, 64 x 8192 (256) 144 / 160 / 171, 128 x 8192 (512) 251 / 161 / 170.
+static bool few_rows(int32_t N, int32_t K, int32_t D, int32_t num_cus, bool x3) {
+    return D % 4 == 0 && (N <= 32 || (int64_t)((N + 63) / 64) * ((K + 31) / 32) <=
+                                         (x3 ? num_cus * 3 / 8 : num_cus));
 }
 // 16-row blocks of X per workgroup of k_score_f32_rows.
 static int32_t rows_blocks(int32_t N) { return N <= 16 ? 1 : (N <= 32 ? 2 : 4); }
 
+// Split of k_score_f32_bf16x3 with the least time as measured: 2.8 us a stage and
+// round of tiles (of the shape that needs fewer rounds, see launch_score_f32),
+// and the reduce's traffic at 4 TB/s.
+static int32_t x3_splits(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_t part_elems) {
+    const auto tiles = [&](int64_t tn, int64_t tk) { return ((N + tn - 1) / tn) * ((K + tk - 1) / tk); };
+    const int64_t t = std::min(tiles(256, 128), tiles(128, 256));
+    const int32_t stages = D / 32;
+    int32_t best = 1;
+    double least = 0.0;
+    for (int32_t sp = 1; sp <= std::min(kX3MaxSplits, stages); ++sp) {
+        if ((size_t)(sp - 1) * (size_t)N * (size_t)K > part_elems) break;  // S holds one
+        const double us = 2.8 * (double)((t * sp + num_cus - 1) / num_cus) * ((stages + sp - 1) / sp) +
+                          (sp > 1 ? 4.0 + 8.0 * sp * (double)N * (double)K / 4e6 : 0.0);
+        if (sp == 1 || us < least) {
+            least = us;
+            best = sp;
+        }
+    }
+    return best;
+}
+
 int32_t score_f32_splits(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_t part_elems) {
-    if (few_rows(N, K, D, num_cus)) {
+    if (few_rows(N, K, D, num_cus, D % 32 == 0)) {
         // Two workgroups a CU, each wave with at least four 32-column steps.
         const int32_t nb = 16 * rows_blocks(N);
         const int64_t groups = (int64_t)((K + 31) / 32) * ((N + nb - 1) / nb);
@@ -641,15 +902,21 @@ int32_t score_f32_splits(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_
                                         (int64_t)(part_elems / ((size_t)N * (size_t)K))});
         return (int32_t)std::max<int64_t>(sp, 1);
     }
-    const int64_t tiles = (int64_t)((N + 127) / 128) * ((K + kSplitTK - 1) / kSplitTK);
-    int32_t best = 1;
-    for (int32_t sp = 2; sp <= 4; sp *= 2) {
-        if (tiles * best >= num_cus) break;  // enough workgroups already
-        if (D % (32 * sp) != 0) break;
-        if ((size_t)sp * (size_t)N * (size_t)K > part_elems) break;
-        best = sp;
-    }
-    return best;
+    return D % 32 == 0 ? x3_splits(N, K, D, num_cus, part_elems) : 1;
+}
+
+// The partials' sum in split order, the bias and the argmax (argmax may be null).
+static hipError_t launch_reduce(const float *part, int32_t splits, int32_t N, int32_t K,
+                                const float *b, float *S, int32_t *argmax, hipStream_t s) {
+    const bool v4 = K % 4 == 0 && ((uintptr_t)S % 16 == 0) && ((uintptr_t)b % 16 == 0) &&
+                    ((uintptr_t)part % 16 == 0);
+    if (v4)
+        hipLaunchKernelGGL(k_reduce_argmax<true>, dim3((N + 3) / 4), dim3(256), 0, s, part, splits,
+                           N, K, b, S, argmax);
+    else
+        hipLaunchKernelGGL(k_reduce_argmax<false>, dim3((N + 3) / 4), dim3(256), 0, s, part, splits,
+                           N, K, b, S, argmax);
+    return hipGetLastError();
 }
 
 hipError_t launch_score_f32(const float *X, int32_t N, const float *W, const float *b, int32_t K,
@@ -664,7 +931,8 @@ hipError_t launch_score_f32(const float *X, int32_t N, const float *W, const flo
             (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         cus = std::max(cus, 1);
     }
-    if (!one_order && aligned && splits >= 1 && few_rows(N, K, D, cus) && (splits == 1 || part)) {
+    const bool x3 = !n_dev && D % 32 == 0;
+    if (!one_order && aligned && splits >= 1 && few_rows(N, K, D, cus, x3) && (splits == 1 || part)) {
         const int32_t nb = rows_blocks(N);
         const dim3 g((K + 31) / 32, (N + 16 * nb - 1) / (16 * nb), splits);
         auto go = [&](auto kern) {
@@ -680,49 +948,46 @@ hipError_t launch_score_f32(const float *X, int32_t N, const float *W, const flo
                                argmax, n_dev);
         return hipGetLastError();
     }
-    // Unsplit products whose tiles fill the CUs in fewer rounds as 128 x 256:
-    // 256 identities per tile (48 KB stages, two-stage ring, one workgroup of
-    // 434 registers a lane per CU), 4/3 the matrix work per copied byte of the
-    // 128 x 128 tile. A round of 128 x 256 tiles takes about 1.91 rounds of
-    // 128 x 128 ones (16384 x 1024 x 7552: 1858 us in 2 rounds against
-    // 1941-1947 in 4), so the wide tile is taken when 1.91 r256 < r128 (on
-    // 5120 x 5120 x 7552, 4 wide rounds against 7: 3.8 ms against 3.45).
-    const size_t nt = (size_t)((N + 127) / 128);
-    const size_t r128 = (nt * (size_t)((K + 127) / 128) + cus - 1) / cus;
-    const size_t r256 = (nt * (size_t)((K + 255) / 256) + cus - 1) / cus;
-    if (aligned && splits == 1 && D % 32 == 0 && K >= 256 && 191 * r256 < 100 * r128) {
-        const dim3 g((N + 127) / 128, (K + 255) / 256, 1);
-        hipLaunchKernelGGL((k_score_f32_split<2, 256>), g, dim3(256), 0, s, X, N, W, b, K, D, S,
-                           1, part, n_dev);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess || !argmax) return e;
-        return launch_argmax(S, N, K, argmax, s, n_dev);
-    }
-    if (aligned && splits >= 1 && D % (32 * splits) == 0 && (splits == 1 || part)) {
-        dim3 g((N + 127) / 128, (K + kSplitTK - 1) / kSplitTK, splits);
-        // 128 x 128 tiles. At least two tiles per CU (512 on the 256-CU
-        // MI355X): a two-stage ring (64 KB of LDS; the workgroup's 270
-        // registers a lane still leave one workgroup per CU, and a shallower
-        // ring measured faster than four stages: 1940-1946 us against
-        // 1960-1964 on 16384 x 1024 x 7552). Otherwise (fewer tiles, or D
-        // split over workgroups) a four-stage ring.
-        if (splits == 1 && (size_t)g.x * g.y >= 512)
-            hipLaunchKernelGGL((k_score_f32_split<2, kSplitTK>), g, dim3(256), 0, s, X, N, W, b, K,
-                               D, S, splits, part, n_dev);
+    if (!one_order && aligned && x3 && splits >= 1 && (splits == 1 || part)) {
+        // The shape that goes with this many splits.
+        const auto tiles = [&](int tn, int tk) { return ((N + tn - 1) / tn) * ((K + tk - 1) / tk); };
+        const auto rounds = [&](int t) { return ((int64_t)t * splits + cus - 1) / cus; };
+        const int tall = tiles(256, 128), wide = tiles(128, 256);
+        if (rounds(tall) <= rounds(wide))
+            hipLaunchKernelGGL((k_score_f32_bf16x3<4, 2>), dim3(tall, splits), dim3(64 * kX3Waves),
+                               0, s, X, N, W, b, K, D, S, splits, part);
         else
-            hipLaunchKernelGGL((k_score_f32_split<4, kSplitTK>), g, dim3(256), 0, s, X, N, W, b, K,
-                               D, S, splits, part, n_dev);
-        if (splits > 1) {
-            const bool v4 = K % 4 == 0 && ((uintptr_t)S % 16 == 0) && ((uintptr_t)b % 16 == 0);
-            if (v4)
-                hipLaunchKernelGGL(k_reduce_argmax<true>, dim3((N + 3) / 4), dim3(256), 0, s, part,
-                                   splits, N, K, b, S, argmax);
-            else
-                hipLaunchKernelGGL(k_reduce_argmax<false>, dim3((N + 3) / 4), dim3(256), 0, s,
-                                   part, splits, N, K, b, S, argmax);
-            return hipGetLastError();
-        }
-        hipError_t e = hipGetLastError();
+            hipLaunchKernelGGL((k_score_f32_bf16x3<2, 4>), dim3(wide, splits), dim3(64 * kX3Waves),
+                               0, s, X, N, W, b, K, D, S, splits, part);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        if (splits > 1) return launch_reduce(part, splits, N, K, b, S, argmax, s);
+        return argmax ? launch_argmax(S, N, K, argmax, s) : hipSuccess;
+    }
+    if (aligned && D % 32 == 0 && splits >= 1) {
+        // 128 x 256 tiles (48 KB stages, two-stage ring, one workgroup of 434
+        // registers a lane per CU), 4/3 the matrix work per copied byte of the
+        // 128 x 128 tile, where they fill the CUs in fewer rounds: a round of
+        // them takes about 1.91 rounds of 128 x 128 ones (16384 x 1024 x 7552:
+        // 1858 us in 2 rounds against 1941-1947 in 4), so when 1.91 r256 < r128
+        // (on 5120 x 5120 x 7552, 4 wide rounds against 7: 3.8 ms against 3.45).
+        const size_t nt = (size_t)((N + 127) / 128);
+        const size_t r128 = (nt * (size_t)((K + 127) / 128) + cus - 1) / cus;
+        const size_t r256 = (nt * (size_t)((K + 255) / 256) + cus - 1) / cus;
+        const bool wide = K >= 256 && 191 * r256 < 100 * r128;
+        const dim3 g((N + 127) / 128, wide ? (K + 255) / 256 : (K + 127) / 128);
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, g, dim3(256), 0, s, X, N, W, b, K, D, S, n_dev);
+        };
+        // 128 x 128 tiles, at least two per CU (512 on the 256-CU MI355X): a
+        // two-stage ring (64 KB of LDS; the workgroup's 270 registers a lane
+        // still leave one workgroup per CU, and a shallower ring measured faster
+        // than four stages: 1940-1946 us against 1960-1964 on 16384 x 1024 x
+        // 7552). Fewer tiles: a four-stage ring.
+        if (wide) go(k_score_f32_tiles<2, 256>);
+        else if ((size_t)g.x * g.y >= 512) go(k_score_f32_tiles<2, 128>);
+        else go(k_score_f32_tiles<4, 128>);
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess || !argmax) return e;
         return launch_argmax(S, N, K, argmax, s, n_dev);
     }
