@@ -168,8 +168,7 @@ def _roofline(kernels):
     dom = max(kernels, key=lambda k: kernels[k]["ms"])
     dk = kernels[dom]
     return {"kernel": dom, "bound": dk["bound"], "achieved": dk["achieved"], "peak": dk["peak"],
-            "unit": dk["unit"], "frac": dk["frac"], "traffic": dk["traffic"],
-            **({"bf16_products": dk["bf16_products"]} if "bf16_products" in dk else {})}
+            "unit": dk["unit"], "frac": dk["frac"], "traffic": dk["traffic"]}
 
 
 def _timed_steps(step, steps, warmup):
