@@ -696,7 +696,8 @@ lbpf_status lbpf_score(lbpf_ctx *ctx, const float *hist, int32_t N, const lbpf_w
         }
         const int32_t sp = n == std::min(rows, N) ? splits : splits_of(n);
         HIP_TRY(launch_score_f32(hist + (size_t)n0 * D, n, w->W, w->b, w->K, w->D, S,
-                                 argmax_opt ? argmax_opt + n0 : nullptr, s, sp, part),
+                                 argmax_opt ? argmax_opt + n0 : nullptr, s, sp, part, nullptr, false,
+                                 score_f32_ranges(n, w->K, w->D, ctx->num_cus, kPartElems)),
                 "score launch");
     }
     if (order) HIP_TRY(hipEventRecord(ctx->scratch_ev, s), "hipEventRecord");
@@ -799,7 +800,8 @@ lbpf_status lbpf_pipeline_create(lbpf_ctx *ctx, const lbpf_weights *w, int32_t m
             el = launch_features(d_crops, max_boxes, ctx->fp, ctx->d_bins, hist, nullptr, cs,
                                  split, lc, d_order, p->d_queue, ctx->num_cus, d_n);
         if (el == hipSuccess && !lp)
-            el = launch_score_f32(hist, max_boxes, w->W, w->b, K, D, S, argmax, cs, 1, nullptr, d_n);
+            el = launch_score_f32(hist, max_boxes, w->W, w->b, K, D, S, argmax, cs, 1, nullptr, d_n,
+                                  false, 1);
         if (el == hipSuccess && lp)
             el = launch_quant_rows(hist, max_boxes, D, w->prec, p->d_xq, p->d_sx, cs, d_n);
         if (el == hipSuccess && lp)

@@ -144,19 +144,198 @@ __global__ __launch_bounds__(512) void k_score_f32(const float *__restrict__ X, 
     }
 }
 
-// One wave per row: lanes scan k = lane, lane + 64, ... keeping the first
-// (lowest k) maximum, then a butterfly picks the larger value, or the lower
-// index on equal values.
-__global__ __launch_bounds__(256) void k_argmax(const float *__restrict__ S, int32_t N, int32_t K,
+// --- Close decisions -----------------------------------------------------------------
+//
+// The named identity does not depend on which FP32 kernel made the scores: where a
+// row's best scores lie within what two orders of summation differ by, those scores
+// are summed again in one fixed order, that of k_score_f32_tiles (per range of D,
+// each eight columns as 0 4 1 5 2 6 3 7, an FMA each; the ranges' sums in order; the
+// bias), written over the others and compared. Within: 2^-17 of the best one's
+// |x w| + |b|, 30 times the usual difference; about 1 row in 8000 of a gallery's (a
+// wave takes 45 us over 7552 columns in one range, 12 in four: 16384 x 1024 1315 us
+// with no such row, 1355 with some; with one in every row 3490).
+struct Closest {
+    float best = -INFINITY, second = -INFINITY;
+    int32_t arg;  // larger than any valid index at first
+    bool nan = false;
+    __device__ explicit Closest(int32_t K) : arg(K) {}
+    __device__ __forceinline__ void see(float v, int32_t k, int32_t K) {
+        second = fmaxf(second, fminf(v, best));
+        nan |= v != v;
+        if (v > best || arg == K) {
+            best = v;
+            arg = k;
+        }
+    }
+    __device__ __forceinline__ void take(float ob, int32_t oa, float os) {
+        second = fmaxf(fmaxf(second, os), fminf(best, ob));
+        if (ob > best || (ob == best && oa < arg)) {
+            best = ob;
+            arg = oa;
+        }
+    }
+    __device__ __forceinline__ void reduce_wave() {
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            const float ob = __shfl_xor(best, off, 64), os = __shfl_xor(second, off, 64);
+            take(ob, __shfl_xor(arg, off, 64), os);
+        }
+        nan = __ballot(nan) != 0;
+    }
+    // Scores from here on are close; no number where none is to be settled. After
+    // reduce_wave, and alike in all lanes (a row without NaN).
+    __device__ __forceinline__ float floor(const float *__restrict__ b) const {
+        if (nan) return NAN;
+        const float bias = b[arg], scale = fabsf(best - bias) + fabsf(bias);
+        return scale < 1e37f ? best - 0x1p-17f * scale : NAN;
+    }
+};
+
+constexpr int kSettleRows = 3;       // candidates a turn
+constexpr int kSettlePieces = 2;     // of 256 columns a step
+constexpr int kSettleStride = 532;   // floats of LDS a row, its 1, 2 or 4 ranges 4 apart
+constexpr int kSettleLds = (1 + kSettleRows) * kSettleStride + 16;
+
+// One wave: row S_n's closest scores again, and the identity. ranges: 1, 2 or 4, D a
+// multiple of 32 ranges.
+__device__ int32_t settle(const float *__restrict__ x, const float *__restrict__ W,
+                          const float *__restrict__ b, float *S_n, int32_t K, int32_t D, int ranges,
+                          const Closest &row, float floor, float *lds) {
+    const int lane = threadIdx.x & 63;
+    __threadfence_block();  // the row's scores, written by other lanes
+    auto score = [&](int32_t k) { return k < K ? S_n[min(k, K - 1)] : -INFINITY; };
+    // More than a wave's worth, all alike: rows of W or X that are the same, not chance.
+    int32_t many = 0;
+    bool alike = true;
+#pragma unroll 8
+    for (int32_t k0 = 0; k0 < K; k0 += 64) {
+        const float v = score(k0 + lane);
+        many += __builtin_popcountll(__ballot(v >= floor));
+        alike = alike && __ballot(v >= floor && v != row.best) == 0;
+    }
+    if (many > 64 && alike) return row.arg;
+
+    // Lane l copies columns 4 (l % per) .. + 3 of a piece of range l / per; lane c *
+    // ranges + r sums range r of candidate c.
+    const int per = 64 / ranges, cols = 4 * per * kSettlePieces;  // of a range, a step
+    const int32_t len = D / ranges;
+    const int32_t at = 4 * (lane % per), from = (lane / per) * len;
+    const int to = (lane / per) * (cols + 4) + at;
+    const int mine = lane % ranges, of = lane / ranges;
+    float best = -INFINITY;
+    int32_t arg = K;
+    int32_t cand = 0;  // lane c: candidate c
+    int n = 0;
+    auto turn = [&]() {
+        float acc = 0.0f;
+        floatx4 v[1 + kSettleRows][kSettlePieces];
+        auto load = [&](int32_t c0) {
+#pragma unroll
+            for (int c = 0; c <= kSettleRows; ++c) {
+                if (c > n) break;  // uniform
+                const float *src =
+                    c == 0 ? x : W + (size_t)__builtin_amdgcn_readlane(cand, c - 1) * D;
+#pragma unroll
+                for (int p = 0; p < kSettlePieces; ++p) {
+                    const int32_t d = c0 + 4 * per * p + at;
+                    v[c][p] = *reinterpret_cast<const floatx4 *>(src + from + min(d, len - 4));
+                    if (d >= len) v[c][p] = floatx4{};  // nothing to add
+                }
+            }
+        };
+        load(0);
+        for (int32_t c0 = 0; c0 < len; c0 += cols) {
+#pragma unroll
+            for (int c = 0; c <= kSettleRows; ++c) {
+                if (c > n) break;
+#pragma unroll
+                for (int p = 0; p < kSettlePieces; ++p)
+                    *reinterpret_cast<floatx4 *>(lds + c * kSettleStride + to + 4 * per * p) = v[c][p];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (c0 + cols < len) load(c0 + cols);
+            if (of < n) {
+                const float *px = lds + mine * (cols + 4), *pw = px + (1 + of) * kSettleStride;
+                // An LDS read's time is that of 16 columns' FMAs: read as far ahead
+                // (past the row's end at last, into what the buffer has room for).
+                floatx4 x0[4], w0[4], x1[4], w1[4];
+                auto read = [&](floatx4(&xs)[4], floatx4(&ws)[4], int j) {
+#pragma unroll
+                    for (int h = 0; h < 4; ++h) {
+                        xs[h] = *reinterpret_cast<const floatx4 *>(px + j + 4 * h);
+                        ws[h] = *reinterpret_cast<const floatx4 *>(pw + j + 4 * h);
+                    }
+                };
+                auto chain = [&](const floatx4(&xs)[4], const floatx4(&ws)[4]) {
+#pragma unroll
+                    for (int h = 0; h < 4; h += 2)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            acc = __builtin_fmaf(xs[h][e], ws[h][e], acc);
+                            acc = __builtin_fmaf(xs[h + 1][e], ws[h + 1][e], acc);
+                        }
+                };
+                read(x0, w0, 0);
+                for (int j = 0; j < cols; j += 32) {
+                    read(x1, w1, j + 16);
+                    __builtin_amdgcn_sched_barrier(0);
+                    chain(x0, w0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    read(x0, w0, j + 32);
+                    __builtin_amdgcn_sched_barrier(0);
+                    chain(x1, w1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+        for (int c = 0; c < n; ++c) {
+            float t = __shfl(acc, c * ranges, 64);
+            for (int r = 1; r < ranges; ++r) t += __shfl(acc, c * ranges + r, 64);
+            const int32_t k = __builtin_amdgcn_readlane(cand, c);
+            t += b[k];
+            if (lane == 0) S_n[k] = t;
+            if (t > best || arg == K) {
+                best = t;
+                arg = k;
+            }
+        }
+        n = 0;
+    };
+    for (int32_t k0 = 0; k0 < K; k0 += 64 * 8) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = score(k0 + 64 * u + lane);
+        for (int u = 0; u < 8; ++u) {
+            uint64_t m = 0;
+#pragma unroll
+            for (int w = 0; w < 8; ++w)
+                if (w == u) m = __ballot(v[w] >= floor);
+            while (m) {
+                if (lane == n) cand = k0 + 64 * u + __builtin_ctzll(m);
+                m &= m - 1;
+                if (++n == kSettleRows) turn();
+            }
+        }
+    }
+    if (n) turn();
+    return arg;
+}
+
+template <bool kSettle>
+__global__ __launch_bounds__(256) void k_argmax(float *S, int32_t N, int32_t K,
                                                 int32_t *__restrict__ out,
-                                                const int32_t *__restrict__ n_dev) {
+                                                const int32_t *__restrict__ n_dev,
+                                                const float *__restrict__ X,
+                                                const float *__restrict__ W,
+                                                const float *__restrict__ b, int32_t D,
+                                                int ranges) {
     const int lane = threadIdx.x & 63;
     if (n_dev) N = *n_dev;
     const int32_t n = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (n >= N) return;
-    const float *row = S + (size_t)n * K;
-    float best = -INFINITY;
-    int32_t arg = K;  // larger than any valid index
+    float *row = S + (size_t)n * K;
+    Closest c(K);
     if ((K & 3) == 0 && ((uintptr_t)S & 15) == 0) {
         // Four consecutive identities a lane per step (16-byte loads), still
         // scanned in increasing order within the lane.
@@ -165,31 +344,19 @@ __global__ __launch_bounds__(256) void k_argmax(const float *__restrict__ S, int
         for (int32_t k = 4 * lane; k < K; k += 256) {
             const f4 v = *reinterpret_cast<const f4 *>(row + k);
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (v[e] > best || arg == K) {
-                    best = v[e];
-                    arg = k + e;
-                }
+            for (int e = 0; e < 4; ++e) c.see(v[e], k + e, K);
         }
     } else {
-        for (int32_t k = lane; k < K; k += 64) {
-            float v = row[k];
-            if (v > best || arg == K) {
-                best = v;
-                arg = k;
-            }
-        }
+        for (int32_t k = lane; k < K; k += 64) c.see(row[k], k, K);
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        float ob = __shfl_xor(best, off, 64);
-        int32_t oa = __shfl_xor(arg, off, 64);
-        if (ob > best || (ob == best && oa < arg)) {
-            best = ob;
-            arg = oa;
-        }
+    c.reduce_wave();
+    if constexpr (kSettle) {
+        __shared__ float lds[4][kSettleLds];
+        const float floor = c.floor(b);
+        if (c.second >= floor)  // uniform
+            c.arg = settle(X + (size_t)n * D, W, b, row, K, D, ranges, c, floor, lds[threadIdx.x >> 6]);
     }
-    if (lane == 0) out[n] = arg;
+    if (lane == 0) out[n] = c.arg;
 }
 
 typedef __attribute__((address_space(3))) void lds_void_t;
@@ -228,8 +395,11 @@ __device__ __forceinline__ void barrier_lds() {
 // wave copies 32 rows of each; chunk c of row r at position c ^ (r % 8)), and
 // a stage's fragments are read one stage ahead. The barrier per stage orders
 // LDS only (barrier_lds), so the copies of later stages stay in flight.
+// kGram: X = W and no bias, so S is its own mirror image to the last bit; tiles
+// below the diagonal are left out and the others written twice (5120 x 5120 x
+// 7552: 3460 us for all tiles, 2040 so).
 
-template <int kRingN, int kTK>
+template <int kRingN, int kTK, bool kGram>
 __global__ __launch_bounds__(256) void k_score_f32_tiles(
     const float *__restrict__ X, int32_t N, const float *__restrict__ W,
     const float *__restrict__ bias, int32_t K, int32_t D, float *__restrict__ S,
@@ -248,6 +418,7 @@ __global__ __launch_bounds__(256) void k_score_f32_tiles(
     const int32_t n0 = blockIdx.x * kTM, k0 = blockIdx.y * kTK;
     if (n_dev) N = *n_dev;  // the grid covers the most rows; tiles past N leave
     if (n0 >= N) return;    // uniform
+    if (kGram && k0 + kTK <= n0) return;  // the mirror image of another tile
     const int nst = D / (kSlice / 4);
     auto swz = [](int row, int chunk) { return chunk ^ (row & 7); };
 
@@ -384,7 +555,9 @@ __global__ __launch_bounds__(256) void k_score_f32_tiles(
         }
     };
     for_each([&](int i, int j, int r, int32_t n, int32_t k) {
-        S[(size_t)n * K + k] = acc[i][j][r] + bias[k];
+        const float v = acc[i][j][r] + bias[k];
+        S[(size_t)n * K + k] = v;
+        if constexpr (kGram) S[(size_t)k * K + n] = v;
     });
 }
 
@@ -646,14 +819,15 @@ template <bool kVec>
 __global__ __launch_bounds__(256) void k_reduce_argmax(const float *__restrict__ part,
                                                        int32_t splits, int32_t N, int32_t K,
                                                        const float *__restrict__ bias,
-                                                       float *S,
-                                                       int32_t *__restrict__ out) {
+                                                       float *S, int32_t *__restrict__ out,
+                                                       const float *__restrict__ X,
+                                                       const float *__restrict__ W, int32_t D,
+                                                       int ranges) {
     const int lane = threadIdx.x & 63;
     const int32_t n = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (n >= N) return;
     const size_t plane = (size_t)N * K, row = (size_t)n * K;
-    float best = -INFINITY;
-    int32_t arg = K;
+    Closest c(K);
     if constexpr (kVec) {
         for (int32_t k = 4 * lane; k < K; k += 256) {
             floatx4 v = *reinterpret_cast<const floatx4 *>(S + row + k);
@@ -662,11 +836,7 @@ __global__ __launch_bounds__(256) void k_reduce_argmax(const float *__restrict__
             v += *reinterpret_cast<const floatx4 *>(bias + k);
             *reinterpret_cast<floatx4 *>(S + row + k) = v;
 #pragma unroll
-            for (int c = 0; c < 4; ++c)  // k + c ascending: a strict > keeps the first
-                if (v[c] > best || arg == K) {
-                    best = v[c];
-                    arg = k + c;
-                }
+            for (int e = 0; e < 4; ++e) c.see(v[e], k + e, K);  // ascending: the first is kept
         }
     } else {
         for (int32_t k = lane; k < K; k += 64) {
@@ -674,23 +844,17 @@ __global__ __launch_bounds__(256) void k_reduce_argmax(const float *__restrict__
             for (int q = 0; q < splits - 1; ++q) v += part[(size_t)q * plane + row + k];
             v += bias[k];
             S[row + k] = v;
-            if (v > best || arg == K) {
-                best = v;
-                arg = k;
-            }
+            c.see(v, k, K);
         }
     }
     if (!out) return;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const float ob = __shfl_xor(best, off, 64);
-        const int32_t oa = __shfl_xor(arg, off, 64);
-        if (ob > best || (ob == best && oa < arg)) {
-            best = ob;
-            arg = oa;
-        }
-    }
-    if (lane == 0) out[n] = arg;
+    c.reduce_wave();
+    __shared__ float lds[4][kSettleLds];
+    const float floor = ranges ? c.floor(bias) : NAN;
+    if (c.second >= floor)  // uniform
+        c.arg = settle(X + (size_t)n * D, W, bias, S + row, K, D, ranges, c, floor,
+                       lds[threadIdx.x >> 6]);
+    if (lane == 0) out[n] = c.arg;
 }
 
 // --- FP32, few feature rows ---------------------------------------------------------
@@ -798,16 +962,20 @@ __global__ __launch_bounds__(512) void k_score_f32_rows(
 __global__ __launch_bounds__(1024) void k_row_argmax(const float *__restrict__ part, int32_t splits,
                                                      int32_t N, int32_t K,
                                                      const float *__restrict__ bias,
-                                                     float *__restrict__ S,
+                                                     float *S,
                                                      int32_t *__restrict__ out,
-                                                     const int32_t *__restrict__ n_dev) {
-    __shared__ float sv[16];
+                                                     const int32_t *__restrict__ n_dev,
+                                                     const float *__restrict__ X,
+                                                     const float *__restrict__ W, int32_t D,
+                                                     int ranges) {
+    __shared__ float sv[16], ss[16];
+    __shared__ bool sn[16];
     __shared__ int32_t sa[16];
+    __shared__ float lds[kSettleLds];
     const int32_t n = blockIdx.x;
     if (n_dev && n >= *n_dev) return;  // uniform
     const size_t plane = (size_t)N * K, row = (size_t)n * K;
-    float best = -INFINITY;
-    int32_t arg = K;  // larger than any valid index
+    Closest c(K);
     for (int32_t k = threadIdx.x; k < K; k += blockDim.x) {
         float v;
         if (splits > 1) {
@@ -825,33 +993,27 @@ __global__ __launch_bounds__(1024) void k_row_argmax(const float *__restrict__ p
         } else {
             v = S[row + k];
         }
-        if (v > best || arg == K) {
-            best = v;
-            arg = k;
-        }
+        c.see(v, k, K);
     }
     if (!out) return;
-    auto take = [&](float ob, int32_t oa) {
-        if (ob > best || (ob == best && oa < arg)) {
-            best = ob;
-            arg = oa;
-        }
-    };
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const float ob = __shfl_xor(best, off, 64);
-        const int32_t oa = __shfl_xor(arg, off, 64);
-        take(ob, oa);
-    }
+    c.reduce_wave();
+    const int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) {
-        sv[threadIdx.x >> 6] = best;
-        sa[threadIdx.x >> 6] = arg;
+        sv[wave] = c.best;
+        ss[wave] = c.second;
+        sn[wave] = c.nan;
+        sa[wave] = c.arg;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < (int)(blockDim.x >> 6); ++w) take(sv[w], sa[w]);
-        out[n] = arg;
+    if (wave != 0) return;
+    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) {
+        c.take(sv[w], sa[w], ss[w]);
+        c.nan |= sn[w];
     }
+    const float floor = ranges ? c.floor(bias) : NAN;
+    if (c.second >= floor)  // uniform
+        c.arg = settle(X + (size_t)n * D, W, bias, S + row, K, D, ranges, c, floor, lds);
+    if (threadIdx.x == 0) out[n] = c.arg;
 }
 
 }  // namespace
@@ -905,23 +1067,36 @@ int32_t score_f32_splits(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_
     return D % 32 == 0 ? x3_splits(N, K, D, num_cus, part_elems) : 1;
 }
 
+int32_t score_f32_ranges(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_t part_elems) {
+    const int64_t tiles = (int64_t)((N + 127) / 128) * ((K + 127) / 128);
+    int32_t best = 1;
+    for (int32_t sp = 2; sp <= 4; sp *= 2) {
+        if (tiles * best >= num_cus || D % (32 * sp) != 0 ||
+            (size_t)sp * (size_t)N * (size_t)K > part_elems)
+            break;
+        best = sp;
+    }
+    return best;
+}
+
 // The partials' sum in split order, the bias and the argmax (argmax may be null).
 static hipError_t launch_reduce(const float *part, int32_t splits, int32_t N, int32_t K,
-                                const float *b, float *S, int32_t *argmax, hipStream_t s) {
+                                const float *b, float *S, int32_t *argmax, hipStream_t s,
+                                const float *X, const float *W, int32_t D, int ranges) {
     const bool v4 = K % 4 == 0 && ((uintptr_t)S % 16 == 0) && ((uintptr_t)b % 16 == 0) &&
                     ((uintptr_t)part % 16 == 0);
     if (v4)
         hipLaunchKernelGGL(k_reduce_argmax<true>, dim3((N + 3) / 4), dim3(256), 0, s, part, splits,
-                           N, K, b, S, argmax);
+                           N, K, b, S, argmax, X, W, D, ranges);
     else
         hipLaunchKernelGGL(k_reduce_argmax<false>, dim3((N + 3) / 4), dim3(256), 0, s, part, splits,
-                           N, K, b, S, argmax);
+                           N, K, b, S, argmax, X, W, D, ranges);
     return hipGetLastError();
 }
 
 hipError_t launch_score_f32(const float *X, int32_t N, const float *W, const float *b, int32_t K,
                             int32_t D, float *S, int32_t *argmax, hipStream_t s, int32_t splits,
-                            float *part, const int32_t *n_dev, bool one_order) {
+                            float *part, const int32_t *n_dev, bool one_order, int32_t ranges) {
     if (N <= 0 || K <= 0) return hipSuccess;
     const bool aligned = ((uintptr_t)X % 16 == 0) && ((uintptr_t)W % 16 == 0);
     int cus = 256;
@@ -945,7 +1120,7 @@ hipError_t launch_score_f32(const float *X, int32_t N, const float *W, const flo
         else tail ? go(k_score_f32_rows<4, true>) : go(k_score_f32_rows<4, false>);
         if (splits > 1 || argmax)
             hipLaunchKernelGGL(k_row_argmax, dim3(N), dim3(K > 512 ? 1024 : 256), 0, s, part, splits, N, K, b, S,
-                               argmax, n_dev);
+                               argmax, n_dev, X, W, D, D % 32 == 0 ? ranges : 0);
         return hipGetLastError();
     }
     if (!one_order && aligned && x3 && splits >= 1 && (splits == 1 || part)) {
@@ -961,8 +1136,12 @@ hipError_t launch_score_f32(const float *X, int32_t N, const float *W, const flo
                                0, s, X, N, W, b, K, D, S, splits, part);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        if (splits > 1) return launch_reduce(part, splits, N, K, b, S, argmax, s);
-        return argmax ? launch_argmax(S, N, K, argmax, s) : hipSuccess;
+        if (splits > 1) return launch_reduce(part, splits, N, K, b, S, argmax, s, X, W, D, ranges);
+        if (!argmax) return hipSuccess;
+        if (ranges == 0) return launch_argmax(S, N, K, argmax, s);
+        hipLaunchKernelGGL(k_argmax<true>, dim3((N + 3) / 4), dim3(256), 0, s, S, N, K, argmax, n_dev,
+                           X, W, b, D, ranges);
+        return hipGetLastError();
     }
     if (aligned && D % 32 == 0 && splits >= 1) {
         // 128 x 256 tiles (48 KB stages, two-stage ring, one workgroup of 434
@@ -984,9 +1163,11 @@ hipError_t launch_score_f32(const float *X, int32_t N, const float *W, const flo
         // still leave one workgroup per CU, and a shallower ring measured faster
         // than four stages: 1940-1946 us against 1960-1964 on 16384 x 1024 x
         // 7552). Fewer tiles: a four-stage ring.
-        if (wide) go(k_score_f32_tiles<2, 256>);
-        else if ((size_t)g.x * g.y >= 512) go(k_score_f32_tiles<2, 128>);
-        else go(k_score_f32_tiles<4, 128>);
+        const bool gram = one_order && X == W && N == K;
+        if (wide) gram ? go(k_score_f32_tiles<2, 256, true>) : go(k_score_f32_tiles<2, 256, false>);
+        else if ((size_t)g.x * g.y >= 512)
+            gram ? go(k_score_f32_tiles<2, 128, true>) : go(k_score_f32_tiles<2, 128, false>);
+        else gram ? go(k_score_f32_tiles<4, 128, true>) : go(k_score_f32_tiles<4, 128, false>);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess || !argmax) return e;
         return launch_argmax(S, N, K, argmax, s, n_dev);
@@ -1006,7 +1187,8 @@ hipError_t launch_score_f32(const float *X, int32_t N, const float *W, const flo
 hipError_t launch_argmax(const float *S, int32_t N, int32_t K, int32_t *argmax, hipStream_t s,
                          const int32_t *n_dev) {
     if (N <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_argmax, dim3((N + 3) / 4), dim3(256), 0, s, S, N, K, argmax, n_dev);
+    hipLaunchKernelGGL(k_argmax<false>, dim3((N + 3) / 4), dim3(256), 0, s, const_cast<float *>(S), N,
+                       K, argmax, n_dev, nullptr, nullptr, nullptr, 0, 0);
     return hipGetLastError();
 }
 
