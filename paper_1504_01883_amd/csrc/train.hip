@@ -251,7 +251,7 @@ hipError_t launch_train_j(const TrainArgs &a, hipStream_t s) {
 // 64 samples of the epoch's order at once (one LDS read of g per lane), takes
 // the first whose projected gradient is not 0, updates, and tests again from
 // the sample after it: the same steps as visiting the samples one by one.
-// A second wave draws the next epoch's order meanwhile. FP32 throughout.
+// Other waves draw the next epochs' orders meanwhile. FP32 throughout.
 
 __device__ __forceinline__ float wave_sum_f32(float v) {
 #pragma unroll
@@ -260,28 +260,7 @@ __device__ __forceinline__ float wave_sum_f32(float v) {
 }
 
 typedef float gf4 __attribute__((ext_vector_type(4)));
-
-// Eight 16-byte pieces of LDS at byte offsets 0, 1024, .., 7168 from addr,
-// waited for in the same block: the eight results land in distinct registers,
-// so the reads go out back to back. The outputs are early-clobber: a read
-// that returns while later ones are still being issued must not land in the
-// address register.
-__device__ __forceinline__ void lds_read8(uint32_t addr, gf4 (&v)[8]) {
-    asm volatile(
-        "ds_read_b128 %0, %8\n\t"
-        "ds_read_b128 %1, %8 offset:1024\n\t"
-        "ds_read_b128 %2, %8 offset:2048\n\t"
-        "ds_read_b128 %3, %8 offset:3072\n\t"
-        "ds_read_b128 %4, %8 offset:4096\n\t"
-        "ds_read_b128 %5, %8 offset:5120\n\t"
-        "ds_read_b128 %6, %8 offset:6144\n\t"
-        "ds_read_b128 %7, %8 offset:7168\n\t"
-        "s_waitcnt lgkmcnt(0)"
-        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]),
-          "=&v"(v[7])
-        : "v"(addr)
-        : "memory");
-}
+typedef float gf4u __attribute__((ext_vector_type(4), aligned(4)));  // a row of G
 
 __device__ __forceinline__ float readlane_f(float v, int l) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
@@ -301,19 +280,26 @@ __global__ __launch_bounds__(256) void k_gram_diag(const float *__restrict__ G, 
 }
 
 // sigma = 1 / (lower median of the norms), 1 when that median is 0: the
-// element of rank (N-1)/2, ties ranked by index.
+// element of rank (N-1)/2, ties ranked by index. 16 elements a workgroup, each
+// compared with all by 16 lanes (a lane for each element and N serial loads: 293 us
+// at N = 5120, 17 us so).
 __global__ __launch_bounds__(256) void k_gram_sigma(const float *__restrict__ norms, int32_t N,
                                                     float *__restrict__ sigma) {
-    const uint32_t want = (uint32_t)(N - 1) / 2;
-    for (int32_t i = blockIdx.x * 256 + threadIdx.x; i < N; i += gridDim.x * 256) {
-        const float v = norms[i];
-        uint32_t rank = 0;
-        for (int32_t j = 0; j < N; ++j) {
-            const float u = norms[j];
-            rank += (u < v || (u == v && j < i)) ? 1u : 0u;
-        }
-        if (rank == want) *sigma = v > 0.0f ? 1.0f / v : 1.0f;
+    __shared__ uint32_t rank[16];
+    const int e = threadIdx.x & 15, part = threadIdx.x >> 4;
+    const int32_t i = min((int32_t)blockIdx.x * 16 + e, N - 1);
+    if (threadIdx.x < 16) rank[threadIdx.x] = 0;
+    __syncthreads();
+    const float v = norms[i];
+    uint32_t r = 0;
+#pragma unroll 8
+    for (int32_t j = part; j < N; j += 16) {
+        const float u = norms[j];
+        r += (u < v || (u == v && j < i)) ? 1u : 0u;
     }
+    atomicAdd(&rank[e], r);
+    __syncthreads();
+    if (part == 0 && rank[e] == (uint32_t)(N - 1) / 2) *sigma = v > 0.0f ? 1.0f / v : 1.0f;
 }
 
 // A[k][i] = alpha[k][i] y_ki, the left operand of a warm start's margins.
@@ -346,9 +332,9 @@ struct GramArgs {
 // the identity, i = N-1 down to 1 swapping i with r mod (i+1), r = draw
 // e(N-1) + (N-1-i) of the class's splitmix64 stream; segment s takes the
 // steps i in [max(1, N - (s+1) L), N-1 - s L], L = ceil((N-1) / nseg), and
-// segment 0 first writes the identity. One wave: the draws of 64 swaps in
-// parallel, then the swaps one after another by lane 0 (each needs the
-// previous one's result).
+// segment 0 first writes the identity. One wave, 64 swaps at a time: a swap waits
+// for the last one before it that touched one of its two entries, and runs of swaps
+// that wait for none of their own run go at once.
 __device__ void gram_order(int16_t *ord, int32_t N, uint64_t state0, int32_t e, int seg, int nseg,
                            int lane) {
     if (seg == 0)
@@ -358,44 +344,82 @@ __device__ void gram_order(int16_t *ord, int32_t N, uint64_t state0, int32_t e, 
     const uint64_t base = (uint64_t)e * (uint64_t)(N - 1);
     for (int32_t top = hi; top >= lo; top -= 64) {
         const int32_t i = top - lane;
-        int32_t j = 0;
+        int32_t j = -1;
         if (i >= lo) {
             const uint64_t r = splitmix64_at(state0, base + (uint64_t)(N - 1 - i));
             j = (int32_t)(r % (uint64_t)(i + 1));
         }
         const int cnt = min(64, top - lo + 1);
+        // Entry i of a swap is touched before only as an earlier one's j.
+        int last = -1;
         for (int t = 0; t < cnt; ++t) {
             const int32_t jt = __builtin_amdgcn_readlane(j, t);
-            const int32_t it = top - t;
-            if (lane == 0) {
-                const int16_t u = ord[it], v = ord[jt];
-                ord[it] = v;
-                ord[jt] = u;
+            if (lane > t && (j == jt || i == jt)) last = t;
+        }
+        for (int t = 0; t < cnt;) {  // swaps t .. end - 1
+            const uint64_t wait = __ballot(lane > t && lane < cnt && last >= t);
+            const int end = wait ? __builtin_ctzll(wait) : cnt;
+            if (lane >= t && lane < end) {
+                const int16_t u = ord[i], v = ord[j];
+                ord[i] = v;
+                ord[j] = u;
             }
+            t = end;
         }
     }
 }
 
-// One workgroup per class: wave 0 solves, waves 1..W draw epoch orders
-// (W = blockDim / 64 - 1). The order of epoch f is built by wave 1 + f mod W
+// A block of 64 samples of the epoch's order, one a lane, and G of the header
+// comment under the present g and c. An update's time is its instructions and
+// their latency, so what the block fixes is worked out once.
+struct GramBlock {
+    int32_t i;
+    float y, al, q, G;
+    uint64_t lower, upper, inside;  // lanes with alpha <= 0, >= C, between; valid ones
+};
+
+// One workgroup per class: waves 0..kS-1 solve, waves kS..kS+W-1 draw epoch orders
+// (W = blockDim / 64 - kS). The order of epoch f is built by order wave f mod W
 // in W segments during the W epochs before f, so each wave does 1/W of an
 // order per epoch and every epoch ends at one barrier; W + 1 order buffers
-// (epoch f in buffer f mod (W + 1)). Dynamic LDS ((15 + 2W) N bytes): g,
-// alpha, the diagonal s2 G_ii + 1 (FP32 each), y (int8), the orders (int16).
-// kV4: the Gram rows are read as float4 (N % 4 == 0).
-template <bool kV4>
-__global__ __launch_bounds__(320) void k_train_gram(GramArgs a) {
+// (epoch f in buffer f mod (W + 1)).
+//
+// An update is a serial chain: g of the next 64 samples from LDS, the first of
+// them with a projected gradient, its step, its row of G, d times that row added
+// to g. The solver waves run the chain alike, each on its own; only the row is
+// shared out (wave w: columns 256 (kS u + w) + 4 lane .. + 3, u < kU). kTwo: from
+// one of two copies of g into the other, and one hand-shake an update tells that
+// all parts are written (a wave is one update ahead of another at most, and writes
+// the copy that no one reads any more); else in place, with a hand-shake before the
+// writes too. The rows of the next two samples, as things stand, are on their way
+// to registers. The order of every sum is that of a single wave.
+//
+// 256 classes x 5120 samples (35 thousand updates in the longest class, rows of
+// 20 KB out of the 105 MB matrix, 2.9 TB/s): 32 ms, 0.92 us an update; 51 ms with
+// one solver wave, no row ahead and one swap of an order at a time. Whole trainings,
+// before and after: 64 x 640 17.1 / 9.5 ms, 13 x 91 4.4 / 3.5, 254 x 5842 191 / 51,
+// 330 x 7920 (in place) 273 / 149. Up to 1024 samples one wave: a row is 4 pieces
+// then, about what a hand-shake takes (280 cycles).
+//
+// Dynamic LDS, N4 = N rounded up to 4: g (two copies if kTwo), alpha, the diagonal
+// s2 G_ii + 1 (FP32 each), the orders (int16), y (int8). Entries of g past N hold
+// what follows a row in memory and are not used.
+template <int kS, int kU, bool kTwo>
+__global__ __launch_bounds__(64 * (kS + 4)) void k_train_gram(GramArgs a) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    const int32_t N = a.N;
-    const int W = (int)(blockDim.x >> 6) - 1, B = W + 1;
-    float *g = reinterpret_cast<float *>(smem);
-    float *al = g + N;
-    float *qd = al + N;
-    int16_t *ord = reinterpret_cast<int16_t *>(qd + N);  // [W + 1][N]
-    int8_t *ys = reinterpret_cast<int8_t *>(ord + (size_t)B * N);
+    const int32_t N = a.N, N4 = (N + 3) & ~3;
+    const int W = (int)(blockDim.x >> 6) - kS, B = W + 1;
+    float *g = reinterpret_cast<float *>(smem);  // the present copy
+    float *g_next = kTwo ? g + N4 : g;
+    float *al = g_next + N4;
+    float *qd = al + N4;
+    int16_t *ord = reinterpret_cast<int16_t *>(qd + N4);  // [W + 1][N4]
+    int8_t *ys = reinterpret_cast<int8_t *>(ord + (size_t)B * N4);
     __shared__ int32_t done[2];
+    __shared__ uint32_t marks[4];  // hand-shakes each solver wave has come to
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int32_t k = blockIdx.x;
     const float sig = *a.sigma, s2 = sig * sig, C = a.C;
     const bool warm = a.g0 != nullptr;
@@ -405,122 +429,165 @@ __global__ __launch_bounds__(320) void k_train_gram(GramArgs a) {
         g[i] = warm ? a.g0[(size_t)k * N + i] : 0.0f;
         qd[i] = s2 * a.G[(size_t)i * N + i] + 1.0f;
     }
+    if (tid < 4) marks[tid] = 0;
     const uint64_t state0 = a.seed ^ (0x5851F42D4C957F2Dull * (uint64_t)(k + 1));
     __syncthreads();
 
-    float c = 0.0f;  // solver wave: sum alpha y (the bias weight)
-    if (wave == 0 && warm) {
+    float c = 0.0f;  // solver waves: sum alpha y (the bias weight)
+    if (wave < kS && warm) {
         float part = 0.0f;
         for (int32_t i = lane; i < N; i += 64) part += ys[i] > 0 ? al[i] : -al[i];
         c = wave_sum_f32(part);
     }
+    gf4 r0[kU], r1[kU], r2[kU];  // rows id0, id1, id2 of G, or on their way
+    int32_t id0 = -1, id1 = -1, id2 = -1;
+    int32_t col[kU];  // columns past the end repeat the last ones
+#pragma unroll
+    for (int u = 0; u < kU; ++u) col[u] = min(256 * (kS * u + wave) + 4 * lane, N4 - 4);
+    auto load = [&](int32_t i, gf4(&r)[kU]) {
+        const float *row = a.G + (size_t)i * N;
+#pragma unroll
+        for (int u = 0; u < kU; ++u) r[u] = *reinterpret_cast<const gf4u *>(row + col[u]);
+    };
+    uint32_t mark = 0;
+    // All solver waves are here, with their LDS reads and writes done. They make
+    // the same updates, so each comes.
+    auto meet = [&]() {
+        ++mark;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        if (lane == 0)
+            __hip_atomic_store(&marks[wave], mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        while (__ballot((int32_t)(__hip_atomic_load(&marks[lane & (kS - 1)], __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_WORKGROUP) - mark) < 0)) {
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    };
+
     int32_t epoch = a.max_epochs;
     // e < 0: the first orders only.
     for (int32_t e = -W; e < a.max_epochs; ++e) {
-        if (wave == 0) {
+        if (wave < kS) {
             if (e >= 0) {
-                const int16_t *od = ord + (size_t)(e % B) * N;
-                float max_pg = 0.0f;
+                const int16_t *od = ord + (size_t)(e % B) * N4;
+                // The present block and the one after it, whose duals no step of
+                // the present one changes; the samples of the block after that.
+                GramBlock now, after;
+                int32_t far;
+                auto read = [&](GramBlock &w, int32_t i, int32_t p) {
+                    const bool valid = p < N;
+                    w.i = i;
+                    w.y = ys[i] > 0 ? 1.0f : -1.0f;
+                    w.al = al[i];
+                    w.q = qd[i];
+                    const uint64_t v = __ballot(valid), lo = __ballot(w.al <= 0.0f);
+                    const uint64_t up = __ballot(w.al >= C) & ~lo;
+                    w.lower = v & lo;
+                    w.upper = v & up;
+                    w.inside = v & ~(lo | up);
+                };
+                // Lanes whose projected gradient is not 0.
+                auto test = [&](GramBlock &w, float gi) {
+                    w.G = w.y * (s2 * gi + c) - 1.0f;
+                    return (__ballot(w.G < 0.0f) & w.lower) | (__ballot(w.G > 0.0f) & w.upper) |
+                           (__ballot(w.G != 0.0f) & w.inside);
+                };
                 int32_t s = 0;
-                while (s < N) {  // uniform
-                    const int32_t p = s + lane;
-                    const bool v = p < N;
-                    const int32_t i = v ? od[p] : 0;
-                    const float y = ys[i] > 0 ? 1.0f : -1.0f;
-                    const float ai = al[i], qi = qd[i];
-                    const float G = y * (s2 * g[i] + c) - 1.0f;
-                    float PG = G;
-                    if (ai <= 0.0f) PG = G < 0.0f ? G : 0.0f;
-                    else if (ai >= C) PG = G > 0.0f ? G : 0.0f;
-                    const uint64_t m = __ballot(v && PG != 0.0f);
-                    if (m == 0) {
-                        s += 64;
-                        continue;
-                    }
-                    const int t = __builtin_ctzll(m);
-                    const int32_t it = __builtin_amdgcn_readlane(i, t);
-                    const float Gt = readlane_f(G, t), at = readlane_f(ai, t);
-                    const float yt = readlane_f(y, t), q = readlane_f(qi, t);
-                    max_pg = fmaxf(max_pg, fabsf(readlane_f(PG, t)));
-                    if (q > 0.0f) {
-                        const float an = fminf(fmaxf(at - Gt / q, 0.0f), C);
-                        if (lane == 0) al[it] = an;
-                        const float d = (an - at) * yt;
-                        if (d != 0.0f) {
-                            const float *row = a.G + (size_t)it * N;
-                            if constexpr (kV4) {
-                                // 24 float4 per lane in flight (a row of up
-                                // to 6144 values in one round), then the
-                                // updates.
-                                typedef float f4 __attribute__((ext_vector_type(4)));
-                                for (int32_t j0 = 4 * lane; j0 < N; j0 += 256 * 24) {
-                                    // Every load unconditional, its address kept
-                                    // inside the row (pieces past the end are
-                                    // not used): guarded loads would keep the old
-                                    // values of r alive across updates.
-                                    f4 r[24];
-#pragma unroll
-                                    for (int u = 0; u < 24; ++u)
-                                        r[u] = *reinterpret_cast<const f4 *>(row + min(j0 + 256 * u, N - 4));
-                                    // Groups of eight pieces that lie inside g
-                                    // for every lane (2048 (q + 1) <= N - j0 +
-                                    // 4 lane): one LDS round trip a group; the
-                                    // rest piece by piece.
-                                    const int32_t nfull = (N - (j0 - 4 * lane)) / 2048;
-#pragma unroll
-                                    for (int q = 0; q < 3; ++q) {
-                                        if (q < nfull) {  // uniform
-                                            gf4 gv[8];
-                                            lds_read8((uint32_t)(uintptr_t)(g + j0 + 2048 * q), gv);
-#pragma unroll
-                                            for (int u = 0; u < 8; ++u) {
-                                                gf4 v = gv[u];
-                                                const f4 ru = r[8 * q + u];
-                                                v.x += d * ru.x;
-                                                v.y += d * ru.y;
-                                                v.z += d * ru.z;
-                                                v.w += d * ru.w;
-                                                *reinterpret_cast<gf4 *>(g + j0 + 2048 * q + 256 * u) = v;
-                                            }
-                                        } else {
-                                            // Piece u lies inside g for every lane
-                                            // when base + 256 (u + 1) <= N, for none
-                                            // when base + 256 u >= N (uniform tests).
-                                            const int32_t base = j0 - 4 * lane;
-#pragma unroll
-                                            for (int u = 8 * q; u < 8 * q + 8; ++u) {
-                                                const int32_t j = j0 + 256 * u;
-                                                if (base + 256 * u >= N) break;
-                                                if (base + 256 * (u + 1) <= N || j < N) {
-                                                    f4 gv = *reinterpret_cast<const f4 *>(g + j);
-                                                    gv.x += d * r[u].x;
-                                                    gv.y += d * r[u].y;
-                                                    gv.z += d * r[u].z;
-                                                    gv.w += d * r[u].w;
-                                                    *reinterpret_cast<f4 *>(g + j) = gv;
-                                                }
-                                            }
-                                        }
-                                    }
-                                }
-                            } else {
-#pragma unroll 8
-                                for (int32_t j = lane; j < N; j += 64) g[j] += d * row[j];
-                            }
-                            c += d;
+                float max_pg = 0.0f;  // of the samples this lane held
+                const int32_t i0 = lane < N ? od[lane] : 0, i1 = 64 + lane < N ? od[64 + lane] : 0;
+                far = 128 + lane < N ? od[128 + lane] : 0;
+                read(now, i0, lane);
+                read(after, i1, 64 + lane);
+                uint64_t m = test(now, g[i0]), m2 = test(after, g[i1]);
+                // The next sample that moves and its step; false at the end.
+                int32_t it = 0;
+                float d = 0.0f, an = 0.0f;
+                auto next = [&]() {
+                    for (;;) {
+                        while (m == 0) {
+                            s += 64;
+                            if (s >= N) return false;
+                            now = after;
+                            m = m2;
+                            const float gf = g[far];
+                            read(after, far, s + 64 + lane);
+                            far = s + 128 + lane < N ? od[s + 128 + lane] : 0;
+                            m2 = test(after, gf);
                         }
+                        // Every lane its own step, then the first one's.
+                        const float al_new = fminf(fmaxf(now.al - now.G / now.q, 0.0f), C);
+                        const int t = __builtin_ctzll(m);
+                        const float dl = now.q > 0.0f ? (al_new - now.al) * now.y : 0.0f;
+                        it = __builtin_amdgcn_readlane(now.i, t);
+                        d = readlane_f(dl, t);
+                        an = readlane_f(al_new, t);
+                        max_pg = fmaxf(max_pg, fabsf(readlane_f(now.G, t)));
+                        // Visited: t and the lanes below it.
+                        const uint64_t open = t < 63 ? ~0ull << (t + 1) : 0;
+                        now.lower &= open;
+                        now.upper &= open;
+                        now.inside &= open;
+                        m &= open;
+                        if (d != 0.0f) return true;
                     }
-                    s += t + 1;
+                };
+                auto step = [&](gf4(&r)[kU], int32_t &id, gf4(&rb)[kU], int32_t &idb) {
+                    if (id != it) {
+                        load(it, r);
+                        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+                    }
+                    // The second sample that moves from here if this step changes
+                    // little (the first one's row was asked for a step ago).
+                    const uint64_t w = m & (m - 1);
+                    const uint64_t w2 = w ? w : m ? m2 : m2 & (m2 - 1);
+                    const int t2 = __builtin_ctzll(w2 | 1ull << 63);
+                    idb = w ? __builtin_amdgcn_readlane(now.i, t2) : __builtin_amdgcn_readlane(after.i, t2);
+                    load(idb, rb);
+                    id = -1;
+                    gf4 v[kU];
+#pragma unroll
+                    for (int u = 0; u < kU; ++u) v[u] = *reinterpret_cast<const gf4 *>(g + col[u]);
+#pragma unroll
+                    for (int u = 0; u < kU; ++u)
+#pragma unroll
+                        for (int x = 0; x < 4; ++x) v[u][x] += d * r[u][x];
+                    if constexpr (!kTwo && kS > 1) meet();
+                    // Lanes past the end write what the last columns' lanes do, or,
+                    // where those may have been ahead, nothing.
+#pragma unroll
+                    for (int u = 0; u < kU; ++u)
+                        if (kTwo || kS == 1 || 256 * (kS * u + wave) + 4 * lane < N4)
+                            *reinterpret_cast<gf4 *>(g_next + col[u]) = v[u];
+                    if constexpr (kTwo) {
+                        float *t = g;
+                        g = g_next;
+                        g_next = t;
+                    }
+                    if constexpr (kS > 1) meet();
+                    // Not before every solver wave has taken the step: one that has
+                    // not may yet read the old dual with a later block.
+                    if (wave == 0 && lane == 0) al[it] = an;
+                    c += d;
+                    const float ga = g[now.i], gb = g[after.i];
+                    m = test(now, ga);
+                    m2 = test(after, gb);
+                };
+                for (;;) {
+                    if (!next()) break;
+                    step(r0, id0, r2, id2);
+                    if (!next()) break;
+                    step(r1, id1, r0, id0);
+                    if (!next()) break;
+                    step(r2, id2, r1, id1);
                 }
-                if (lane == 0) done[e & 1] = max_pg < a.eps;
+                if (tid == 0) done[e & 1] = max_pg < a.eps;
             }
         } else {
-            // The epoch f in [e + 1, e + W] with f = wave - 1 (mod W), at
-            // its segment e - f + W.
-            const int w = wave - 1;
+            // The epoch f in [e + 1, e + W] with f = w (mod W), at its segment
+            // e - f + W.
+            const int w = wave - kS;
             const int32_t f = e + 1 + (((w - (e + 1)) % W) + W) % W;
             if (f >= 0 && f < a.max_epochs)
-                gram_order(ord + (size_t)(f % B) * N, N, state0, f, (int)(e - f + W), W, lane);
+                gram_order(ord + (size_t)(f % B) * N4, N, state0, f, (int)(e - f + W), W, lane);
         }
         __syncthreads();
         if (e >= 0 && done[e & 1] != 0) {  // uniform
@@ -536,45 +603,70 @@ __global__ __launch_bounds__(320) void k_train_gram(GramArgs a) {
 }
 
 // W_k = s2 sum_i alpha_ki y_ki x_i (samples in index order, zero duals
-// skipped); thread t owns coordinates t + 256 j.
-template <int kJ>
+// skipped); thread t of workgroup (k, p) owns coordinates 2048 p + t + 256 j. The
+// samples with a dual are listed first, so that four of them are in flight at a
+// time (one at a time, all coordinates of a class in one workgroup: 1250 us at 256
+// classes x 5120 samples x 7552, 89 us so).
 __global__ __launch_bounds__(256) void k_gram_weights(const float *__restrict__ X,
                                                       const int32_t *__restrict__ labels,
                                                       int32_t N, int32_t D,
                                                       const float *__restrict__ alpha,
                                                       const float *__restrict__ sigma,
                                                       float *__restrict__ W) {
-    __shared__ float coef[1024];
-    const int tid = threadIdx.x;
+    constexpr int kJ = 8, kList = 1024;
+    __shared__ float coef[kList];
+    __shared__ int32_t index[kList];
+    __shared__ int32_t listed[4];  // by each wave
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int32_t k = blockIdx.x;
+    int32_t d[kJ];
+#pragma unroll
+    for (int j = 0; j < kJ; ++j) d[j] = 2048 * (int32_t)blockIdx.y + tid + 256 * j;
     float acc[kJ];
 #pragma unroll
     for (int j = 0; j < kJ; ++j) acc[j] = 0.0f;
-    for (int32_t i0 = 0; i0 < N; i0 += 1024) {
-        const int32_t n = min(1024, N - i0);
+    for (int32_t i0 = 0; i0 < N; i0 += kList) {
+        // Wave w lists samples i0 + 256 w .. + 255, in order, from entry 256 w on.
         __syncthreads();
-        for (int32_t t = tid; t < n; t += 256) {
-            const float av = alpha[(size_t)k * N + i0 + t];
-            coef[t] = labels[i0 + t] == k ? av : -av;
-        }
-        __syncthreads();
-        for (int32_t t = 0; t < n; ++t) {
-            const float cf = coef[t];
-            if (cf == 0.0f) continue;  // uniform
-            const float *x = X + (size_t)(i0 + t) * D;
+        int32_t n = 0;
 #pragma unroll
-            for (int j = 0; j < kJ; ++j) {
-                const int d = tid + 256 * j;
-                if (d < D) acc[j] += cf * x[d];
+        for (int q = 0; q < 4; ++q) {
+            const int32_t i = i0 + 256 * wave + 64 * q + lane;
+            const float av = i < N ? alpha[(size_t)k * N + i] : 0.0f;
+            const uint64_t m = __ballot(av != 0.0f);
+            if (av != 0.0f) {
+                const int e = 256 * wave + n + __builtin_popcountll(m & ((1ull << lane) - 1));
+                coef[e] = labels[i] == k ? av : -av;
+                index[e] = i;
+            }
+            n += __builtin_popcountll(m);
+        }
+        if (lane == 0) listed[wave] = n;
+        __syncthreads();
+        for (int w = 0; w < 4; ++w) {
+            const int end = 256 * w + listed[w];
+            for (int t = 256 * w; t < end; t += 4) {
+                float x[4][kJ];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const float *row = X + (size_t)index[min(t + u, end - 1)] * D;
+#pragma unroll
+                    for (int j = 0; j < kJ; ++j) x[u][j] = row[min(d[j], D - 1)];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (t + u >= end) break;  // uniform
+                    const float cf = coef[t + u];
+#pragma unroll
+                    for (int j = 0; j < kJ; ++j) acc[j] += cf * x[u][j];
+                }
             }
         }
     }
     const float sg = *sigma, s2 = sg * sg;
 #pragma unroll
-    for (int j = 0; j < kJ; ++j) {
-        const int d = tid + 256 * j;
-        if (d < D) W[(size_t)k * D + d] = s2 * acc[j];
-    }
+    for (int j = 0; j < kJ; ++j)
+        if (d[j] < D) W[(size_t)k * D + d[j]] = s2 * acc[j];
 }
 
 }  // namespace
@@ -601,7 +693,7 @@ hipError_t launch_train_gram(const float *X, const int32_t *labels, int32_t N, i
     hipError_t e = launch_score_f32(X, N, X, zeros, N, D, G, nullptr, s, 1, nullptr, nullptr, true);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_gram_diag, rows, blk, 0, s, G, N, norms);
-    hipLaunchKernelGGL(k_gram_sigma, rows, blk, 0, s, norms, N, sigma);
+    hipLaunchKernelGGL(k_gram_sigma, dim3((N + 15) / 16), blk, 0, s, norms, N, sigma);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const bool w = warm && alpha;
     if (w) {
@@ -612,27 +704,31 @@ hipError_t launch_train_gram(const float *X, const int32_t *labels, int32_t N, i
             return e;
     }
     GramArgs a{G, labels, sigma, w ? G0 : nullptr, N, K, C, eps, max_epochs, seed, al, b, epochs};
-    // As many order waves (at most 4) as the LDS holds buffers for: (15 + 2W) N
-    // bytes, W >= 1 for every N up to kGramMaxN.
-    const int nw = (int)std::min<size_t>(4, (kGramLds / n - 15) / 2);
-    const size_t lds = (15 + 2 * (size_t)nw) * n;
-    const bool v4 = N % 4 == 0;
-    const void *kern = v4 ? (const void *)k_train_gram<true> : (const void *)k_train_gram<false>;
-    if ((e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) !=
-        hipSuccess)
-        return e;
-    if (v4)
-        hipLaunchKernelGGL(k_train_gram<true>, dim3(K), dim3(64 * (1 + nw)), lds, s, a);
-    else
-        hipLaunchKernelGGL(k_train_gram<false>, dim3(K), dim3(64 * (1 + nw)), lds, s, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    auto wts = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(K), blk, 0, s, X, labels, N, D, al, sigma, W);
+    // Bytes of LDS a sample, less the orders' 2 (W + 1): two copies of g where more
+    // than one wave solves and they fit beside two orders. As many order waves (at
+    // most 4) as there is room for, one at least.
+    const size_t n4 = (n + 3) & ~(size_t)3;
+    const bool two = N > 1024 && n4 * (17 + 4) <= kGramLds;
+    const size_t bytes = two ? 17 : 13;
+    const int nw = (int)std::min<size_t>(4, (kGramLds / n4 - bytes) / 2 - 1);
+    const size_t lds = (bytes + 2 * ((size_t)nw + 1)) * n4;
+    auto solve = [&](auto kern, int solvers) {
+        if ((e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)lds)) != hipSuccess)
+            return;
+        hipLaunchKernelGGL(kern, dim3(K), dim3(64 * (solvers + nw)), lds, s, a);
+        e = hipGetLastError();
     };
-    if (D <= 4 * 256) wts(k_gram_weights<4>);
-    else if (D <= 8 * 256) wts(k_gram_weights<8>);
-    else if (D <= 16 * 256) wts(k_gram_weights<16>);
-    else wts(k_gram_weights<32>);
+    if (N <= 256) solve(k_train_gram<1, 1, false>, 1);
+    else if (N <= 1024) solve(k_train_gram<1, 4, false>, 1);
+    else if (!two) solve(k_train_gram<4, 8, false>, 4);
+    else if (N <= 2048) solve(k_train_gram<2, 4, true>, 2);
+    else if (N <= 4096) solve(k_train_gram<4, 4, true>, 4);
+    else if (N <= 5120) solve(k_train_gram<4, 5, true>, 4);
+    else solve(k_train_gram<4, 8, true>, 4);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_gram_weights, dim3(K, (D + 2047) / 2048), blk, 0, s, X, labels, N, D, al,
+                       sigma, W);
     return hipGetLastError();
 }
 
