@@ -262,6 +262,23 @@ __device__ __forceinline__ float wave_sum_f32(float v) {
 typedef float gf4 __attribute__((ext_vector_type(4)));
 typedef float gf4u __attribute__((ext_vector_type(4), aligned(4)));  // a row of G
 
+// Four 16-byte pieces of LDS kStride bytes apart, waited for in the same block: the
+// results land in distinct registers, so the reads go out back to back. The outputs
+// are early-clobber: a read that returns while later ones are still being issued
+// must not land in the address register.
+template <int kStride>
+__device__ __forceinline__ void lds_read4(uint32_t addr, gf4 &a, gf4 &b, gf4 &c, gf4 &d) {
+    asm volatile(
+        "ds_read_b128 %0, %4\n\t"
+        "ds_read_b128 %1, %4 offset:%5\n\t"
+        "ds_read_b128 %2, %4 offset:%6\n\t"
+        "ds_read_b128 %3, %4 offset:%7\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d)
+        : "v"(addr), "n"(kStride), "n"(2 * kStride), "n"(3 * kStride)
+        : "memory");
+}
+
 __device__ __forceinline__ float readlane_f(float v, int l) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
 }
@@ -444,6 +461,7 @@ __global__ __launch_bounds__(64 * (kS + 4)) void k_train_gram(GramArgs a) {
     int32_t col[kU];  // columns past the end repeat the last ones
 #pragma unroll
     for (int u = 0; u < kU; ++u) col[u] = min(256 * (kS * u + wave) + 4 * lane, N4 - 4);
+    const int whole = (N4 / 256 - wave + kS - 1) / kS;  // pieces inside for every lane
     auto load = [&](int32_t i, gf4(&r)[kU]) {
         const float *row = a.G + (size_t)i * N;
 #pragma unroll
@@ -545,7 +563,15 @@ __global__ __launch_bounds__(64 * (kS + 4)) void k_train_gram(GramArgs a) {
                     id = -1;
                     gf4 v[kU];
 #pragma unroll
-                    for (int u = 0; u < kU; ++u) v[u] = *reinterpret_cast<const gf4 *>(g + col[u]);
+                    for (int u = 0; u < kU; u += 4)
+                        if (kU % 4 == 0 && u + 4 <= whole)  // uniform
+                            lds_read4<1024 * kS>((uint32_t)(uintptr_t)(g + col[u]), v[u],
+                                                 v[min(u + 1, kU - 1)], v[min(u + 2, kU - 1)],
+                                                 v[min(u + 3, kU - 1)]);
+                        else
+#pragma unroll
+                            for (int t = u; t < min(u + 4, kU); ++t)
+                                v[t] = *reinterpret_cast<const gf4 *>(g + col[t]);
 #pragma unroll
                     for (int u = 0; u < kU; ++u)
 #pragma unroll
