@@ -17,7 +17,7 @@
 // to 8192 values are quantised by k_quant_rows_vec in one read (the row held
 // in registers, vector stores), longer ones by k_quant_rows.
 //
-// Products of few tiles run k_score_lp_rows (operands straight to registers).
+// Products of few tiles run k_score_lp_rows (D shared by a workgroup's waves).
 //
 // Other large products (N >= 512, K >= 256) run k_score_lp_big (256 x 256 tiles
 // through an LDS ring, described there), whose epilogue also reduces each
@@ -433,19 +433,34 @@ __global__ __launch_bounds__(256) void k_score_lp(const uint8_t *__restrict__ Xq
     }
 }
 
+typedef __attribute__((address_space(3))) void lds_void_t;
+typedef __attribute__((address_space(1))) const void glb_void_t;
+
+template <int kVm>
+__device__ __forceinline__ void wait_vm() {
+    static_assert(kVm >= 0 && kVm < 64, "vmcnt range");
+    // gfx9 s_waitcnt: vmcnt[3:0], expcnt[6:4], lgkmcnt[11:8], vmcnt[15:14].
+    __builtin_amdgcn_s_waitcnt((kVm & 15) | (7 << 4) | (15 << 8) | ((kVm >> 4) << 14));
+}
+
+__device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >> 1) & 3); }
+
 // --- GEMM, few tiles -------------------------------------------------------------
 //
 // For products whose 256-wide tiles leave most CUs idle (a serving batch of 256
 // rows x 1024 identities is 4 tiles of 256 x 256, each 118 serial stages). A
 // workgroup of 8 wave64 owns 32 kNB feature rows x 32 kKB identities; its waves
-// take the 64-byte steps of the reduction in turn (step s by wave s % 8), each
-// with its operands straight from global memory in registers, and meet in LDS
-// in wave order. Lane (l % 32, l / 32) of an operand block holds bytes
-// 32 (l / 32) .. + 31 of its row's step, for both operands alike. Bound by the
-// operand traffic between L2 and the CUs: 256 x 1024 in BF16 moves 248 MB in
-// about 25 us, 10 TB/s (198 us on the 256 x 256 tiles); 16 waves a workgroup, or
-// four steps in flight a wave instead of one, change nothing. Weights are the first operand: a lane
-// then holds four consecutive identities of one feature row.
+// take the 64-byte steps of the reduction in turn (step s by wave s % 8) and meet in
+// LDS in wave order. Each wave streams its steps through a ring of its own (16 KB:
+// four steps of 32 + 32 rows or two of 64 + 64; global_load_lds, chunk c of a row at
+// c ^ ((row / 2) % 4)), waits for its own copies only, and meets no barrier before
+// the end. Lane (l % 32, l / 32) of an operand block reads bytes 32 (l / 32) .. + 31
+// of its row's step, for both operands alike. Operands loaded straight to registers
+// touch 32 rows a load, and the cache looks up a row a cycle: 256 x 1024 in BF16
+// took 42 us a call so, 29 through the ring (16 rows a load, whole 64-byte pieces;
+// 248 MB of operands to the CUs), 176 on the 256 x 256 tiles. 16 waves a workgroup
+// changed nothing. Weights are the first operand: a lane then holds four consecutive
+// identities of one feature row.
 constexpr int kRowsWaves = 8;
 
 template <int kMode, int kNB, int kKB>
@@ -454,38 +469,67 @@ __global__ __launch_bounds__(64 * kRowsWaves) void k_score_lp_rows(
     const uint8_t *__restrict__ Wq, const float *__restrict__ sw, const float *__restrict__ bias,
     int32_t K, int32_t pitch, float *__restrict__ S, const int32_t *__restrict__ n_dev,
     int32_t a_pitch, int32_t a_seg) {
-    __shared__ f32x4 red[kRowsWaves][kNB * kKB * 4][64];
+    constexpr int kRowsOf = 32 * (kNB + kKB), kStage = 64 * kRowsOf;  // X rows, then W rows
+    constexpr int kRing = 16384 / kStage, kCopies = kStage / 1024;
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[kRowsWaves][kRing][kStage];
+    static_assert(sizeof(f32x4) * kNB * kKB * 4 * 64 <= sizeof(lds[0]), "sums in the ring's place");
+    f32x4(*red)[kNB * kKB * 4][64] = reinterpret_cast<f32x4(*)[kNB * kKB * 4][64]>(&lds[0][0][0]);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: scalar steps
     const int fr = lane & 31, fq = lane >> 5;
     const int32_t n0 = blockIdx.y * 32 * kNB, k0 = blockIdx.x * 32 * kKB;
     if (n_dev) N = *n_dev;
     if (n0 >= N) return;  // uniform
-    const uint8_t *xp[kNB], *wp[kKB];
+    // Copy j: rows 16 j + l / 4 of the stage, lane l the chunk that belongs at l % 4.
+    const uint8_t *src[kCopies];
 #pragma unroll
-    for (int i = 0; i < kNB; ++i)
-        xp[i] = Xq + (size_t)min(n0 + 32 * i + fr, N - 1) * a_pitch + 32 * fq;
-#pragma unroll
-    for (int j = 0; j < kKB; ++j)
-        wp[j] = Wq + (size_t)min(k0 + 32 * j + fr, K - 1) * pitch + 32 * fq;
+    for (int j = 0; j < kCopies; ++j) {
+        const int row = 16 * j + (lane >> 2), chunk = swz(row, lane & 3);
+        src[j] = (j < 2 * kNB ? Xq + (size_t)min(n0 + row, N - 1) * a_pitch
+                              : Wq + (size_t)min(k0 + row - 32 * kNB, K - 1) * pitch) + 16 * chunk;
+    }
     f32x16 acc[kNB][kKB];
 #pragma unroll
     for (int i = 0; i < kNB; ++i)
 #pragma unroll
         for (int j = 0; j < kKB; ++j) acc[i][j] = f32x16{};
     const int32_t steps = pitch / 64;
-    for (int32_t s = wave; s < steps; s += kRowsWaves) {
-        const int32_t kb = 64 * s, kba = (a_seg && kb >= a_seg) ? kb - a_seg : kb;
+    // Stage t of this wave is step wave + 8 t; past the end the last step again, so
+    // that every stage counts the same copies.
+    auto copy = [&](int32_t t) {
+        const int32_t kb = 64 * min(wave + kRowsWaves * t, steps - 1);
+        const int32_t kba = (a_seg && kb >= a_seg) ? kb - a_seg : kb;
+#pragma unroll
+        for (int j = 0; j < kCopies; ++j)
+            __builtin_amdgcn_global_load_lds(
+                (glb_void_t *)(src[j] + (j < 2 * kNB ? kba : kb)),
+                (lds_void_t *)(&lds[wave][t % kRing][j * 1024]), 16, 0, 0);
+    };
+    const int32_t stages = (steps - wave + kRowsWaves - 1) / kRowsWaves;
+#pragma unroll
+    for (int t = 0; t < kRing; ++t) copy(t);
+    for (int32_t t = 0; t < stages; ++t) {
+        wait_vm<(kRing - 1) * kCopies>();
+        asm volatile("" ::: "memory");
+        const uint8_t *st = lds[wave][t % kRing];
         u32x4 a[kNB][2], b[kKB][2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
 #pragma unroll
-            for (int i = 0; i < kNB; ++i)
-                a[i][h] = *reinterpret_cast<const u32x4 *>(xp[i] + kba + 16 * h);
+            for (int i = 0; i < kNB; ++i) {
+                const int row = 32 * i + fr;
+                a[i][h] = *reinterpret_cast<const u32x4 *>(st + 64 * row + 16 * swz(row, 2 * fq + h));
+            }
 #pragma unroll
-            for (int j = 0; j < kKB; ++j)
-                b[j][h] = *reinterpret_cast<const u32x4 *>(wp[j] + kb + 16 * h);
+            for (int j = 0; j < kKB; ++j) {
+                const int row = 32 * (kNB + j) + fr;
+                b[j][h] = *reinterpret_cast<const u32x4 *>(st + 64 * row + 16 * swz(row, 2 * fq + h));
+            }
         }
+        // Read before the slot is copied to again.
+        __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));  // lgkmcnt(0)
+        asm volatile("" ::: "memory");
+        copy(t + kRing);
         constexpr int kSubs = (kMode == LBPF_FP8_E4M3) ? 1 : 2;
 #pragma unroll
         for (int sub = 0; sub < kSubs; ++sub)
@@ -495,6 +539,8 @@ __global__ __launch_bounds__(64 * kRowsWaves) void k_score_lp_rows(
                 for (int j = 0; j < kKB; ++j)
                     acc[i][j] = mfma_step<kMode>(b[j], a[i], acc[i][j], sub);
     }
+    wait_vm<0>();
+    __syncthreads();  // the copies past the end are in, the ring's reads done
     // Register 4 g + t of lane l: identity 8 g + 4 (l / 32) + t, row l % 32.
 #pragma unroll
     for (int i = 0; i < kNB; ++i)
@@ -554,18 +600,6 @@ constexpr int kStages = 5;  // 5 x 32 KB: all of the 160 KB LDS
 // included: 8 waves BF16 827 TFLOP/s, FP8 1278; 4 waves 784 and 1182.
 constexpr int kBigWaves = 8;
 constexpr int kStageBytes = 2 * kBigT * kStageB;  // A then B
-
-typedef __attribute__((address_space(3))) void lds_void_t;
-typedef __attribute__((address_space(1))) const void glb_void_t;
-
-template <int kVm>
-__device__ __forceinline__ void wait_vm() {
-    static_assert(kVm >= 0 && kVm < 64, "vmcnt range");
-    // gfx9 s_waitcnt: vmcnt[3:0], expcnt[6:4], lgkmcnt[11:8], vmcnt[15:14].
-    __builtin_amdgcn_s_waitcnt((kVm & 15) | (7 << 4) | (15 << 8) | ((kVm >> 4) << 14));
-}
-
-__device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >> 1) & 3); }
 
 // Workgroup barrier ordering LDS accesses only. __syncthreads would also
 // drain every outstanding global access, including the LDS copies of the
@@ -978,19 +1012,19 @@ hipError_t launch_quant_rows(const float *X, int32_t rows, int32_t D, int32_t mo
 
 // Side of k_score_lp_rows' tile for a product, 0 for the 256-wide tile kernels.
 // 32 x 32 tiles up to two per CU of this GPU (and for up to 32 rows, where W is
-// read once anyway), then 64 x 64 tiles up to two per CU, beyond which the
+// read once anyway), then 64 x 64 tiles up to four per CU, beyond which the
 // 256-wide tiles' lower operand traffic wins. At two tiles of 32 a CU the two
 // sides are level; a pipeline's batch that fills half its rows then runs half
-// of them at once (256 of 512 rows x 1024, BF16: 61 us on the 64 side). Whole calls in us, 32 / 64 / 256-wide
-// tiles, BF16: 256 x 1024 42 / 71 / 176, 512 x 1024 70 / 73 / 210, 1024 x 1024
-// 126 / 78 / 213, 2048 x 1024 (512 tiles of 64) 241 / 143 / 221, 4096 x 1024
-// (1024) 473 / 275 / 242, 32 x 8192 44 / 62 / 161, 256 x 8192 (512) 248 / 132 /
-// 180, 512 x 8192 (1024) 483 / 244 / 217; FP8 512 x 8192 245 / 131 / 125, split
-// FP16 2048 x 1024 672 / 373 / 593 and 4096 x 1024 1340 / 738 / 616.
+// of them at once. Whole calls in us, side 32 / 64 / 256-wide tiles, BF16: 512 x
+// 1024 (512 tiles of 32) 45 / 46 / 210, 768 x 512 (384) 47 / 52 / -, 64 x 8192 (512)
+// 56 / 52 / -, 2048 x 1024 (512 tiles of 64) - / 93 / 221, 4096 x 1024 (1024) - /
+// 173 / 240, 512 x 8192 (1024) - / 149 / 216, 6000 x 1024 (1504) - / 250 / 255, 8192
+// x 1024 (2048) - / 335 / 280; FP8 512 x 8192 - / 85 / 124, 8192 x 1024 - / 198 /
+// 170; split FP16 4096 x 1024 - / 486 / 615, 6000 x 1024 - / 702 / 637.
 static int rows_side(int32_t N, int32_t K) {
     auto tiles = [&](int64_t t) { return ((N + t - 1) / t) * ((K + t - 1) / t); };
     if (N <= 32 || tiles(32) <= 512) return 32;
-    return tiles(64) <= 512 ? 64 : 0;
+    return tiles(64) <= 1024 ? 64 : 0;
 }
 
 hipError_t launch_score_lp(const uint8_t *Xq, const float *sx, int32_t N, const uint8_t *Wq,

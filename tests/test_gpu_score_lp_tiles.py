@@ -1,6 +1,6 @@
 """Reduced-precision scoring on every tile shape and at the edges of the rule
 that chooses it: 32 x 32 tiles (at most two per CU, or up to 32 rows), 64 x 64
-tiles (at most two per CU), the 256 x 128 and 256 x 256 tiles beyond. Scores
+tiles (at most four per CU), the 256 x 128 and 256 x 256 tiles beyond. Scores
 against the exact product of the quantised operands within the FP32
 accumulation bound, identities the first maximum of the call's own scores."""
 import numpy as np
@@ -17,8 +17,9 @@ SHAPES = [
     (1, 1), (31, 33), (32, 2050),    # 32 x 32
     (512, 1024), (513, 1025),        # 512 tiles of 32; 64 x 64
     (33, 8200),                      # 64 x 64, one row of tiles
-    (300, 8200),                     # 256 x 128
-    (2100, 1030),                    # 256 x 256
+    (300, 8200), (2100, 1030), (512, 8192),  # 64 x 64
+    (480, 9000),                     # 256 x 128
+    (600, 8200),                     # 256 x 256
 ]
 
 
