@@ -151,9 +151,11 @@ __global__ __launch_bounds__(512) void k_score_f32(const float *__restrict__ X, 
 // are summed again in one fixed order, that of k_score_f32_tiles (per range of D,
 // each eight columns as 0 4 1 5 2 6 3 7, an FMA each; the ranges' sums in order; the
 // bias), written over the others and compared. Within: 2^-17 of the best one's
-// |x w| + |b|, 30 times the usual difference; about 1 row in 8000 of a gallery's (a
-// wave takes 45 us over 7552 columns in one range, 12 in four: 16384 x 1024 1315 us
-// with no such row, 1355 with some; with one in every row 3490).
+// |x w| + |b|, 30 times the usual difference; about 1 row in 8000 of a gallery's. A
+// wave takes about 25 us over 7552 columns in one range, 7 in four: a chain of FMAs
+// in one lane a score, its operands staged in LDS by all lanes and read 16 columns
+// ahead. 16384 x 1024: 1303 us with no close row, 1326 with some, 1990 with one or
+// more in every row.
 struct Closest {
     float best = -INFINITY, second = -INFINITY;
     int32_t arg;  // larger than any valid index at first
@@ -198,7 +200,7 @@ constexpr int kSettleLds = (1 + kSettleRows) * kSettleStride + 16;
 
 // One wave: row S_n's closest scores again, and the identity. ranges: 1, 2 or 4, D a
 // multiple of 32 ranges.
-__device__ int32_t settle(const float *__restrict__ x, const float *__restrict__ W,
+__device__ __forceinline__ int32_t settle(const float *__restrict__ x, const float *__restrict__ W,
                           const float *__restrict__ b, float *S_n, int32_t K, int32_t D, int ranges,
                           const Closest &row, float floor, float *lds) {
     const int lane = threadIdx.x & 63;
@@ -207,10 +209,13 @@ __device__ int32_t settle(const float *__restrict__ x, const float *__restrict__
     // More than a wave's worth, all alike: rows of W or X that are the same, not chance.
     int32_t many = 0;
     bool alike = true;
+    uint64_t blocks = 0;  // of 64 scores, the first 64 blocks: with a close one
 #pragma unroll 8
     for (int32_t k0 = 0; k0 < K; k0 += 64) {
         const float v = score(k0 + lane);
-        many += __builtin_popcountll(__ballot(v >= floor));
+        const uint64_t close = __ballot(v >= floor);
+        many += __builtin_popcountll(close);
+        if (close && k0 < 64 * 64) blocks |= 1ull << (k0 / 64);
         alike = alike && __ballot(v >= floor && v != row.best) == 0;
     }
     if (many > 64 && alike) return row.arg;
@@ -226,15 +231,27 @@ __device__ int32_t settle(const float *__restrict__ x, const float *__restrict__
     int32_t arg = K;
     int32_t cand = 0;  // lane c: candidate c
     int n = 0;
-    auto turn = [&]() {
+    int32_t k0 = 0;
+    uint64_t m = 0;  // close ones of the block before k0, not taken yet
+    for (;;) {
+        for (n = 0; n < kSettleRows; ++n) {
+            while (m == 0 && k0 < K) {
+                if (k0 >= 64 * 64 || (blocks >> (k0 / 64)) & 1) m = __ballot(score(k0 + lane) >= floor);
+                k0 += 64;
+            }
+            if (m == 0) break;
+            if (lane == n) cand = k0 - 64 + __builtin_ctzll(m);
+            m &= m - 1;
+        }
+        if (n == 0) return arg;
         float acc = 0.0f;
         floatx4 v[1 + kSettleRows][kSettlePieces];
         auto load = [&](int32_t c0) {
 #pragma unroll
             for (int c = 0; c <= kSettleRows; ++c) {
-                if (c > n) break;  // uniform
+                // Fewer than kSettleRows: the first candidate again.
                 const float *src =
-                    c == 0 ? x : W + (size_t)__builtin_amdgcn_readlane(cand, c - 1) * D;
+                    c == 0 ? x : W + (size_t)__builtin_amdgcn_readlane(cand, c <= n ? c - 1 : 0) * D;
 #pragma unroll
                 for (int p = 0; p < kSettlePieces; ++p) {
                     const int32_t d = c0 + 4 * per * p + at;
@@ -247,7 +264,6 @@ __device__ int32_t settle(const float *__restrict__ x, const float *__restrict__
         for (int32_t c0 = 0; c0 < len; c0 += cols) {
 #pragma unroll
             for (int c = 0; c <= kSettleRows; ++c) {
-                if (c > n) break;
 #pragma unroll
                 for (int p = 0; p < kSettlePieces; ++p)
                     *reinterpret_cast<floatx4 *>(lds + c * kSettleStride + to + 4 * per * p) = v[c][p];
@@ -300,26 +316,7 @@ __device__ int32_t settle(const float *__restrict__ x, const float *__restrict__
                 arg = k;
             }
         }
-        n = 0;
-    };
-    for (int32_t k0 = 0; k0 < K; k0 += 64 * 8) {
-        float v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = score(k0 + 64 * u + lane);
-        for (int u = 0; u < 8; ++u) {
-            uint64_t m = 0;
-#pragma unroll
-            for (int w = 0; w < 8; ++w)
-                if (w == u) m = __ballot(v[w] >= floor);
-            while (m) {
-                if (lane == n) cand = k0 + 64 * u + __builtin_ctzll(m);
-                m &= m - 1;
-                if (++n == kSettleRows) turn();
-            }
-        }
     }
-    if (n) turn();
-    return arg;
 }
 
 template <bool kSettle>
