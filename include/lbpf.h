@@ -473,10 +473,12 @@ int32_t lbpf_weights_count(const lbpf_weights *weights);
 /* Score N feature rows against every enrolled identity (step 6).
  * hist: DEVICE [N][D] FP32. scores_opt: DEVICE [N][K] FP32 or NULL.
  * argmax_opt: DEVICE [N] int32 or NULL (not both NULL). N = 0 is a no-op.
- * In FP32 the scores are accumulated in FP32 by MFMA (when the product has
- * too few 128 x 128 output tiles to fill the GPU, the feature dimension is
- * split into up to 4 equal ranges whose partial sums are added in range
- * order, so results are deterministic); in the reduced precisions the
+ * In FP32 every value enters in full (as itself, or as three exact BF16 parts
+ * on the BF16 matrix cores) and sums are FP32; products that would leave the
+ * GPU idle split the feature dimension into ranges whose partial sums are
+ * added in range order, so results are deterministic. Close scores are summed
+ * again in one fixed order (feature dimensions of a multiple of 32), so that
+ * the identity does not depend on the way taken. In the reduced precisions the
  * operands are converted as documented for lbpf_precision and the products
  * accumulated in FP32. Errors: LBPF_E_INVALID, LBPF_E_HIP. */
 lbpf_status lbpf_score(lbpf_ctx *ctx, const float *hist, int32_t N, const lbpf_weights *weights,

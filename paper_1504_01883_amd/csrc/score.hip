@@ -580,9 +580,9 @@ __global__ __launch_bounds__(256) void k_score_f32_tiles(
 // loads 24 floats (two stages ahead), splits them and writes the three planes into
 // one of two 72 KB LDS buffers (16-byte chunk c of a row at c ^ ((row / 2) % 4));
 // one plane is read by as many waves as a BF16 product's operand would be, but
-// multiplied twice as often. 16384 x 1024 x 7552 1355 us (FP32 MFMA, 128 x 256
-// tiles: 1850), 4096 x 256 103 (135): 1.12 PFLOP/s of BF16, the matrix cores busy
-// 59% at a clock that falls below 2 GHz under them; waves out of step, raised
+// multiplied twice as often. 16384 x 1024 x 7552 1270-1360 us (FP32 MFMA, 128 x 256
+// tiles: 1850), 4096 x 256 99 (135): 1.12-1.2 PFLOP/s of BF16, the matrix cores busy
+// 54% at a clock that falls below 2 GHz under them; waves out of step, raised
 // wave priority during the MFMAs, or VALU work interleaved by scheduling barriers
 // gained nothing (1330-1370 us against 1300 before the check below, 25 us of it).
 //
