@@ -662,11 +662,19 @@ lbpf_status lbpf_score(lbpf_ctx *ctx, const float *hist, int32_t N, const lbpf_w
     HIP_TRY(hipStreamIsCapturing(s, &cap), "hipStreamIsCapturing");
     const bool capturing = cap != hipStreamCaptureStatusNone;
     // FP32 products too small to fill the GPU with tiles split D. The partials
-    // go to the context's score scratch, or to the smaller one where that holds
-    // the scores (or may, for calls running beside a captured graph).
-    const bool roomy = scores_opt && !capturing;
-    float *part = roomy ? ctx->d_scores : ctx->d_part;
-    const size_t part_elems = roomy ? ctx->scores_elems : kPartElems;
+    // go to the context's score scratch, past the scores if it holds them, or to
+    // the smaller one where that has more room (or may, for calls running beside
+    // a captured graph). Argmax only, 4096 x 256: 153 us with the smaller, 120 so.
+    float *part = ctx->d_part;
+    size_t part_elems = kPartElems;
+    if (!capturing && w->prec == LBPF_FP32) {
+        const size_t held =
+            scores_opt ? 0 : ((size_t)std::min(rows, N) * (size_t)w->K + 63) / 64 * 64;
+        if (held + kPartElems < ctx->scores_elems) {
+            part = ctx->d_scores + held;
+            part_elems = ctx->scores_elems - held;
+        }
+    }
     auto splits_of = [&](int32_t n) {
         return w->prec == LBPF_FP32
                    ? score_f32_splits(n, w->K, w->D, ctx->num_cus, part_elems) : 1;
