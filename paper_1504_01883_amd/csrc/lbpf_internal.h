@@ -35,7 +35,7 @@ lbpf_status set_last_error(lbpf_status s, const std::string &msg);
 struct FeatParams {
     int32_t grid_x, grid_y;
     int32_t nbins;        // 59 or 256
-    int32_t window;       // depth half-width in mm; <= 0 disables the mask
+    int32_t window;       // depth half-width in mm, 1 .. 65536; 0 disables the mask
     int32_t use_grey, use_depth;
     int32_t nch;          // use_grey + use_depth
     int32_t dim;          // nch * grid_x * grid_y * nbins

@@ -224,7 +224,9 @@ lbpf_status lbpf_create(lbpf_ctx **out, const lbpf_feature_cfg *cfg, size_t hbm_
     fp.grid_x = c.grid_x;
     fp.grid_y = c.grid_y;
     fp.nbins = c.mapping == LBPF_MAP_U59 ? 59 : 256;
-    fp.window = c.depth_window_mm;
+    // No two u16 depths are 65536 apart: wider windows mean the same, and the
+    // kernels add the half-width to a depth in 32 bits.
+    fp.window = std::min(std::max(c.depth_window_mm, 0), 65536);
     fp.use_grey = c.modality != LBPF_MOD_DEPTH;
     fp.use_depth = c.modality != LBPF_MOD_GREY;
     fp.nch = fp.use_grey + fp.use_depth;
