@@ -6,7 +6,7 @@
 //   * k_score_f32_rows (few rows or few identities, D a multiple of 4): operands
 //     straight to registers, D shared by the waves of a workgroup;
 //   * k_score_f32_bf16x3 (D a multiple of 32, 16-byte aligned rows): each value
-//     split exactly into three BF16 parts, six BF16 products, FP32 sums;
+//     split exactly into three BF16 parts, six of the nine BF16 products, FP32 sums;
 //   * k_score_f32_tiles (the same shapes, for callers that keep one order of
 //     summation, and row counts on the device): FP32 MFMA, tiles through LDS;
 //   * k_score_f32 (any D): v_mfma_f32_16x16x4f32 (D[m][n] += sum_k A[m][k]
@@ -562,17 +562,22 @@ __global__ __launch_bounds__(256) void k_score_f32_tiles(
 //
 // An FP32 value is the exact sum of three BF16 values: h = bf16(v), m =
 // bf16(v - h), l = v - h - m (8 + 8 + 8 significant bits, each remainder exact
-// in FP32). The product keeps the six terms h h, h m, m h, h l, l h, m m; what it
-// drops (m l, l m, l l) is at most 2^-25 of |x w| with either sign. Six BF16 MFMA
-// take 6 / 16 of the FP32 MFMA's cycles for the same product.
+// in FP32). Of the nine partial products of x w six are kept, h h, h m, m h, h l,
+// l h, m m; left out are m l and l m, at most 2^-25 of |x w| each and with either
+// sign (2^-27.4 in root mean square, both), and l l. Six BF16 MFMA take 6 / 16 of the FP32 MFMA's cycles.
 //
-// The matrix cores truncate as they accumulate, so every kFlush stages the
-// accumulators are added (round to nearest) to a running sum and start again
-// from zero. Error against 64 bits, relative to the condition scale, root mean
-// square, against the FP32 MFMA kernel's, 4096 x 1024 x 7552: histograms
-// against enrolled weights 1.8e-8 / 7.2e-8, uniform against normal values
-// 4.5e-9 / 2.7e-8, positive values 9.6e-8 / 1.3e-6, log-normal values over 10
-// decades 9.5e-8 / 5.1e-7 (kFlush 4 to 16 level, without it 2 to 3 times more).
+// h h and the five smaller terms are summed apart (lead, rest): an MFMA rounds its
+// sum to FP32, so in one accumulator six roundings a product would fall on the
+// large sum; apart, one does, none while the 16-bit products h h fit 24 bits, and
+// the others fall on 2^-8 of it. Every kFlush stages lead is added to a running
+// sum and starts again from zero; rest joins at the end. Error against 64 bits
+// relative to the condition scale, root mean square, against the FP32 MFMA
+// kernel's (all in one accumulator), 2048 x 1024 x 7552, normal weights: dense
+// uniform rows 1.8e-9 / 1.8e-8 (4.2e-9), 64 values that are not 0 a row 9.4e-9 /
+// 1.9e-8 (1.8e-8), 8 2.3e-8 / 2.4e-8 (3.2e-8), 2 2.9e-8 / 2.8e-8 (3.7e-8, and a
+// largest error of 2.6e-7 where the others have 1.2e-7). The third set of
+// accumulators takes the registers to 256 a lane; the loads' addresses are kept in
+// one register each for it.
 //
 // A workgroup of 8 waves owns 64 kWN feature rows x 64 kWK identities (256 x 128
 // or 128 x 256) over one of `splits` ranges of the 32-column stages of D; each
@@ -580,11 +585,11 @@ __global__ __launch_bounds__(256) void k_score_f32_tiles(
 // loads 24 floats (two stages ahead), splits them and writes the three planes into
 // one of two 72 KB LDS buffers (16-byte chunk c of a row at c ^ ((row / 2) % 4));
 // one plane is read by as many waves as a BF16 product's operand would be, but
-// multiplied twice as often. 16384 x 1024 x 7552 1270-1360 us (FP32 MFMA, 128 x 256
-// tiles: 1850), 4096 x 256 99 (135): 1.12-1.2 PFLOP/s of BF16, the matrix cores busy
-// 54% at a clock that falls below 2 GHz under them; waves out of step, raised
-// wave priority during the MFMAs, or VALU work interleaved by scheduling barriers
-// gained nothing (1330-1370 us against 1300 before the check below, 25 us of it).
+// multiplied twice as often. Whole calls, this / one accumulator / FP32 MFMA in
+// 128 x 256 tiles: 16384 x 1024 x 7552 1230 / 1281 / 1850 us, 4096 x 256 108 / 112 /
+// 135: 1.24 PFLOP/s of BF16. With one accumulator, waves out of step, raised wave
+// priority during the MFMAs, or VALU work interleaved by scheduling barriers gained
+// nothing (1330-1370 us against 1300).
 //
 // A tile is computed again by FP32 MFMAs on operands straight from memory where
 // the split does not hold: a result is not finite (h rounds to infinity, or m =
@@ -592,6 +597,9 @@ __global__ __launch_bounds__(256) void k_score_f32_tiles(
 // the tile's largest value and not 0, or 0 where that is above 2^30 (D up to 2^14
 // keeps 24 bits then).
 constexpr int kX3Waves = 8, kX3MaxSplits = 16;
+// A tile's operands are addressed in 32 bits from its first row: 256 rows of 4 D bytes.
+constexpr int32_t kX3MaxD = 1 << 21;
+static bool x3_takes(int32_t D) { return D % 32 == 0 && D <= kX3MaxD; }
 
 __device__ __forceinline__ bool finite_f32(float v) {
     return fabsf(v) <= 3.402823466e38f;
@@ -629,29 +637,35 @@ __global__ __launch_bounds__(64 * kX3Waves) void k_score_f32_bf16x3(
     const int32_t st1 = (int32_t)((int64_t)stages * (sp + 1) / splits);
 
     auto swz = [](int row, int chunk) { return chunk ^ ((row >> 1) & 3); };
-    const float *src[kGroups];
-    int dst[kGroups];
+    // Group i's rows are all X's or all W's. Rows past the matrices' ends re-read the
+    // last one (not stored).
+    static_assert(kTN * 4 % kT == 0, "a group of X rows or of W rows");
+    constexpr int kOfX = kTN * 4 / kT;
+    const float *Xt = X + (size_t)n0 * D, *Wt = W + (size_t)k0 * D;
+    uint32_t src[kGroups];  // bytes from the tile's first row
+    const int dst = (tid >> 2) * 64 + 16 * swz(tid >> 2, tid & 3);  // group 0's, then 8 KB apart
 #pragma unroll
     for (int i = 0; i < kGroups; ++i) {
-        // Rows past the matrices' ends re-read the last one (not stored).
         const int row = (i * kT + tid) >> 2, c = tid & 3;
-        const float *base = row < kTN ? X + (size_t)min(n0 + row, N - 1) * D
-                                        : W + (size_t)min(k0 + row - kTN, K - 1) * D;
-        src[i] = base + 8 * c;
-        dst[i] = row * 64 + 16 * swz(row, c);
+        const int32_t r = i < kOfX ? min(row, N - 1 - n0) : min(row - kTN, K - 1 - k0);
+        src[i] = ((uint32_t)r * (uint32_t)D + 8 * c) * 4;
     }
     floatx4 raw[kGroups][2];
     auto load = [&](int32_t st) {
+        typedef __attribute__((address_space(1))) const char gchar;
+        const auto *x = (gchar *)(Xt + 32 * st), *w = (gchar *)(Wt + 32 * st);
 #pragma unroll
-        for (int i = 0; i < kGroups; ++i)
+        for (int i = 0; i < kGroups; ++i) {
+            asm volatile("" : "+v"(src[i]));  // one register, not a 64-bit sum kept for the loop
 #pragma unroll
             for (int h = 0; h < 2; ++h)
-                raw[i][h] = *reinterpret_cast<const floatx4 *>(src[i] + 32 * st + 4 * h);
+                raw[i][h] = *(__attribute__((address_space(1))) const floatx4 *)((i < kOfX ? x : w) + src[i] + 16 * h);
+        }
     };
     const int fr = lane & 31, fq = lane >> 5;
-    floatx16 acc[2][2], sum[2][2];  // [identity block][row block]
+    floatx16 lead[2][2], rest[2][2], sum[2][2];  // [identity block][row block]
 
-    float top[kGroups] = {};  // largest |v|
+    float top = 0.0f;  // largest |v|
     auto store = [&](int b) {
 #pragma unroll
         for (int i = 0; i < kGroups; ++i) {
@@ -659,7 +673,7 @@ __global__ __launch_bounds__(64 * kX3Waves) void k_score_f32_bf16x3(
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const floatx2 v = {raw[i][e >> 1][2 * (e & 1)], raw[i][e >> 1][2 * (e & 1) + 1]};
-                asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(top[i]) : "v"(v[0]), "v"(v[1]));
+                asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(top) : "v"(v[0]), "v"(v[1]));
                 // Two a conversion; the pair's halves are floats as they are.
                 auto pack = [](floatx2 f) {
                     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
@@ -673,33 +687,43 @@ __global__ __launch_bounds__(64 * kX3Waves) void k_score_f32_bf16x3(
                 mv[e] = pack(r);
                 lv[e] = pack(rest(r, mv[e]));
             }
-            *reinterpret_cast<uintx4 *>(&lds[b][0][dst[i]]) = hv;
-            *reinterpret_cast<uintx4 *>(&lds[b][1][dst[i]]) = mv;
-            *reinterpret_cast<uintx4 *>(&lds[b][2][dst[i]]) = lv;
+            *reinterpret_cast<uintx4 *>(&lds[b][0][dst + 16 * kT * i]) = hv;
+            *reinterpret_cast<uintx4 *>(&lds[b][1][dst + 16 * kT * i]) = mv;
+            *reinterpret_cast<uintx4 *>(&lds[b][2][dst + 16 * kT * i]) = lv;
         }
     };
+    // lead[..]: h h; rest[..]: the terms 2^-8 of it and below.
     auto stage = [&](int b) {
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            bf16x8 x[2][3], w[2][3];
-#pragma unroll
-            for (int q = 2; q >= 0; --q)
+            bf16x8 xh[2], wh[2], xo[2], wo[2];
+            auto read = [&](int q, int row, bf16x8(&v)[2]) {
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
-                    const int rx = wn * 64 + 32 * i + fr, rw = kTN + wk * 64 + 32 * i + fr;
-                    const int c = 2 * s + fq;
-                    x[i][q] = *reinterpret_cast<const bf16x8 *>(&lds[b][q][rx * 64 + 16 * swz(rx, c)]);
-                    w[i][q] = *reinterpret_cast<const bf16x8 *>(&lds[b][q][rw * 64 + 16 * swz(rw, c)]);
+                    const int r = row + 32 * i + fr;
+                    v[i] = *reinterpret_cast<const bf16x8 *>(&lds[b][q][r * 64 + 16 * swz(r, 2 * s + fq)]);
                 }
-            constexpr int qw[6] = {2, 0, 1, 1, 0, 0}, qx[6] = {0, 2, 1, 0, 1, 0};
-#pragma unroll
-            for (int t = 0; t < 6; ++t)
+            };
+            auto mul = [&](const bf16x8(&w)[2], const bf16x8(&x)[2], floatx16(&to)[2][2]) {
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
 #pragma unroll
                     for (int i = 0; i < 2; ++i)
-                        acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                            w[j][qw[t]], x[i][qx[t]], acc[j][i], 0, 0, 0);
+                        to[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[j], x[i], to[j][i], 0, 0, 0);
+            };
+            const int rx = wn * 64, rw = kTN + wk * 64;
+            read(0, rx, xh);
+            read(0, rw, wh);
+            read(2, rw, wo);
+            mul(wh, xh, lead);
+            mul(wo, xh, rest);
+            read(2, rx, xo);
+            mul(wh, xo, rest);
+            read(1, rx, xo);
+            mul(wh, xo, rest);
+            read(1, rw, wo);
+            mul(wo, xh, rest);
+            mul(wo, xo, rest);
         }
     };
     auto flush = [&](bool first) {
@@ -707,9 +731,9 @@ __global__ __launch_bounds__(64 * kX3Waves) void k_score_f32_bf16x3(
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                if (first) sum[j][i] = floatx16{};
-                else sum[j][i] += acc[j][i];
-                acc[j][i] = floatx16{};
+                if (first) sum[j][i] = rest[j][i] = floatx16{};
+                else sum[j][i] += lead[j][i];
+                lead[j][i] = floatx16{};
             }
     };
     flush(true);
@@ -726,15 +750,16 @@ __global__ __launch_bounds__(64 * kX3Waves) void k_score_f32_bf16x3(
         __syncthreads();
     }
     flush(false);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) sum[j][i] += rest[j][i];
 
     // A split value is off by 2^-134 at most, so a result by 2^-134 D max |v|.
     uint32_t *most = reinterpret_cast<uint32_t *>(&lds[0][0][0]);
-    float mine = top[0];
-#pragma unroll
-    for (int i = 1; i < kGroups; ++i) mine = fmaxf(mine, top[i]);
     if (tid == 0) *most = 0;
     __syncthreads();
-    atomicMax(most, __float_as_uint(mine));
+    atomicMax(most, __float_as_uint(top));
     __syncthreads();
     const float all = __uint_as_float(*most);
     const float small = all * 0x1p-96f, none = all > 0x1p30f ? -1.0f : 0.0f;
@@ -1052,7 +1077,7 @@ static int32_t x3_splits(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_
 }
 
 int32_t score_f32_splits(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_t part_elems) {
-    if (few_rows(N, K, D, num_cus, D % 32 == 0)) {
+    if (few_rows(N, K, D, num_cus, x3_takes(D))) {
         // Two workgroups a CU, each wave with at least four 32-column steps.
         const int32_t nb = 16 * rows_blocks(N);
         const int64_t groups = (int64_t)((K + 31) / 32) * ((N + nb - 1) / nb);
@@ -1061,7 +1086,7 @@ int32_t score_f32_splits(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_
                                         (int64_t)(part_elems / ((size_t)N * (size_t)K))});
         return (int32_t)std::max<int64_t>(sp, 1);
     }
-    return D % 32 == 0 ? x3_splits(N, K, D, num_cus, part_elems) : 1;
+    return x3_takes(D) ? x3_splits(N, K, D, num_cus, part_elems) : 1;
 }
 
 int32_t score_f32_ranges(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_t part_elems) {
@@ -1103,7 +1128,7 @@ hipError_t launch_score_f32(const float *X, int32_t N, const float *W, const flo
             (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         cus = std::max(cus, 1);
     }
-    const bool x3 = !n_dev && D % 32 == 0;
+    const bool x3 = !n_dev && x3_takes(D);
     if (!one_order && aligned && splits >= 1 && few_rows(N, K, D, cus, x3) && (splits == 1 || part)) {
         const int32_t nb = rows_blocks(N);
         const dim3 g((K + 31) / 32, (N + 16 * nb - 1) / (16 * nb), splits);
