@@ -478,12 +478,24 @@ int32_t lbpf_weights_count(const lbpf_weights *weights);
  * lowest part, at most 2^-24 of |x w|, are left out) and sums are FP32. The
  * error is no larger than that of one FP32 FMA a product (within 3% where a
  * row has one product that is not 0, a tenth of it in dense rows of 7552).
- * Products that would leave the GPU idle split the feature dimension into ranges whose partial sums are
- * added in range order, so results are deterministic. Close scores are summed
- * again in one fixed order (feature dimensions of a multiple of 32), so that
- * the identity does not depend on the way taken. In the reduced precisions the
- * operands are converted as documented for lbpf_precision and the products
- * accumulated in FP32. Errors: LBPF_E_INVALID, LBPF_E_HIP. */
+ * Products that would leave the GPU idle split the feature dimension into
+ * ranges whose partial sums are added in range order. The same call gives the
+ * same results; the last bits of a score may differ between calls that differ
+ * in N, in the outputs asked for or in where they run (eager, captured, a
+ * pipeline), which choose kernels and ranges, and with rows beside it that hold
+ * infinities or NaN.
+ * Identities: where a row's best scores lie within what rounding may turn round
+ * (judged by the norms of the row and of the weights), those scores are summed
+ * again in one order, that of lbpf_score's FP32 matrix-core tiles: 1, 2 or 4
+ * ranges of D, by N and K (pipelines: one), where D is a multiple of 32.
+ * They replace the others in scores_opt when argmax_opt is
+ * given, and the first largest names the identity, which so does not depend on
+ * the kernel that made the scores (with another number of ranges one of two
+ * scores that close may win over the other). A row with many scores that close
+ * takes longer: about 25 us for each three at D = 7552.
+ * In the reduced precisions the operands are converted as documented for
+ * lbpf_precision and the products accumulated in FP32, in an order that N and K
+ * choose. Errors: LBPF_E_INVALID, LBPF_E_HIP. */
 lbpf_status lbpf_score(lbpf_ctx *ctx, const float *hist, int32_t N, const lbpf_weights *weights,
                        float *scores_opt, int32_t *argmax_opt, void *stream);
 
@@ -512,8 +524,11 @@ lbpf_status lbpf_score_plain(lbpf_ctx *ctx, const float *hist, int32_t N,
  * (step 6) as lbpf_score with FP32 weights, without a context: hist DEVICE
  * [N][D] FP32, W DEVICE [K][D] FP32 row-major, b DEVICE [K] FP32 (the caller
  * owns all three), scores_opt DEVICE [N][K] FP32 or NULL, argmax_opt DEVICE
- * [N] int32 or NULL (not both NULL). The same kernels and results as
- * lbpf_score. The call allocates nothing: the scratch its kernels need (each
+ * [N] int32 or NULL (not both NULL). The same kernels as lbpf_score, over
+ * as many ranges as this scratch holds (last bits may differ); the weights'
+ * norms are not at hand, so scores count as close within 2^-12 of |x w|, too
+ * little where a row is nearly at right angles to all its best weights. The
+ * call allocates nothing: the scratch its kernels need (each
  * pass's scores when no score buffer is given, the partial tiles when the
  * feature dimension is split over workgroups) is a static device array of
  * LBPF_NOALLOC_SCRATCH_BYTES that the library holds on every GPU it runs on

@@ -156,19 +156,21 @@ hipError_t launch_track(const int32_t *prev, const int32_t *ps, int32_t P, const
 // summed with the argmax by a second kernel); otherwise the 64 x 64-tile
 // kernels. splits: from score_f32_splits; 0 selects the 64 x 64-tile kernels.
 int32_t score_f32_splits(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_t part_elems);
-// Ranges of D of the order in which close scores are summed again to name an
-// identity (1, 2 or 4): as many as let 128 x 128 tiles fill the GPU, as far as
-// part_elems holds their sums.
-int32_t score_f32_ranges(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_t part_elems);
+// The order in which close scores are summed again to name an identity: 1, 2 or 4
+// ranges of D, as many as let 128 x 128 tiles fill the GPU, as far as part_elems
+// holds their sums; 0: none (D not a multiple of 32).
+int32_t score_f32_order(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_t part_elems);
 // S is always written; argmax (may be null) gets each row's best identity.
 // one_order: FP32 MFMA tiles whatever the sizes (the trainer's Gram products,
 // whose steps follow their last bits); n_dev: these or the few-rows kernel.
-// ranges: from score_f32_ranges (0: close scores are compared as they are).
+// order: from score_f32_order (0: close scores are compared as they are). norm: the
+// Euclidean norms of the rows of W, from launch_row_norms (null: not known).
 hipError_t launch_score_f32(const float *X, int32_t N, const float *W, const float *b,
                             int32_t K, int32_t D, float *S, int32_t *argmax, hipStream_t s,
                             int32_t splits = 0, float *part = nullptr,
                             const int32_t *n_dev = nullptr, bool one_order = false,
-                            int32_t ranges = 0);
+                            int32_t order = 0, const float *norm = nullptr);
+hipError_t launch_row_norms(const float *W, int32_t K, int32_t D, float *norm, hipStream_t s);
 hipError_t launch_argmax(const float *S, int32_t N, int32_t K, int32_t *argmax, hipStream_t s,
                          const int32_t *n_dev = nullptr);
 

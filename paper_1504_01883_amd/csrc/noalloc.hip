@@ -103,7 +103,7 @@ extern "C" lbpf_status lbpf_score_noalloc(const float *hist, int32_t N, const fl
         const int32_t sp = score_f32_splits(n, K, D, ds.num_cus, part_elems);
         e = launch_score_f32(hist + (size_t)n0 * Dz, n, W, b, K, D, S,
                              argmax_opt ? argmax_opt + n0 : nullptr, s, sp, part, nullptr, false,
-                             score_f32_ranges(n, K, D, ds.num_cus, part_elems));
+                             score_f32_order(n, K, D, ds.num_cus, part_elems));
         if (e != hipSuccess)
             return set_last_error(LBPF_E_HIP, std::string("score launch: ") + hipGetErrorString(e));
     }

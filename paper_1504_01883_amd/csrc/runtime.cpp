@@ -118,6 +118,7 @@ struct lbpf_weights {
     float *b = nullptr;
     uint8_t *Wq = nullptr;    // quantised rows (reduced precision)
     float *sw = nullptr;      // their scales
+    float *norm = nullptr;    // Euclidean norms of the rows (FP32 precision only)
     size_t bytes = 0;
 };
 
@@ -556,7 +557,7 @@ lbpf_status lbpf_weights_create(lbpf_ctx *ctx, const float *W, const float *b, i
     const bool lp = precision != LBPF_FP32;
     const size_t bbytes = sizeof(float) * (size_t)K;
     const size_t wbytes = lp ? (size_t)K * lp_pitch(D, precision) + bbytes
-                             : sizeof(float) * (size_t)K * D;
+                             : sizeof(float) * (size_t)K * D + bbytes;
     // Reduced-precision weights need the context's feature quantisation
     // scratch: kLpChunkRows rows at this precision's feature pitch (at least
     // the BF16 one). It is allocated with the first such weights and grows
@@ -611,6 +612,8 @@ lbpf_status lbpf_weights_create(lbpf_ctx *ctx, const float *W, const float *b, i
         if (e == hipSuccess) e = hipMalloc((void **)&w->W, sizeof(float) * (size_t)K * D);
         if (e == hipSuccess)
             e = hipMemcpyAsync(w->W, W, sizeof(float) * (size_t)K * D, hipMemcpyDeviceToDevice, s);
+        if (e == hipSuccess) e = hipMalloc((void **)&w->norm, bbytes);
+        if (e == hipSuccess) e = launch_row_norms(w->W, K, D, w->norm, s);
     } else {
         if (e == hipSuccess) e = hipMalloc((void **)&w->Wq, (size_t)K * lp_pitch(D, precision));
         if (e == hipSuccess) e = hipMalloc((void **)&w->sw, bbytes);
@@ -632,6 +635,7 @@ void lbpf_weights_destroy(lbpf_weights *w) {
     if (w->b) (void)hipFree(w->b);
     if (w->Wq) (void)hipFree(w->Wq);
     if (w->sw) (void)hipFree(w->sw);
+    if (w->norm) (void)hipFree(w->norm);
     if (w->ctx) w->ctx->used -= w->bytes;
     delete w;
 }
@@ -707,7 +711,7 @@ lbpf_status lbpf_score(lbpf_ctx *ctx, const float *hist, int32_t N, const lbpf_w
         const int32_t sp = n == std::min(rows, N) ? splits : splits_of(n);
         HIP_TRY(launch_score_f32(hist + (size_t)n0 * D, n, w->W, w->b, w->K, w->D, S,
                                  argmax_opt ? argmax_opt + n0 : nullptr, s, sp, part, nullptr, false,
-                                 score_f32_ranges(n, w->K, w->D, ctx->num_cus, kPartElems)),
+                                 score_f32_order(n, w->K, w->D, ctx->num_cus, kPartElems), w->norm),
                 "score launch");
     }
     if (order) HIP_TRY(hipEventRecord(ctx->scratch_ev, s), "hipEventRecord");
@@ -811,7 +815,7 @@ lbpf_status lbpf_pipeline_create(lbpf_ctx *ctx, const lbpf_weights *w, int32_t m
                                  split, lc, d_order, p->d_queue, ctx->num_cus, d_n);
         if (el == hipSuccess && !lp)
             el = launch_score_f32(hist, max_boxes, w->W, w->b, K, D, S, argmax, cs, 1, nullptr, d_n,
-                                  false, 1);
+                                  false, 1, w->norm);
         if (el == hipSuccess && lp)
             el = launch_quant_rows(hist, max_boxes, D, w->prec, p->d_xq, p->d_sx, cs, d_n);
         if (el == hipSuccess && lp)

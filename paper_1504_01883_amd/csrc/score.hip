@@ -26,6 +26,7 @@ namespace lbpf {
 namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
 
 constexpr int kTile = 64;
 constexpr int kRowsWaves = 8;      // waves of k_score_f32_rows
@@ -146,168 +147,350 @@ __global__ __launch_bounds__(512) void k_score_f32(const float *__restrict__ X, 
 
 // --- Close decisions -----------------------------------------------------------------
 //
-// The named identity does not depend on which FP32 kernel made the scores: where a
-// row's best scores lie within what two orders of summation differ by, those scores
-// are summed again in one fixed order, that of k_score_f32_tiles (per range of D,
-// each eight columns as 0 4 1 5 2 6 3 7, an FMA each; the ranges' sums in order; the
-// bias), written over the others and compared. Within: 2^-17 of the best one's
-// |x w| + |b|, 30 times the usual difference; about 1 row in 8000 of a gallery's. A
-// wave takes about 25 us over 7552 columns in one range, 7 in four: a chain of FMAs
-// in one lane a score, its operands staged in LDS by all lanes and read 16 columns
-// ahead. 16384 x 1024: 1303 us with no close row, 1326 with some, 1990 with one or
-// more in every row.
+// Where a row's best scores lie within what two orders of summation differ by, those
+// scores are summed again in one fixed order, written over the others and compared:
+// the order of the FP32 MFMA tiles (per range of D, each eight columns as 0 4 1 5 2 6
+// 3 7, an FMA each; the ranges' sums in order; the bias). So the named identity does
+// not follow the kernel that made the scores.
+//
+// Within: each score may be off by 2^-23 sqrt(D) |x| |w|, 4.8 standard deviations of
+// D roundings of sums as large as |x| |w| (no partial sum is larger), and by 2^-22 of
+// itself for the bias's addition. Of |x| the scoring kernels leave the value or an
+// upper bound. Where the weights' norms are not known, 2^-13 of |x w| stands for the
+// first: 60 times the usual difference, but too little where x is nearly at right
+// angles to all the weights close to the best.
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
+
+struct Window {
+    // An identity's share: reach |of[k] - from v|, of the norms of the weights' rows,
+    // reach = 2^-23 sqrt(D) |x|, from = 0; or of the biases, reach = 2^-13, from = 1.
+    // reach no number: no score is settled.
+    float reach, from;
+    const float *__restrict__ of;
+    // xn: |x|, or more.
+    __device__ Window(const float *norm, const float *bias, float xn, int32_t D)
+        : reach(norm ? 0x1p-23f * sqrtf((float)D) * xn : 0x1p-13f), from(norm ? 0.0f : 1.0f),
+          of(norm ? norm : bias) {
+        if (!(reach < 1e30f)) reach = NAN;
+    }
+    __device__ __forceinline__ float off(float v, float of_k) const {
+        return reach * fabsf(of_k - from * v) + 0x1p-22f * fabsf(v);
+    }
+    // The most a score may be in another order; itself where that makes no sense.
+    __device__ __forceinline__ float upper(float v, float of_k) const {
+        return fabsf(v) < 1e37f ? v + off(v, of_k) : v;
+    }
+};
+
 struct Closest {
-    float best = -INFINITY, second = -INFINITY;
+    float best = -INFINITY, most = -INFINITY;   // the best score and its upper
+    float top = -INFINITY, second = -INFINITY;  // the highest uppers
     int32_t arg;  // larger than any valid index at first
     bool nan = false;
     __device__ explicit Closest(int32_t K) : arg(K) {}
-    __device__ __forceinline__ void see(float v, int32_t k, int32_t K) {
-        second = fmaxf(second, fminf(v, best));
+    __device__ __forceinline__ void see(float v, float upper, int32_t k, int32_t K) {
+        second = fmaxf(second, fminf(upper, top));
+        top = fmaxf(top, upper);
         nan |= v != v;
         if (v > best || arg == K) {
             best = v;
+            most = upper;
             arg = k;
         }
     }
-    __device__ __forceinline__ void take(float ob, int32_t oa, float os) {
-        second = fmaxf(fmaxf(second, os), fminf(best, ob));
+    __device__ __forceinline__ void take(float ob, float om, int32_t oa, float ot, float os) {
+        second = fmaxf(fmaxf(second, os), fminf(top, ot));
+        top = fmaxf(top, ot);
         if (ob > best || (ob == best && oa < arg)) {
             best = ob;
+            most = om;
             arg = oa;
         }
     }
     __device__ __forceinline__ void reduce_wave() {
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) {
-            const float ob = __shfl_xor(best, off, 64), os = __shfl_xor(second, off, 64);
-            take(ob, __shfl_xor(arg, off, 64), os);
+            const float ob = __shfl_xor(best, off, 64), om = __shfl_xor(most, off, 64),
+                        ot = __shfl_xor(top, off, 64), os = __shfl_xor(second, off, 64);
+            take(ob, om, __shfl_xor(arg, off, 64), ot, os);
         }
         nan = __ballot(nan) != 0;
     }
-    // Scores from here on are close; no number where none is to be settled. After
-    // reduce_wave, and alike in all lanes (a row without NaN).
-    __device__ __forceinline__ float floor(const float *__restrict__ b) const {
-        if (nan) return NAN;
-        const float bias = b[arg], scale = fabsf(best - bias) + fabsf(bias);
-        return scale < 1e37f ? best - 0x1p-17f * scale : NAN;
+    // Scores whose uppers reach this are close; no number where none is to be settled.
+    // After reduce_wave, and alike in all lanes (a row without NaN).
+    __device__ __forceinline__ float floor(const Window &w) const {
+        if (nan || !(fabsf(best) < 1e37f) || !(w.reach >= 0.0f)) return NAN;
+        return best - (most - best);
     }
 };
 
 constexpr int kSettleRows = 3;       // candidates a turn
+constexpr int kSettleAsk = 4;        // as many close ones at most are asked for their partial sums
 constexpr int kSettlePieces = 2;     // of 256 columns a step
 constexpr int kSettleStride = 532;   // floats of LDS a row, its 1, 2 or 4 ranges 4 apart
 constexpr int kSettleLds = (1 + kSettleRows) * kSettleStride + 16;
 
-// One wave: row S_n's closest scores again, and the identity. ranges: 1, 2 or 4, D a
-// multiple of 32 ranges.
-__device__ __forceinline__ int32_t settle(const float *__restrict__ x, const float *__restrict__ W,
-                          const float *__restrict__ b, float *S_n, int32_t K, int32_t D, int ranges,
-                          const Closest &row, float floor, float *lds) {
+// The fixed order's ranges: 1, 2 or 4 of equal length, D a multiple of 32 times that.
+struct Ranges {
+    int n;
+    int32_t len;
+    __device__ Ranges(int order, int32_t D) : n(order), len(D / order) {}
+    __device__ __forceinline__ int32_t own(int, int32_t) const { return len; }
+};
+
+// 16 columns onto a sum, in the fixed order.
+__device__ __forceinline__ float chain16(const floatx4 (&x)[4], const floatx4 (&w)[4], float acc) {
+#pragma unroll
+    for (int h = 0; h < 4; h += 2)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            acc = __builtin_fmaf(x[h][e], w[h][e], acc);
+            acc = __builtin_fmaf(x[h + 1][e], w[h + 1][e], acc);
+        }
+    return acc;
+}
+
+// One wave: up to kSettleRows scores (lane c: identity cand of candidate c) in the
+// fixed order; lane c * ranges + r returns range r's sum of candidate c. A chain of
+// FMAs in one lane a sum, its operands staged in LDS by all lanes (lane l copies
+// columns 4 (l % per) .. + 3 of a piece of range l / per) and read 16 columns ahead:
+// 25 us over 7552 columns in one range, 7 in four.
+__device__ __forceinline__ float settle_few(const float *__restrict__ x, const float *__restrict__ W,
+                                            int32_t D, const Ranges &rg, int32_t cand, int n, float *lds) {
     const int lane = threadIdx.x & 63;
+    const int per = 64 / rg.n, cols = 4 * per * kSettlePieces;  // of a range, a step
+    const int32_t at = 4 * (lane % per), from = (lane / per) * rg.len, own = rg.own(lane / per, D);
+    const int to = (lane / per) * (cols + 4) + at;
+    const int mine = lane % rg.n, of = lane / rg.n;
+    float acc = 0.0f;
+    floatx4 v[1 + kSettleRows][kSettlePieces];
+    auto load = [&](int32_t c0) {
+#pragma unroll
+        for (int c = 0; c <= kSettleRows; ++c) {
+            // Fewer than kSettleRows: the first candidate again.
+            const float *src =
+                c == 0 ? x : W + (size_t)__builtin_amdgcn_readlane(cand, c <= n ? c - 1 : 0) * D;
+#pragma unroll
+            for (int p = 0; p < kSettlePieces; ++p) {
+                const int32_t d = c0 + 4 * per * p + at;
+                v[c][p] = *reinterpret_cast<const floatx4 *>(src + min(from + d, D - 4));
+                if (d >= own) v[c][p] = floatx4{};  // nothing to add
+            }
+        }
+    };
+    load(0);
+    for (int32_t c0 = 0; c0 < rg.len; c0 += cols) {
+#pragma unroll
+        for (int c = 0; c <= kSettleRows; ++c) {
+#pragma unroll
+            for (int p = 0; p < kSettlePieces; ++p)
+                *reinterpret_cast<floatx4 *>(lds + c * kSettleStride + to + 4 * per * p) = v[c][p];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (c0 + cols < rg.len) load(c0 + cols);
+        if (of < n) {
+            const float *px = lds + mine * (cols + 4), *pw = px + (1 + of) * kSettleStride;
+            // An LDS read's time is that of 16 columns' FMAs: read as far ahead
+            // (past the row's end at last, into what the buffer has room for).
+            floatx4 x0[4], w0[4], x1[4], w1[4];
+            auto read = [&](floatx4(&xs)[4], floatx4(&ws)[4], int j) {
+#pragma unroll
+                for (int h = 0; h < 4; ++h) {
+                    xs[h] = *reinterpret_cast<const floatx4 *>(px + j + 4 * h);
+                    ws[h] = *reinterpret_cast<const floatx4 *>(pw + j + 4 * h);
+                }
+            };
+            read(x0, w0, 0);
+            for (int j = 0; j < cols; j += 32) {
+                read(x1, w1, j + 16);
+                __builtin_amdgcn_sched_barrier(0);
+                acc = chain16(x0, w0, acc);
+                __builtin_amdgcn_sched_barrier(0);
+                read(x0, w0, j + 32);
+                __builtin_amdgcn_sched_barrier(0);
+                acc = chain16(x1, w1, acc);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    return acc;
+}
+
+// Sum over a wave's lanes up to this one.
+__device__ __forceinline__ float scan_wave(float v) {
+    auto add = [&](auto ctrl, auto rows) {
+        v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value,
+                                                        decltype(rows)::value, 0xF, false));
+    };
+    using std::integral_constant;
+    const integral_constant<int, 0xF> all;
+    add(integral_constant<int, 0x111>(), all);                             // row_shr:1
+    add(integral_constant<int, 0x112>(), all);                             // row_shr:2
+    add(integral_constant<int, 0x114>(), all);                             // row_shr:4
+    add(integral_constant<int, 0x118>(), all);                             // row_shr:8
+    add(integral_constant<int, 0x142>(), integral_constant<int, 0xA>());  // row_bcast:15
+    add(integral_constant<int, 0x143>(), integral_constant<int, 0xC>());  // row_bcast:31
+    return v;
+}
+
+// One wave: what two orders of summation of x u and of x w differ by, from the partial
+// sums themselves (every fourth): twice Window's share of the root of their squares'
+// sum. Where the terms have either sign that is 50 times less than Window's bound by
+// the norms, so that few of the rows the norms alone would have settled (1 in 100 of
+// random weights) are. About 6 us, where settle_few takes 15 to 25.
+__device__ __forceinline__ floatx2 spread(const float *__restrict__ x, const float *__restrict__ u,
+                                          const float *__restrict__ w, int32_t D, const Ranges &rg) {
+    constexpr int kFly = 4;  // 256 columns each, on their way at a time
+    const int lane = threadIdx.x & 63;
+    floatx2 sum{0.0f, 0.0f};
+    for (int r = 0; r < rg.n; ++r) {
+        const int32_t from = r * rg.len, own = rg.own(r, D);
+        floatx2 before{0.0f, 0.0f};
+        floatx4 a[2][kFly], b[2][kFly], c[2][kFly];
+        auto load = [&](int g, int32_t d0) {
+#pragma unroll
+            for (int f = 0; f < kFly; ++f) {
+                const int32_t at = min(from + d0 + 256 * f + 4 * lane, D - 4);
+                a[g][f] = *reinterpret_cast<const floatx4 *>(x + at);
+                b[g][f] = *reinterpret_cast<const floatx4 *>(u + at);
+                c[g][f] = *reinterpret_cast<const floatx4 *>(w + at);
+            }
+        };
+        auto add = [&](int g, int32_t d0) {
+#pragma unroll
+            for (int f = 0; f < kFly; ++f) {
+                const bool in = d0 + 256 * f + 4 * lane < own;
+                const floatx4 s = a[g][f] * b[g][f], t = a[g][f] * c[g][f];
+                const floatx2 v{scan_wave(in ? s.x + s.y + (s.z + s.w) : 0.0f),
+                                scan_wave(in ? t.x + t.y + (t.z + t.w) : 0.0f)};
+                const floatx2 p = before + v;
+                if (in) sum += p * p;
+                before += floatx2{__int_as_float(__builtin_amdgcn_readlane(__float_as_int(v.x), 63)),
+                                  __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v.y), 63))};
+            }
+        };
+        load(0, 0);
+        for (int32_t d0 = 0; d0 < own; d0 += 512 * kFly) {
+            load(1, d0 + 256 * kFly);
+            add(0, d0);
+            load(0, d0 + 512 * kFly);
+            add(1, d0 + 256 * kFly);
+        }
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1)
+        sum += floatx2{__shfl_xor(sum.x, off, 64), __shfl_xor(sum.y, off, 64)};
+    return floatx2{0x1p-22f * sqrtf(4.0f * sum.x), 0x1p-22f * sqrtf(4.0f * sum.y)};
+}
+
+// One wave: |x|.
+__device__ __forceinline__ float norm_of(const float *__restrict__ x, int32_t D) {
+    constexpr int kFly = 8;
+    const int lane = threadIdx.x & 63;
+    float sum = 0.0f;
+    for (int32_t d0 = 0; d0 < D; d0 += 256 * kFly) {
+        floatx4 a[kFly];
+#pragma unroll
+        for (int u = 0; u < kFly; ++u)
+            a[u] = *reinterpret_cast<const floatx4 *>(x + min(d0 + 256 * u + 4 * lane, D - 4));
+#pragma unroll
+        for (int u = 0; u < kFly; ++u) {
+            const floatx4 t = a[u] * a[u];
+            sum += d0 + 256 * u + 4 * lane < D ? t.x + t.y + (t.z + t.w) : 0.0f;
+        }
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    return sqrtf(sum);
+}
+
+// One wave: row S_n's close scores again, and the identity. order: see Ranges.
+//
+// Whole calls in us, D = 7552 (FP32 MFMA tiles throughout / this), weights normal and
+// rows uniform: no row close 5 x 1024 131 / 18, 4096 x 256 135 / 106, 16384 x 1024 1847
+// / 1295; as they come (26 of 4096 rows and 212 of 16384 within the first window, 0 and
+// 6 within the second) 132 / 17, 135 / 112, 1847 / 1314; in every row two copies within
+// rounding 135 / 46, 137 / 174, 1845 / 1770; in every row 64 copies 138 / 473, 140 /
+// 1211, 1846 / 12305.
+__device__ __forceinline__ int32_t settle(const float *__restrict__ x, const float *__restrict__ W,
+                                          const float *__restrict__ b, float *S_n, int32_t K,
+                                          int32_t D, int order, const Closest &row, float row_floor,
+                                          const Window &row_win, float *lds) {
+    const int lane = threadIdx.x & 63;
+    const Ranges rg(order, D);
+    // Alike in all lanes.
+    auto uniform = [](float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); };
+    float floor = uniform(row_floor);
+    const float row_best = uniform(row.best);
+    const int32_t row_arg = __builtin_amdgcn_readfirstlane(row.arg);
+    Window win = row_win;
+    win.reach = uniform(row_win.reach);
     __threadfence_block();  // the row's scores, written by other lanes
     auto score = [&](int32_t k) { return k < K ? S_n[min(k, K - 1)] : -INFINITY; };
-    // More than a wave's worth, all alike: rows of W or X that are the same, not chance.
+    auto close = [&](float v, int32_t k) { return k < K && win.upper(v, win.of[min(k, K - 1)]) >= floor; };
     int32_t many = 0;
     bool alike = true;
     uint64_t blocks = 0;  // of 64 scores, the first 64 blocks: with a close one
-#pragma unroll 8
-    for (int32_t k0 = 0; k0 < K; k0 += 64) {
-        const float v = score(k0 + lane);
-        const uint64_t close = __ballot(v >= floor);
-        many += __builtin_popcountll(close);
-        if (close && k0 < 64 * 64) blocks |= 1ull << (k0 / 64);
-        alike = alike && __ballot(v >= floor && v != row.best) == 0;
+    auto count = [&]() {
+        many = 0;
+        alike = true;
+        blocks = 0;
+#pragma unroll 4
+        for (int32_t k0 = 0; k0 < K; k0 += 64) {
+            const float v = score(k0 + lane);
+            const bool is = close(v, k0 + lane);
+            const uint64_t m = __ballot(is);
+            many += __builtin_popcountll(m);
+            if (m && k0 < 64 * 64) blocks |= 1ull << (k0 / 64);
+            alike = alike && __ballot(is && v != row_best) == 0;
+        }
+    };
+    count();
+    if (many > kSettleAsk && win.from == 0.0f) {
+        // The norm itself, where the window may be of a bound of it.
+        win = Window(win.of, b, uniform(norm_of(x, D)), D);
+        floor = row_best - win.off(row_best, win.of[row_arg]);
+        count();
     }
-    if (many > 64 && alike) return row.arg;
-
-    // Lane l copies columns 4 (l % per) .. + 3 of a piece of range l / per; lane c *
-    // ranges + r sums range r of candidate c.
-    const int per = 64 / ranges, cols = 4 * per * kSettlePieces;  // of a range, a step
-    const int32_t len = D / ranges;
-    const int32_t at = 4 * (lane % per), from = (lane / per) * len;
-    const int to = (lane / per) * (cols + 4) + at;
-    const int mine = lane % ranges, of = lane / ranges;
+    // More than a wave's worth, all alike: rows of W or X that are the same, not chance.
+    if (many < 2 || (many > 64 && alike)) return row_arg;
+    if (many <= kSettleAsk) {  // once more by their own partial sums
+        bool other = false;
+        for (int32_t k0 = 0; k0 < K && !other; k0 += 64) {
+            if (k0 < 64 * 64 && !((blocks >> (k0 / 64)) & 1)) continue;
+            uint64_t m = __ballot(close(score(k0 + lane), k0 + lane) && k0 + lane != row_arg);
+            for (; m && !other; m &= m - 1) {
+                const int32_t k = k0 + __builtin_ctzll(m);
+                const float v = S_n[k];
+                const floatx2 off = spread(x, W + (size_t)row_arg * D, W + (size_t)k * D, D, rg);
+                other = v + 0x1p-22f * fabsf(v) + off.y >= row_best - 0x1p-22f * fabsf(row_best) - off.x;
+            }
+        }
+        if (!other) return row_arg;
+    }
     float best = -INFINITY;
     int32_t arg = K;
-    int32_t cand = 0;  // lane c: candidate c
-    int n = 0;
+    int32_t cand = 0;
     int32_t k0 = 0;
     uint64_t m = 0;  // close ones of the block before k0, not taken yet
     for (;;) {
-        for (n = 0; n < kSettleRows; ++n) {
+        int n = 0;
+        for (; n < kSettleRows; ++n) {
             while (m == 0 && k0 < K) {
-                if (k0 >= 64 * 64 || (blocks >> (k0 / 64)) & 1) m = __ballot(score(k0 + lane) >= floor);
+                if (k0 >= 64 * 64 || (blocks >> (k0 / 64)) & 1) m = __ballot(close(score(k0 + lane), k0 + lane));
                 k0 += 64;
             }
             if (m == 0) break;
-            if (lane == n) cand = k0 - 64 + __builtin_ctzll(m);
+            const int32_t k = k0 - 64 + __builtin_ctzll(m);
+            if (lane == n) cand = k;
             m &= m - 1;
         }
         if (n == 0) return arg;
-        float acc = 0.0f;
-        floatx4 v[1 + kSettleRows][kSettlePieces];
-        auto load = [&](int32_t c0) {
-#pragma unroll
-            for (int c = 0; c <= kSettleRows; ++c) {
-                // Fewer than kSettleRows: the first candidate again.
-                const float *src =
-                    c == 0 ? x : W + (size_t)__builtin_amdgcn_readlane(cand, c <= n ? c - 1 : 0) * D;
-#pragma unroll
-                for (int p = 0; p < kSettlePieces; ++p) {
-                    const int32_t d = c0 + 4 * per * p + at;
-                    v[c][p] = *reinterpret_cast<const floatx4 *>(src + from + min(d, len - 4));
-                    if (d >= len) v[c][p] = floatx4{};  // nothing to add
-                }
-            }
-        };
-        load(0);
-        for (int32_t c0 = 0; c0 < len; c0 += cols) {
-#pragma unroll
-            for (int c = 0; c <= kSettleRows; ++c) {
-#pragma unroll
-                for (int p = 0; p < kSettlePieces; ++p)
-                    *reinterpret_cast<floatx4 *>(lds + c * kSettleStride + to + 4 * per * p) = v[c][p];
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            if (c0 + cols < len) load(c0 + cols);
-            if (of < n) {
-                const float *px = lds + mine * (cols + 4), *pw = px + (1 + of) * kSettleStride;
-                // An LDS read's time is that of 16 columns' FMAs: read as far ahead
-                // (past the row's end at last, into what the buffer has room for).
-                floatx4 x0[4], w0[4], x1[4], w1[4];
-                auto read = [&](floatx4(&xs)[4], floatx4(&ws)[4], int j) {
-#pragma unroll
-                    for (int h = 0; h < 4; ++h) {
-                        xs[h] = *reinterpret_cast<const floatx4 *>(px + j + 4 * h);
-                        ws[h] = *reinterpret_cast<const floatx4 *>(pw + j + 4 * h);
-                    }
-                };
-                auto chain = [&](const floatx4(&xs)[4], const floatx4(&ws)[4]) {
-#pragma unroll
-                    for (int h = 0; h < 4; h += 2)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            acc = __builtin_fmaf(xs[h][e], ws[h][e], acc);
-                            acc = __builtin_fmaf(xs[h + 1][e], ws[h + 1][e], acc);
-                        }
-                };
-                read(x0, w0, 0);
-                for (int j = 0; j < cols; j += 32) {
-                    read(x1, w1, j + 16);
-                    __builtin_amdgcn_sched_barrier(0);
-                    chain(x0, w0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    read(x0, w0, j + 32);
-                    __builtin_amdgcn_sched_barrier(0);
-                    chain(x1, w1);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        }
+        const float acc = settle_few(x, W, D, rg, cand, n, lds);
         for (int c = 0; c < n; ++c) {
-            float t = __shfl(acc, c * ranges, 64);
-            for (int r = 1; r < ranges; ++r) t += __shfl(acc, c * ranges + r, 64);
+            float t = __shfl(acc, c * rg.n, 64);
+            for (int r = 1; r < rg.n; ++r) t += __shfl(acc, c * rg.n + r, 64);
             const int32_t k = __builtin_amdgcn_readlane(cand, c);
             t += b[k];
             if (lane == 0) S_n[k] = t;
@@ -320,38 +503,62 @@ __device__ __forceinline__ int32_t settle(const float *__restrict__ x, const flo
 }
 
 template <bool kSettle>
-__global__ __launch_bounds__(256) void k_argmax(float *S, int32_t N, int32_t K,
-                                                int32_t *__restrict__ out,
+__global__ __launch_bounds__(256) void k_argmax(float *S, int32_t N, int32_t K, int32_t *out,
                                                 const int32_t *__restrict__ n_dev,
                                                 const float *__restrict__ X,
                                                 const float *__restrict__ W,
-                                                const float *__restrict__ b, int32_t D,
-                                                int ranges) {
+                                                const float *__restrict__ b,
+                                                const float *__restrict__ norm, int32_t D, int order) {
     const int lane = threadIdx.x & 63;
     if (n_dev) N = *n_dev;
     const int32_t n = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (n >= N) return;
     float *row = S + (size_t)n * K;
     Closest c(K);
-    if ((K & 3) == 0 && ((uintptr_t)S & 15) == 0) {
+    const bool vec = (K & 3) == 0 && ((uintptr_t)S & 15) == 0;
+    // The first scores are asked for before the bound of the row's norm, which the
+    // scoring kernel left where the identity goes, is waited for.
+    constexpr int kFirst = kSettle ? 4 : 0;
+    const float *ofs = norm ? norm : b;
+    floatx4 v[kFirst + 1], of[kFirst + 1];
+    if (vec) {
+#pragma unroll
+        for (int j = 0; j < kFirst; ++j) {
+            const int32_t k = min(4 * lane + 256 * j, K - 4);
+            v[j] = *reinterpret_cast<const floatx4 *>(row + k);
+            of[j] = *reinterpret_cast<const floatx4u *>(ofs + k);
+        }
+    }
+    const float xn = kSettle ? __int_as_float(out[n]) : 0.0f;
+    __builtin_amdgcn_sched_barrier(0);
+    const Window win(norm, b, xn, D);
+    if (vec) {
         // Four consecutive identities a lane per step (16-byte loads), still
         // scanned in increasing order within the lane.
-        typedef float f4 __attribute__((ext_vector_type(4)));
-#pragma unroll 4
-        for (int32_t k = 4 * lane; k < K; k += 256) {
-            const f4 v = *reinterpret_cast<const f4 *>(row + k);
+        auto see4 = [&](int32_t k, const floatx4 &vs, const floatx4 &os) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) c.see(v[e], k + e, K);
+            for (int e = 0; e < 4; ++e) c.see(vs[e], kSettle ? win.upper(vs[e], os[e]) : vs[e], k + e, K);
+        };
+#pragma unroll
+        for (int j = 0; j < kFirst; ++j)
+            if (4 * lane + 256 * j < K) see4(4 * lane + 256 * j, v[j], of[j]);
+#pragma unroll 4
+        for (int32_t k = 4 * lane + 256 * kFirst; k < K; k += 256) {
+            floatx4 os{};
+            if constexpr (kSettle) os = *reinterpret_cast<const floatx4u *>(win.of + k);
+            see4(k, *reinterpret_cast<const floatx4 *>(row + k), os);
         }
     } else {
-        for (int32_t k = lane; k < K; k += 64) c.see(row[k], k, K);
+        for (int32_t k = lane; k < K; k += 64)
+            c.see(row[k], kSettle ? win.upper(row[k], win.of[k]) : row[k], k, K);
     }
     c.reduce_wave();
     if constexpr (kSettle) {
         __shared__ float lds[4][kSettleLds];
-        const float floor = c.floor(b);
+        const float floor = c.floor(win);
         if (c.second >= floor)  // uniform
-            c.arg = settle(X + (size_t)n * D, W, b, row, K, D, ranges, c, floor, lds[threadIdx.x >> 6]);
+            c.arg = settle(X + (size_t)n * D, W, b, row, K, D, order, c, floor, win,
+                                  lds[threadIdx.x >> 6]);
     }
     if (lane == 0) out[n] = c.arg;
 }
@@ -361,7 +568,6 @@ typedef __attribute__((address_space(1))) const void glb_void_t;
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
 
 template <int kVm>
@@ -609,7 +815,7 @@ template <int kWN, int kWK>
 __global__ __launch_bounds__(64 * kX3Waves) void k_score_f32_bf16x3(
     const float *__restrict__ X, int32_t N, const float *__restrict__ W,
     const float *__restrict__ bias, int32_t K, int32_t D, float *__restrict__ S, int32_t splits,
-    float *__restrict__ part) {
+    float *__restrict__ part, float *__restrict__ xn) {
     static_assert(kWN * kWK == kX3Waves, "64 x 64 per wave");
     constexpr int kT = 64 * kX3Waves, kFlush = 8, kTN = 64 * kWN, kTK = 64 * kWK;
     constexpr int kRows = kTN + kTK;              // X rows, then W rows
@@ -665,7 +871,7 @@ __global__ __launch_bounds__(64 * kX3Waves) void k_score_f32_bf16x3(
     const int fr = lane & 31, fq = lane >> 5;
     floatx16 lead[2][2], rest[2][2], sum[2][2];  // [identity block][row block]
 
-    float top = 0.0f;  // largest |v|
+    float top[2] = {};  // largest |v| of this thread's rows of X, and of W
     auto store = [&](int b) {
 #pragma unroll
         for (int i = 0; i < kGroups; ++i) {
@@ -673,7 +879,7 @@ __global__ __launch_bounds__(64 * kX3Waves) void k_score_f32_bf16x3(
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const floatx2 v = {raw[i][e >> 1][2 * (e & 1)], raw[i][e >> 1][2 * (e & 1) + 1]};
-                asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(top) : "v"(v[0]), "v"(v[1]));
+                asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(top[i < kOfX ? 0 : 1]) : "v"(v[0]), "v"(v[1]));
                 // Two a conversion; the pair's halves are floats as they are.
                 auto pack = [](floatx2 f) {
                     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
@@ -755,11 +961,25 @@ __global__ __launch_bounds__(64 * kX3Waves) void k_score_f32_bf16x3(
 #pragma unroll
         for (int i = 0; i < 2; ++i) sum[j][i] += rest[j][i];
 
+    // A bound of each row's norm over this range, for Window, by the tiles of the first
+    // identities. (The norms themselves, 16 FMAs a stage here, cost 3% of the call.)
+    if (xn && k0 == 0) {
+        float v = top[0];  // of 8 in each 32 columns; a row's four lanes are neighbours
+        v = fmaxf(v, __shfl_xor(v, 1, 64));
+        v = fmaxf(v, __shfl_xor(v, 2, 64));
+#pragma unroll
+        for (int i = 0; i < kOfX; ++i) {
+            const int32_t n = n0 + ((i * kT + tid) >> 2);
+            if ((tid & 3) == 0 && n < N) xn[(size_t)sp * N + n] = sqrtf(32.0f * (float)(st1 - st0)) * v;
+        }
+    }
+
     // A split value is off by 2^-134 at most, so a result by 2^-134 D max |v|.
     uint32_t *most = reinterpret_cast<uint32_t *>(&lds[0][0][0]);
     if (tid == 0) *most = 0;
+    const float mine = fmaxf(top[0], top[1]);
     __syncthreads();
-    atomicMax(most, __float_as_uint(top));
+    atomicMax(most, __float_as_uint(mine));
     __syncthreads();
     const float all = __uint_as_float(*most);
     const float small = all * 0x1p-96f, none = all > 0x1p30f ? -1.0f : 0.0f;
@@ -843,39 +1063,71 @@ __global__ __launch_bounds__(256) void k_reduce_argmax(const float *__restrict__
                                                        const float *__restrict__ bias,
                                                        float *S, int32_t *__restrict__ out,
                                                        const float *__restrict__ X,
-                                                       const float *__restrict__ W, int32_t D,
-                                                       int ranges) {
+                                                       const float *__restrict__ W,
+                                                       const float *__restrict__ norm,
+                                                       const float *__restrict__ xn, int32_t D,
+                                                       int order) {
     const int lane = threadIdx.x & 63;
     const int32_t n = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (n >= N) return;
     const size_t plane = (size_t)N * K, row = (size_t)n * K;
     Closest c(K);
+    const float *ofs = norm ? norm : bias;
+    float xx = xn && lane < splits ? xn[(size_t)lane * N + n] : 0.0f;  // a lane a range
+    static_assert(kX3MaxSplits <= 64, "a lane a range");
+    auto sum4 = [&](int32_t k) {
+        floatx4 v = *reinterpret_cast<const floatx4 *>(S + row + k);
+        for (int q = 0; q < splits - 1; ++q)
+            v += *reinterpret_cast<const floatx4 *>(part + (size_t)q * plane + row + k);
+        return v + *reinterpret_cast<const floatx4 *>(bias + k);
+    };
+    auto sum1 = [&](int32_t k) {
+        float v = S[row + k];
+        for (int q = 0; q < splits - 1; ++q) v += part[(size_t)q * plane + row + k];
+        return v + bias[k];
+    };
+    // The first sums before the norms are waited for.
+    const int32_t first = kVec ? min(4 * lane, K - 4) : min(lane, K - 1);
+    floatx4 v4{}, of4{};
+    float v1 = 0.0f;
     if constexpr (kVec) {
-        for (int32_t k = 4 * lane; k < K; k += 256) {
-            floatx4 v = *reinterpret_cast<const floatx4 *>(S + row + k);
-            for (int q = 0; q < splits - 1; ++q)
-                v += *reinterpret_cast<const floatx4 *>(part + (size_t)q * plane + row + k);
-            v += *reinterpret_cast<const floatx4 *>(bias + k);
-            *reinterpret_cast<floatx4 *>(S + row + k) = v;
+        v4 = sum4(first);
+        of4 = *reinterpret_cast<const floatx4u *>(ofs + first);
+    } else {
+        v1 = sum1(first);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    xx *= xx;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) c.see(v[e], k + e, K);  // ascending: the first is kept
+    for (int off = 32; off >= 1; off >>= 1) xx += __shfl_xor(xx, off, 64);
+    const Window win(norm, bias, sqrtf(xx), D);
+    if constexpr (kVec) {
+        for (int32_t k = 4 * lane; k < K;) {
+            *reinterpret_cast<floatx4 *>(S + row + k) = v4;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)  // ascending: the first is kept
+                c.see(v4[e], win.upper(v4[e], of4[e]), k + e, K);
+            k += 256;
+            if (k >= K) break;
+            v4 = sum4(k);
+            of4 = *reinterpret_cast<const floatx4u *>(ofs + k);
         }
     } else {
-        for (int32_t k = lane; k < K; k += 64) {
-            float v = S[row + k];
-            for (int q = 0; q < splits - 1; ++q) v += part[(size_t)q * plane + row + k];
-            v += bias[k];
-            S[row + k] = v;
-            c.see(v, k, K);
+        for (int32_t k = lane; k < K;) {
+            S[row + k] = v1;
+            c.see(v1, win.upper(v1, ofs[k]), k, K);
+            k += 64;
+            if (k >= K) break;
+            v1 = sum1(k);
         }
     }
     if (!out) return;
     c.reduce_wave();
     __shared__ float lds[4][kSettleLds];
-    const float floor = ranges ? c.floor(bias) : NAN;
+    const float floor = xn ? c.floor(win) : NAN;
     if (c.second >= floor)  // uniform
-        c.arg = settle(X + (size_t)n * D, W, bias, S + row, K, D, ranges, c, floor,
-                       lds[threadIdx.x >> 6]);
+        c.arg = settle(X + (size_t)n * D, W, bias, S + row, K, D, order, c, floor, win,
+                              lds[threadIdx.x >> 6]);
     if (lane == 0) out[n] = c.arg;
 }
 
@@ -897,7 +1149,7 @@ template <int kNB, bool kTail>
 __global__ __launch_bounds__(512) void k_score_f32_rows(
     const float *__restrict__ X, int32_t N, const float *__restrict__ W,
     const float *__restrict__ bias, int32_t K, int32_t D, float *__restrict__ S, int32_t splits,
-    float *__restrict__ part, const int32_t *__restrict__ n_dev) {
+    float *__restrict__ part, const int32_t *__restrict__ n_dev, float *__restrict__ xn) {
     constexpr int kWB = 2, kU = kNB == 4 ? 2 : 4;
     __shared__ floatx4 red[kRowsWaves][kWB][kNB][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -905,6 +1157,23 @@ __global__ __launch_bounds__(512) void k_score_f32_rows(
     const int32_t k0 = blockIdx.x * 16 * kWB, n0 = blockIdx.y * 16 * kNB, sp = blockIdx.z;
     if (n_dev) N = *n_dev;
     if (n0 >= N) return;  // uniform
+    if (xn && k0 >= K) {  // a workgroup behind the identities': the rows' norms, for Window
+        const int32_t lo = 32 * (int32_t)((int64_t)((D + 31) >> 5) * sp / splits);
+        const int32_t hi = min(32 * (int32_t)((int64_t)((D + 31) >> 5) * (sp + 1) / splits), D);
+        for (int j = wave; j < 16 * kNB && n0 + j < N; j += kRowsWaves) {
+            const float *x = X + (size_t)(n0 + j) * D;
+            float v = 0.0f;
+#pragma unroll 4
+            for (int32_t d = lo + 4 * lane; d < hi; d += 256) {
+                const floatx4 t = *reinterpret_cast<const floatx4 *>(x + d);
+                v += t.x * t.x + t.y * t.y + (t.z * t.z + t.w * t.w);
+            }
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+            if (lane == 0) xn[(size_t)sp * N + n0 + j] = sqrtf(v);
+        }
+        return;
+    }
     const float *wp[kWB], *xp[kNB];
 #pragma unroll
     for (int i = 0; i < kWB; ++i) wp[i] = W + (size_t)min(k0 + 16 * i + r, K - 1) * D + 8 * q;
@@ -977,51 +1246,81 @@ __global__ __launch_bounds__(512) void k_score_f32_rows(
 
 // One workgroup per row, for few rows: as k_reduce_argmax (splits > 1: the
 // partials summed in split order, the bias added, S written) or k_argmax
-// (splits == 1: S read), with 1024 lanes on a row and every partial of an
+// (splits == 1: S read), with 512 lanes on a row and every partial of an
 // identity in flight at once. A wave per row (k_argmax, k_reduce_argmax) walks
 // the row in dependent steps of memory latency, which pays only once there are
 // rows enough to fill the GPU with waves.
-__global__ __launch_bounds__(1024) void k_row_argmax(const float *__restrict__ part, int32_t splits,
+__global__ __launch_bounds__(512) void k_row_argmax(const float *__restrict__ part, int32_t splits,
                                                      int32_t N, int32_t K,
-                                                     const float *__restrict__ bias,
-                                                     float *S,
-                                                     int32_t *__restrict__ out,
+                                                     const float *__restrict__ bias, float *S,
+                                                     int32_t *out,
                                                      const int32_t *__restrict__ n_dev,
                                                      const float *__restrict__ X,
-                                                     const float *__restrict__ W, int32_t D,
-                                                     int ranges) {
-    __shared__ float sv[16], ss[16];
-    __shared__ bool sn[16];
-    __shared__ int32_t sa[16];
+                                                     const float *__restrict__ W,
+                                                     const float *__restrict__ norm,
+                                                     const float *xn, int32_t D, int order) {
+    __shared__ float sv[8], sm[8], st[8], ss[8];
+    __shared__ bool sn[8];
+    __shared__ int32_t sa[8];
     __shared__ float lds[kSettleLds];
     const int32_t n = blockIdx.x;
-    if (n_dev && n >= *n_dev) return;  // uniform
+    if (n_dev) N = *n_dev;
+    if (n >= N) return;  // uniform
     const size_t plane = (size_t)N * K, row = (size_t)n * K;
     Closest c(K);
-    for (int32_t k = threadIdx.x; k < K; k += blockDim.x) {
-        float v;
-        if (splits > 1) {
-            float p[kRowsMaxSplits];
+    constexpr int kTwo = 2;
+    float p[kTwo][kRowsMaxSplits], bk[kTwo], of[kTwo];
+    const float *ofs = norm ? norm : bias;
+    auto load = [&](int32_t k0) {
 #pragma unroll
-            for (int q = 0; q < kRowsMaxSplits; ++q)
-                p[q] = part[(size_t)min(q, splits - 1) * plane + row + k];
-            const float bk = bias[k];
-            v = p[0];
+        for (int u = 0; u < kTwo; ++u) {
+            const int32_t k = min(k0 + u * (int32_t)blockDim.x, K - 1);
+            of[u] = ofs[k];
+            bk[u] = bias[k];
+            if (splits == 1) {
+                p[u][0] = S[row + k];
+            } else {
 #pragma unroll
-            for (int q = 1; q < kRowsMaxSplits; ++q)
-                if (q < splits) v += p[q];  // uniform
-            v += bk;
-            S[row + k] = v;
-        } else {
-            v = S[row + k];
+                for (int q = 0; q < kRowsMaxSplits; ++q)
+                    p[u][q] = part[(size_t)min(q, splits - 1) * plane + row + k];
+            }
         }
-        c.see(v, k, K);
+    };
+    load(threadIdx.x);
+    float xx = 0.0f;
+    if (xn) {  // one split: where the identity goes
+        float t[kRowsMaxSplits];
+#pragma unroll
+        for (int q = 0; q < kRowsMaxSplits; ++q) t[q] = xn[(size_t)min(q, splits - 1) * N + n];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < kRowsMaxSplits; ++q) xx += q < splits ? t[q] * t[q] : 0.0f;
+    }
+    const Window win(norm, bias, sqrtf(xx), D);
+    for (int32_t k0 = threadIdx.x; k0 < K;) {
+#pragma unroll
+        for (int u = 0; u < kTwo; ++u) {
+            const int32_t k = k0 + u * (int32_t)blockDim.x;
+            float v = p[u][0];
+            if (splits > 1) {
+#pragma unroll
+                for (int q = 1; q < kRowsMaxSplits; ++q)
+                    if (q < splits) v += p[u][q];  // uniform
+                v += bk[u];
+                if (k < K) S[row + k] = v;
+            }
+            if (k < K) c.see(v, win.upper(v, of[u]), k, K);
+        }
+        k0 += kTwo * (int32_t)blockDim.x;
+        if (k0 < K) load(k0);
     }
     if (!out) return;
     c.reduce_wave();
     const int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) {
         sv[wave] = c.best;
+        sm[wave] = c.most;
+        st[wave] = c.top;
         ss[wave] = c.second;
         sn[wave] = c.nan;
         sa[wave] = c.arg;
@@ -1029,16 +1328,36 @@ __global__ __launch_bounds__(1024) void k_row_argmax(const float *__restrict__ p
     __syncthreads();
     if (wave != 0) return;
     for (int w = 1; w < (int)(blockDim.x >> 6); ++w) {
-        c.take(sv[w], sa[w], ss[w]);
+        c.take(sv[w], sm[w], sa[w], st[w], ss[w]);
         c.nan |= sn[w];
     }
-    const float floor = ranges ? c.floor(bias) : NAN;
+    const float floor = xn ? c.floor(win) : NAN;
     if (c.second >= floor)  // uniform
-        c.arg = settle(X + (size_t)n * D, W, bias, S + row, K, D, ranges, c, floor, lds);
+        c.arg = settle(X + (size_t)n * D, W, bias, S + row, K, D, order, c, floor, win, lds);
     if (threadIdx.x == 0) out[n] = c.arg;
 }
 
+// Euclidean norms of the rows of W, one workgroup a row, summed in FP64 (weights near
+// FP32's ends have a norm as well).
+__global__ __launch_bounds__(256) void k_weight_norms(const float *__restrict__ W, int32_t D,
+                                                      float *__restrict__ norm) {
+    __shared__ double red[4];
+    const float *w = W + (size_t)blockIdx.x * D;
+    double acc = 0.0;
+    for (int32_t d = threadIdx.x; d < D; d += 256) acc += (double)w[d] * (double)w[d];
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) norm[blockIdx.x] = (float)sqrt(red[0] + red[1] + red[2] + red[3]);
+}
+
 }  // namespace
+
+hipError_t launch_row_norms(const float *W, int32_t K, int32_t D, float *norm, hipStream_t s) {
+    hipLaunchKernelGGL(k_weight_norms, dim3(K), dim3(256), 0, s, W, D, norm);
+    return hipGetLastError();
+}
 
 // Products of few rows (at most 32) or of few 64 x 32 blocks run
 // k_score_f32_rows: below the line a call's time is W's one pass, above it the
@@ -1065,7 +1384,8 @@ static int32_t x3_splits(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_
     int32_t best = 1;
     double least = 0.0;
     for (int32_t sp = 1; sp <= std::min(kX3MaxSplits, stages); ++sp) {
-        if ((size_t)(sp - 1) * (size_t)N * (size_t)K > part_elems) break;  // S holds one
+        // S holds one range's sums; a bound of each row's norm for each range.
+        if (sp > 1 && (size_t)(sp - 1) * (size_t)N * (size_t)K + (size_t)sp * (size_t)N > part_elems) break;
         const double us = 2.8 * (double)((t * sp + num_cus - 1) / num_cus) * ((stages + sp - 1) / sp) +
                           (sp > 1 ? 4.0 + 8.0 * sp * (double)N * (double)K / 4e6 : 0.0);
         if (sp == 1 || us < least) {
@@ -1083,13 +1403,14 @@ int32_t score_f32_splits(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_
         const int64_t groups = (int64_t)((K + 31) / 32) * ((N + nb - 1) / nb);
         int64_t sp = std::min<int64_t>({(2 * (int64_t)num_cus + groups - 1) / groups, kRowsMaxSplits,
                                         std::max(1, (D + 31) / 32 / (4 * kRowsWaves)),
-                                        (int64_t)(part_elems / ((size_t)N * (size_t)K))});
+                                        (int64_t)(part_elems / ((size_t)N * ((size_t)K + 1)))});
         return (int32_t)std::max<int64_t>(sp, 1);
     }
     return x3_takes(D) ? x3_splits(N, K, D, num_cus, part_elems) : 1;
 }
 
-int32_t score_f32_ranges(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_t part_elems) {
+int32_t score_f32_order(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_t part_elems) {
+    if (D % 32 != 0) return 0;
     const int64_t tiles = (int64_t)((N + 127) / 128) * ((K + 127) / 128);
     int32_t best = 1;
     for (int32_t sp = 2; sp <= 4; sp *= 2) {
@@ -1104,21 +1425,23 @@ int32_t score_f32_ranges(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_
 // The partials' sum in split order, the bias and the argmax (argmax may be null).
 static hipError_t launch_reduce(const float *part, int32_t splits, int32_t N, int32_t K,
                                 const float *b, float *S, int32_t *argmax, hipStream_t s,
-                                const float *X, const float *W, int32_t D, int ranges) {
+                                const float *X, const float *W, const float *norm,
+                                const float *xn, int32_t D, int order) {
     const bool v4 = K % 4 == 0 && ((uintptr_t)S % 16 == 0) && ((uintptr_t)b % 16 == 0) &&
                     ((uintptr_t)part % 16 == 0);
     if (v4)
         hipLaunchKernelGGL(k_reduce_argmax<true>, dim3((N + 3) / 4), dim3(256), 0, s, part, splits,
-                           N, K, b, S, argmax, X, W, D, ranges);
+                           N, K, b, S, argmax, X, W, norm, xn, D, order);
     else
         hipLaunchKernelGGL(k_reduce_argmax<false>, dim3((N + 3) / 4), dim3(256), 0, s, part, splits,
-                           N, K, b, S, argmax, X, W, D, ranges);
+                           N, K, b, S, argmax, X, W, norm, xn, D, order);
     return hipGetLastError();
 }
 
 hipError_t launch_score_f32(const float *X, int32_t N, const float *W, const float *b, int32_t K,
                             int32_t D, float *S, int32_t *argmax, hipStream_t s, int32_t splits,
-                            float *part, const int32_t *n_dev, bool one_order, int32_t ranges) {
+                            float *part, const int32_t *n_dev, bool one_order, int32_t order,
+                            const float *norm) {
     if (N <= 0 || K <= 0) return hipSuccess;
     const bool aligned = ((uintptr_t)X % 16 == 0) && ((uintptr_t)W % 16 == 0);
     int cus = 256;
@@ -1129,40 +1452,50 @@ hipError_t launch_score_f32(const float *X, int32_t N, const float *W, const flo
         cus = std::max(cus, 1);
     }
     const bool x3 = !n_dev && x3_takes(D);
+    // Where the rows' norms (or bounds of them) go: behind the partial sums, or (one range) where
+    // the identities go after them.
+    const auto norms_at = [&](float *behind) {
+        return !argmax || !order ? nullptr : splits > 1 ? behind : reinterpret_cast<float *>(argmax);
+    };
     if (!one_order && aligned && splits >= 1 && few_rows(N, K, D, cus, x3) && (splits == 1 || part)) {
         const int32_t nb = rows_blocks(N);
-        const dim3 g((K + 31) / 32, (N + 16 * nb - 1) / (16 * nb), splits);
+        float *xn = norms_at(part + (size_t)splits * N * K);
+        const dim3 g((K + 31) / 32 + (xn ? 1 : 0), (N + 16 * nb - 1) / (16 * nb), splits);
         auto go = [&](auto kern) {
             hipLaunchKernelGGL(kern, g, dim3(64 * kRowsWaves), 0, s, X, N, W, b, K, D, S, splits,
-                               part, n_dev);
+                               part, n_dev, xn);
         };
         const bool tail = D % 32 != 0;
         if (nb == 1) tail ? go(k_score_f32_rows<1, true>) : go(k_score_f32_rows<1, false>);
         else if (nb == 2) tail ? go(k_score_f32_rows<2, true>) : go(k_score_f32_rows<2, false>);
         else tail ? go(k_score_f32_rows<4, true>) : go(k_score_f32_rows<4, false>);
-        if (splits > 1 || argmax)
-            hipLaunchKernelGGL(k_row_argmax, dim3(N), dim3(K > 512 ? 1024 : 256), 0, s, part, splits, N, K, b, S,
-                               argmax, n_dev, X, W, D, D % 32 == 0 ? ranges : 0);
+        auto best = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(N), dim3(K > 256 ? 512 : 256), 0, s, part, splits, N, K, b, S,
+                               argmax, n_dev, X, W, norm, xn, D, order);
+        };
+        if (splits > 1 || argmax) best(k_row_argmax);
         return hipGetLastError();
     }
     if (!one_order && aligned && x3 && splits >= 1 && (splits == 1 || part)) {
         // The shape that goes with this many splits.
+        float *xn = norms_at(part + (size_t)(splits - 1) * N * K);
         const auto tiles = [&](int tn, int tk) { return ((N + tn - 1) / tn) * ((K + tk - 1) / tk); };
         const auto rounds = [&](int t) { return ((int64_t)t * splits + cus - 1) / cus; };
         const int tall = tiles(256, 128), wide = tiles(128, 256);
         if (rounds(tall) <= rounds(wide))
             hipLaunchKernelGGL((k_score_f32_bf16x3<4, 2>), dim3(tall, splits), dim3(64 * kX3Waves),
-                               0, s, X, N, W, b, K, D, S, splits, part);
+                               0, s, X, N, W, b, K, D, S, splits, part, xn);
         else
             hipLaunchKernelGGL((k_score_f32_bf16x3<2, 4>), dim3(wide, splits), dim3(64 * kX3Waves),
-                               0, s, X, N, W, b, K, D, S, splits, part);
+                               0, s, X, N, W, b, K, D, S, splits, part, xn);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        if (splits > 1) return launch_reduce(part, splits, N, K, b, S, argmax, s, X, W, D, ranges);
+        if (splits > 1)
+            return launch_reduce(part, splits, N, K, b, S, argmax, s, X, W, norm, xn, D, order);
         if (!argmax) return hipSuccess;
-        if (ranges == 0) return launch_argmax(S, N, K, argmax, s);
+        if (!xn) return launch_argmax(S, N, K, argmax, s);
         hipLaunchKernelGGL(k_argmax<true>, dim3((N + 3) / 4), dim3(256), 0, s, S, N, K, argmax, n_dev,
-                           X, W, b, D, ranges);
+                           X, W, b, norm, D, order);
         return hipGetLastError();
     }
     if (aligned && D % 32 == 0 && splits >= 1) {
@@ -1210,7 +1543,7 @@ hipError_t launch_argmax(const float *S, int32_t N, int32_t K, int32_t *argmax, 
                          const int32_t *n_dev) {
     if (N <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_argmax<false>, dim3((N + 3) / 4), dim3(256), 0, s, const_cast<float *>(S), N,
-                       K, argmax, n_dev, nullptr, nullptr, nullptr, 0, 0);
+                       K, argmax, n_dev, nullptr, nullptr, nullptr, nullptr, 0, 0);
     return hipGetLastError();
 }
 
