@@ -487,8 +487,8 @@ int32_t lbpf_weights_count(const lbpf_weights *weights);
  * Identities: where a row's best scores lie within what rounding may turn round
  * (judged by the norms of the row and of the weights), those scores are summed
  * again in one order, that of lbpf_score's FP32 matrix-core tiles: 1, 2 or 4
- * ranges of D, by N and K (pipelines: one), where D is a multiple of 32.
- * They replace the others in scores_opt when argmax_opt is
+ * ranges of D, by N and K (pipelines: one), or quarters where D is not a
+ * multiple of 32. They replace the others in scores_opt when argmax_opt is
  * given, and the first largest names the identity, which so does not depend on
  * the kernel that made the scores (with another number of ranges one of two
  * scores that close may win over the other). A row with many scores that close

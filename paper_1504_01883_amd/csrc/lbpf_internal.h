@@ -158,7 +158,8 @@ hipError_t launch_track(const int32_t *prev, const int32_t *ps, int32_t P, const
 int32_t score_f32_splits(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_t part_elems);
 // The order in which close scores are summed again to name an identity: 1, 2 or 4
 // ranges of D, as many as let 128 x 128 tiles fill the GPU, as far as part_elems
-// holds their sums; 0: none (D not a multiple of 32).
+// holds their sums; -1: D a multiple of 4 but not of 32, in k_score_f32's quarters;
+// 0: none (k_score_f32 serves it).
 int32_t score_f32_order(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_t part_elems);
 // S is always written; argmax (may be null) gets each row's best identity.
 // one_order: FP32 MFMA tiles whatever the sizes (the trainer's Gram products,

@@ -150,8 +150,9 @@ __global__ __launch_bounds__(512) void k_score_f32(const float *__restrict__ X, 
 // Where a row's best scores lie within what two orders of summation differ by, those
 // scores are summed again in one fixed order, written over the others and compared:
 // the order of the FP32 MFMA tiles (per range of D, each eight columns as 0 4 1 5 2 6
-// 3 7, an FMA each; the ranges' sums in order; the bias). So the named identity does
-// not follow the kernel that made the scores.
+// 3 7, an FMA each; the ranges' sums in order; the bias), or, where D is not a
+// multiple of 32, that of k_score_f32. So the named identity does not follow the
+// kernel that made the scores.
 //
 // Within: each score may be off by 2^-23 sqrt(D) |x| |w|, 4.8 standard deviations of
 // D roundings of sums as large as |x| |w| (no partial sum is larger), and by 2^-22 of
@@ -230,23 +231,33 @@ constexpr int kSettlePieces = 2;     // of 256 columns a step
 constexpr int kSettleStride = 532;   // floats of LDS a row, its 1, 2 or 4 ranges 4 apart
 constexpr int kSettleLds = (1 + kSettleRows) * kSettleStride + 16;
 
-// The fixed order's ranges: 1, 2 or 4 of equal length, D a multiple of 32 times that.
+// The fixed order's ranges: 1, 2 or 4 of equal length, D a multiple of 32 times that;
+// or (order < 0) k_score_f32's four quarters, the last ones shorter or empty.
 struct Ranges {
     int n;
     int32_t len;
-    __device__ Ranges(int order, int32_t D) : n(order), len(D / order) {}
-    __device__ __forceinline__ int32_t own(int, int32_t) const { return len; }
+    __device__ Ranges(int order, int32_t D)
+        : n(order < 0 ? 4 : order), len(order < 0 ? ((D + 127) / 128) * 32 : D / order) {}
+    __device__ __forceinline__ int32_t own(int r, int32_t D) const { return min(len, max(D - r * len, 0)); }
 };
 
 // 16 columns onto a sum, in the fixed order.
+template <bool kQuarters>
 __device__ __forceinline__ float chain16(const floatx4 (&x)[4], const floatx4 (&w)[4], float acc) {
+    if constexpr (kQuarters) {
 #pragma unroll
-    for (int h = 0; h < 4; h += 2)
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            acc = __builtin_fmaf(x[h][e], w[h][e], acc);
-            acc = __builtin_fmaf(x[h + 1][e], w[h + 1][e], acc);
-        }
+            for (int h = 0; h < 4; ++h) acc = __builtin_fmaf(x[h][e], w[h][e], acc);
+    } else {
+#pragma unroll
+        for (int h = 0; h < 4; h += 2)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                acc = __builtin_fmaf(x[h][e], w[h][e], acc);
+                acc = __builtin_fmaf(x[h + 1][e], w[h + 1][e], acc);
+            }
+    }
     return acc;
 }
 
@@ -255,6 +266,7 @@ __device__ __forceinline__ float chain16(const floatx4 (&x)[4], const floatx4 (&
 // FMAs in one lane a sum, its operands staged in LDS by all lanes (lane l copies
 // columns 4 (l % per) .. + 3 of a piece of range l / per) and read 16 columns ahead:
 // 25 us over 7552 columns in one range, 7 in four.
+template <bool kQuarters>
 __device__ __forceinline__ float settle_few(const float *__restrict__ x, const float *__restrict__ W,
                                             int32_t D, const Ranges &rg, int32_t cand, int n, float *lds) {
     const int lane = threadIdx.x & 63;
@@ -304,11 +316,11 @@ __device__ __forceinline__ float settle_few(const float *__restrict__ x, const f
             for (int j = 0; j < cols; j += 32) {
                 read(x1, w1, j + 16);
                 __builtin_amdgcn_sched_barrier(0);
-                acc = chain16(x0, w0, acc);
+                acc = chain16<kQuarters>(x0, w0, acc);
                 __builtin_amdgcn_sched_barrier(0);
                 read(x0, w0, j + 32);
                 __builtin_amdgcn_sched_barrier(0);
-                acc = chain16(x1, w1, acc);
+                acc = chain16<kQuarters>(x1, w1, acc);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -339,6 +351,7 @@ __device__ __forceinline__ float scan_wave(float v) {
 // sum. Where the terms have either sign that is 50 times less than Window's bound by
 // the norms, so that few of the rows the norms alone would have settled (1 in 100 of
 // random weights) are. About 6 us, where settle_few takes 15 to 25.
+template <bool kQuarters>
 __device__ __forceinline__ floatx2 spread(const float *__restrict__ x, const float *__restrict__ u,
                                           const float *__restrict__ w, int32_t D, const Ranges &rg) {
     constexpr int kFly = 4;  // 256 columns each, on their way at a time
@@ -413,6 +426,7 @@ __device__ __forceinline__ float norm_of(const float *__restrict__ x, int32_t D)
 // 6 within the second) 132 / 17, 135 / 112, 1847 / 1314; in every row two copies within
 // rounding 135 / 46, 137 / 174, 1845 / 1770; in every row 64 copies 138 / 473, 140 /
 // 1211, 1846 / 12305.
+template <bool kQuarters>
 __device__ __forceinline__ int32_t settle(const float *__restrict__ x, const float *__restrict__ W,
                                           const float *__restrict__ b, float *S_n, int32_t K,
                                           int32_t D, int order, const Closest &row, float row_floor,
@@ -463,7 +477,7 @@ __device__ __forceinline__ int32_t settle(const float *__restrict__ x, const flo
             for (; m && !other; m &= m - 1) {
                 const int32_t k = k0 + __builtin_ctzll(m);
                 const float v = S_n[k];
-                const floatx2 off = spread(x, W + (size_t)row_arg * D, W + (size_t)k * D, D, rg);
+                const floatx2 off = spread<kQuarters>(x, W + (size_t)row_arg * D, W + (size_t)k * D, D, rg);
                 other = v + 0x1p-22f * fabsf(v) + off.y >= row_best - 0x1p-22f * fabsf(row_best) - off.x;
             }
         }
@@ -487,7 +501,7 @@ __device__ __forceinline__ int32_t settle(const float *__restrict__ x, const flo
             m &= m - 1;
         }
         if (n == 0) return arg;
-        const float acc = settle_few(x, W, D, rg, cand, n, lds);
+        const float acc = settle_few<kQuarters>(x, W, D, rg, cand, n, lds);
         for (int c = 0; c < n; ++c) {
             float t = __shfl(acc, c * rg.n, 64);
             for (int r = 1; r < rg.n; ++r) t += __shfl(acc, c * rg.n + r, 64);
@@ -557,7 +571,7 @@ __global__ __launch_bounds__(256) void k_argmax(float *S, int32_t N, int32_t K, 
         __shared__ float lds[4][kSettleLds];
         const float floor = c.floor(win);
         if (c.second >= floor)  // uniform
-            c.arg = settle(X + (size_t)n * D, W, b, row, K, D, order, c, floor, win,
+            c.arg = settle<false>(X + (size_t)n * D, W, b, row, K, D, order, c, floor, win,
                                   lds[threadIdx.x >> 6]);
     }
     if (lane == 0) out[n] = c.arg;
@@ -1126,7 +1140,7 @@ __global__ __launch_bounds__(256) void k_reduce_argmax(const float *__restrict__
     __shared__ float lds[4][kSettleLds];
     const float floor = xn ? c.floor(win) : NAN;
     if (c.second >= floor)  // uniform
-        c.arg = settle(X + (size_t)n * D, W, bias, S + row, K, D, order, c, floor, win,
+        c.arg = settle<false>(X + (size_t)n * D, W, bias, S + row, K, D, order, c, floor, win,
                               lds[threadIdx.x >> 6]);
     if (lane == 0) out[n] = c.arg;
 }
@@ -1250,6 +1264,7 @@ __global__ __launch_bounds__(512) void k_score_f32_rows(
 // identity in flight at once. A wave per row (k_argmax, k_reduce_argmax) walks
 // the row in dependent steps of memory latency, which pays only once there are
 // rows enough to fill the GPU with waves.
+template <bool kQuarters>
 __global__ __launch_bounds__(512) void k_row_argmax(const float *__restrict__ part, int32_t splits,
                                                      int32_t N, int32_t K,
                                                      const float *__restrict__ bias, float *S,
@@ -1333,7 +1348,7 @@ __global__ __launch_bounds__(512) void k_row_argmax(const float *__restrict__ pa
     }
     const float floor = xn ? c.floor(win) : NAN;
     if (c.second >= floor)  // uniform
-        c.arg = settle(X + (size_t)n * D, W, bias, S + row, K, D, order, c, floor, win, lds);
+        c.arg = settle<kQuarters>(X + (size_t)n * D, W, bias, S + row, K, D, order, c, floor, win, lds);
     if (threadIdx.x == 0) out[n] = c.arg;
 }
 
@@ -1410,7 +1425,7 @@ int32_t score_f32_splits(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_
 }
 
 int32_t score_f32_order(int32_t N, int32_t K, int32_t D, int32_t num_cus, size_t part_elems) {
-    if (D % 32 != 0) return 0;
+    if (D % 32 != 0) return D % 4 == 0 ? -1 : 0;
     const int64_t tiles = (int64_t)((N + 127) / 128) * ((K + 127) / 128);
     int32_t best = 1;
     for (int32_t sp = 2; sp <= 4; sp *= 2) {
@@ -1473,7 +1488,7 @@ hipError_t launch_score_f32(const float *X, int32_t N, const float *W, const flo
             hipLaunchKernelGGL(kern, dim3(N), dim3(K > 256 ? 512 : 256), 0, s, part, splits, N, K, b, S,
                                argmax, n_dev, X, W, norm, xn, D, order);
         };
-        if (splits > 1 || argmax) best(k_row_argmax);
+        if (splits > 1 || argmax) order < 0 ? best(k_row_argmax<true>) : best(k_row_argmax<false>);
         return hipGetLastError();
     }
     if (!one_order && aligned && x3 && splits >= 1 && (splits == 1 || part)) {

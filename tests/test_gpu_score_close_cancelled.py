@@ -2,7 +2,9 @@
 another, of mean zero and without bias, so that the scores are small against the sums
 they come from and their order is decided by rounding alone. The identity is the one
 that FP32 sums in the fixed order give (see test_gpu_score_close), for every kernel
-that makes scores. Exact: the sums are emulated to the last bit."""
+that makes scores; where D is not a multiple of 32 in four quarters of ceil(D / 128)
+32 columns, each sixteen as 0 4 8 12 1 5 9 13 .. . Exact: the sums are emulated to the
+last bit."""
 import numpy as np
 import pytest
 import torch
@@ -14,14 +16,20 @@ pytestmark = pytest.mark.gpu
 
 
 def fixed_order(X, W, b, ranges):
-    """An FMA is a product and a sum in 64 bits, rounded once."""
-    length = X.shape[1] // ranges
+    """ranges: 1, 2, 4, or 0 for quarters. An FMA is a product and a sum in 64 bits,
+    rounded once."""
+    D = X.shape[1]
+    if ranges:
+        length, step, inner = D // ranges, 8, [0, 4, 1, 5, 2, 6, 3, 7]
+    else:
+        length, step, inner = (D + 127) // 128 * 32, 16, [4 * k + c for c in range(4) for k in range(4)]
     total = None
-    for lo in range(0, length * ranges, length):
+    for lo in range(0, length * (ranges or 4), length):
         acc = torch.zeros(len(X), len(W), device="cuda")
-        for d0 in range(lo, lo + length, 8):
-            for d in (d0 + c for c in (0, 4, 1, 5, 2, 6, 3, 7)):
-                acc = (X[:, d, None].double() * W[None, :, d].double() + acc.double()).float()
+        for d0 in range(min(lo, D), min(lo + length, D), step):
+            for d in (d0 + c for c in inner):
+                if d < D:
+                    acc = (X[:, d, None].double() * W[None, :, d].double() + acc.double()).float()
         total = acc if total is None else total + acc
     return total + b
 
@@ -50,6 +58,24 @@ def test_copies_only(N, K, ranges):
     assert torch.equal(A[rows].long(), want.argmax(1))
     assert torch.equal(A2[rows], A[rows])
     assert torch.equal(S[rows].gather(1, A[rows].long()[:, None]), want.max(1, keepdim=True).values)
+    wts.close()
+    c.close()
+
+
+@pytest.mark.parametrize("grid,modality,N,K", [((6, 6), lbpf.MOD_BOTH, 20, 300), ((6, 6), lbpf.MOD_BOTH, 300, 60),
+                                               ((2, 2), lbpf.MOD_GREY, 33, 40), ((6, 6), lbpf.MOD_BOTH, 2048, 600)])
+def test_quarters(grid, modality, N, K):
+    """D not a multiple of 32: few rows (D = 4248 and 236), and the kernel whose order
+    that is."""
+    require_gpu()
+    c = lbpf.Context(grid=grid, modality=modality)
+    X, W, b = near_copies(N + K, N, K, c.dim)
+    wts = c.weights(W, b)
+    _, A = c.score(X, wts)
+    rows = slice(0, N, max(1, N // 400))
+    want = fixed_order(X[rows], W, b, 0)
+    torch.cuda.synchronize()
+    assert torch.equal(A[rows].long(), want.argmax(1))
     wts.close()
     c.close()
 
