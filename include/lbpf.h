@@ -492,7 +492,7 @@ int32_t lbpf_weights_count(const lbpf_weights *weights);
  * given, and the first largest names the identity, which so does not depend on
  * the kernel that made the scores (with another number of ranges one of two
  * scores that close may win over the other). A row with many scores that close
- * takes longer: about 25 us for each three at D = 7552.
+ * takes longer: about 60 us for each 64 at D = 7552.
  * In the reduced precisions the operands are converted as documented for
  * lbpf_precision and the products accumulated in FP32, in an order that N and K
  * choose. Errors: LBPF_E_INVALID, LBPF_E_HIP. */

@@ -329,6 +329,62 @@ __device__ __forceinline__ float settle_few(const float *__restrict__ x, const f
     return acc;
 }
 
+// As settle_few for up to 64 / ranges scores at a time (lane c * ranges + r: candidate
+// c's identity), 16 columns a step, two steps on their way: 60 us a turn over 7552
+// columns in one range, 15 in four, mostly the latency of LDS.
+template <bool kQuarters>
+__device__ __forceinline__ float settle_many(const float *__restrict__ x, const float *__restrict__ W,
+                                             int32_t D, const Ranges &rg, int32_t cand, float *lds) {
+    constexpr int kStride = 20;  // floats of LDS a sum's columns: reads in all banks
+    static_assert((64 + 4) * kStride <= kSettleLds, "a wave's LDS");
+    const int lane = threadIdx.x & 63;
+    // Lane l copies columns 4 (l % 4) .. + 3 for the sums of lanes l / 4 + 16 i, and x's
+    // for range l / 4. 16 is a multiple of the ranges: all of one range.
+    const int q = lane >> 2, r = q % rg.n, at = 4 * (lane & 3);
+    const int32_t from = r * rg.len, own = rg.own(r, D);
+    const float *src[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) src[i] = W + (size_t)__shfl(cand, q + 16 * i, 64) * D;
+    floatx4 w0[4], w1[4], x0, x1;
+    auto load = [&](int32_t j, floatx4(&w)[4], floatx4 &xs) {
+        const int32_t d = min(from + j + at, D - 4);
+        const bool in = j + at < own;  // else nothing to add
+        xs = *reinterpret_cast<const floatx4 *>(x + d);
+        if (!in) xs = floatx4{};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            w[i] = *reinterpret_cast<const floatx4 *>(src[i] + d);
+            if (!in) w[i] = floatx4{};
+        }
+    };
+    float acc = 0.0f;
+    const float *pw = lds + lane * kStride, *px = lds + (64 + lane % rg.n) * kStride;
+    auto step = [&](int32_t j, floatx4(&w)[4], floatx4 &xs) {
+        float *to = lds + q * kStride + at;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *reinterpret_cast<floatx4 *>(to + 16 * i * kStride) = w[i];
+        if (q < rg.n) *reinterpret_cast<floatx4 *>(to + 64 * kStride) = xs;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        load(j + 32, w, xs);
+        floatx4 a[4], b[4];
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            a[h] = *reinterpret_cast<const floatx4 *>(px + 4 * h);
+            b[h] = *reinterpret_cast<const floatx4 *>(pw + 4 * h);
+        }
+        acc = chain16<kQuarters>(a, b, acc);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    };
+    load(0, w0, x0);
+    load(16, w1, x1);
+#pragma unroll 1
+    for (int32_t j = 0; j < rg.len; j += 32) {
+        step(j, w0, x0);
+        step(j + 16, w1, x1);
+    }
+    return acc;
+}
+
 // Sum over a wave's lanes up to this one.
 __device__ __forceinline__ float scan_wave(float v) {
     auto add = [&](auto ctrl, auto rows) {
@@ -424,8 +480,8 @@ __device__ __forceinline__ float norm_of(const float *__restrict__ x, int32_t D)
 // rows uniform: no row close 5 x 1024 131 / 18, 4096 x 256 135 / 106, 16384 x 1024 1847
 // / 1295; as they come (26 of 4096 rows and 212 of 16384 within the first window, 0 and
 // 6 within the second) 132 / 17, 135 / 112, 1847 / 1314; in every row two copies within
-// rounding 135 / 46, 137 / 174, 1845 / 1770; in every row 64 copies 138 / 473, 140 /
-// 1211, 1846 / 12305.
+// rounding 135 / 46, 137 / 174, 1845 / 1770; in every row 64 copies 138 / 170, 140 / 651,
+// 1846 / 3150 (three at a time by settle_few: 473, 1211 and 12305).
 template <bool kQuarters>
 __device__ __forceinline__ int32_t settle(const float *__restrict__ x, const float *__restrict__ W,
                                           const float *__restrict__ b, float *S_n, int32_t K,
@@ -483,6 +539,9 @@ __device__ __forceinline__ int32_t settle(const float *__restrict__ x, const flo
         }
         if (!other) return row_arg;
     }
+    // A few at a time by settle_few; more than two turns' worth by settle_many.
+    const int turn = many > 2 * kSettleRows ? 64 / rg.n : kSettleRows;
+
     float best = -INFINITY;
     int32_t arg = K;
     int32_t cand = 0;
@@ -490,22 +549,23 @@ __device__ __forceinline__ int32_t settle(const float *__restrict__ x, const flo
     uint64_t m = 0;  // close ones of the block before k0, not taken yet
     for (;;) {
         int n = 0;
-        for (; n < kSettleRows; ++n) {
+        for (; n < turn; ++n) {
             while (m == 0 && k0 < K) {
                 if (k0 >= 64 * 64 || (blocks >> (k0 / 64)) & 1) m = __ballot(close(score(k0 + lane), k0 + lane));
                 k0 += 64;
             }
             if (m == 0) break;
             const int32_t k = k0 - 64 + __builtin_ctzll(m);
-            if (lane == n) cand = k;
+            if (turn == kSettleRows ? lane == n : lane / rg.n == n) cand = k;
             m &= m - 1;
         }
         if (n == 0) return arg;
-        const float acc = settle_few<kQuarters>(x, W, D, rg, cand, n, lds);
+        const float acc = turn == kSettleRows ? settle_few<kQuarters>(x, W, D, rg, cand, n, lds)
+                                              : settle_many<kQuarters>(x, W, D, rg, cand, lds);
         for (int c = 0; c < n; ++c) {
             float t = __shfl(acc, c * rg.n, 64);
             for (int r = 1; r < rg.n; ++r) t += __shfl(acc, c * rg.n + r, 64);
-            const int32_t k = __builtin_amdgcn_readlane(cand, c);
+            const int32_t k = __builtin_amdgcn_readlane(cand, turn == kSettleRows ? c : c * rg.n);
             t += b[k];
             if (lane == 0) S_n[k] = t;
             if (t > best || arg == K) {

@@ -34,12 +34,19 @@ def fixed_order(X, W, b, ranges):
     return total + b
 
 
-def near_copies(seed, N, K, D):
+def near_copies(seed, N, K, D, copies=None):
     g = torch.Generator(device="cuda")
     g.manual_seed(seed)
     X = torch.rand(N, D, generator=g, device="cuda")
     base = torch.randn(1, D, generator=g, device="cuda")
-    return X, base + 1e-7 * torch.randn(K, D, generator=g, device="cuda"), torch.zeros(K, device="cuda")
+    W = base + 1e-7 * torch.randn(K, D, generator=g, device="cuda")
+    if copies is not None:  # the others: nothing like them
+        other = torch.ones(K, dtype=torch.bool, device="cuda")
+        other[copies] = False
+        W[other] = torch.randn(int(other.sum()), D, generator=g, device="cuda") * 1e-3
+        X *= torch.sign(base)  # scores of the copies above the others'
+        X -= 0.9995 * (X @ base.T) / (base @ base.T) * base
+    return X.contiguous(), W, torch.zeros(K, device="cuda")
 
 
 @pytest.mark.parametrize("N,K,ranges", [(5, 32, 4), (24, 32, 4), (4096, 16, 4), (1000, 700, 4),
@@ -76,6 +83,26 @@ def test_quarters(grid, modality, N, K):
     want = fixed_order(X[rows], W, b, 0)
     torch.cuda.synchronize()
     assert torch.equal(A[rows].long(), want.argmax(1))
+    wts.close()
+    c.close()
+
+
+@pytest.mark.parametrize("N,K,ranges", [(4, 6000, 4), (300, 6000, 2), (1100, 6000, 1)])
+def test_many_copies_among_others(N, K, ranges):
+    """Close ones on both sides of identity 4096, more of them than a wave has lanes."""
+    require_gpu()
+    c = lbpf.Context()
+    copies = torch.randperm(K, generator=torch.Generator().manual_seed(3))[:150].sort().values.cuda()
+    X, W, b = near_copies(N, N, K, c.dim, copies)
+    wts = c.weights(W, b)
+    _, A = c.score(X, wts)
+    rows = slice(0, N, max(1, N // 100))
+    want = fixed_order(X[rows], W[copies], b[copies], ranges)
+    S64 = X[rows].double() @ W.double().T
+    torch.cuda.synchronize()
+    near = torch.isin(S64.argmax(1), copies)  # the others' best may be a row's
+    assert near.sum() >= len(S64) // 4
+    assert torch.equal(A[rows].long()[near], copies[want.argmax(1)][near])
     wts.close()
     c.close()
 
