@@ -322,10 +322,11 @@ void lbpf_graph_destroy(lbpf_graph *graph);
  * each frame's faces are detected, their features extracted and classified;
  * here for a batch of frames from many cameras at once). One replay copies
  * the batch's box table from the pipeline's pinned staging to the device,
- * runs the fused feature kernel (persistent, largest crop first), the scoring
+ * runs the feature kernels (persistent, largest crop first, or, in pipelines of
+ * up to 512 boxes, several workgroups per crop, as suits the batch), the scoring
  * of weights' precision (quantisation, GEMM, argmax) and copies the
  * identities back to host memory; every kernel reads the batch's box count
- * from device memory, so one graph serves batches of 0 .. max_boxes boxes.
+ * from device memory, so the graph serves batches of 0 .. max_boxes boxes.
  * Outputs are caller-owned: hist DEVICE [max_boxes][D] FP32, scores_opt
  * DEVICE [max_boxes][K] FP32 or NULL (then the pipeline keeps its own),
  * argmax DEVICE [max_boxes] int32, argmax_host_opt HOST [max_boxes] int32 in
@@ -342,8 +343,8 @@ lbpf_status lbpf_pipeline_create(lbpf_ctx *ctx, const lbpf_weights *weights, int
                                  int32_t *argmax_host_opt, lbpf_pipeline **out);
 
 /* Queue one batch on `stream`: the boxes (HOST array, validated like
- * lbpf_features, then written into the pinned staging in largest-first
- * order) over the images (HOST array of DEVICE planes, which must stay
+ * lbpf_features, then written into the pinned staging, with their
+ * largest-first order where the kernel takes it) over the images (HOST array of DEVICE planes, which must stay
  * valid until the replay has run), then one graph replay. Results
  * (hist[0 .. n_boxes), scores, argmax, argmax_host) are complete once
  * `stream` has passed this call. Launches on one pipeline must not overlap:

@@ -61,9 +61,9 @@ struct SplitCfg {
     int32_t parts = 0, px = 0;
 };
 SplitCfg split_for(const CropDesc *crops, int32_t n, const FeatParams &fp);
-// For a launch of up to max_n crops whose count and sizes are known on the
-// device only: split up to 512 crops, in grids whose rows hold the median parts
-// of the largest crop.
+// For a captured launch of up to max_n crops whose count and sizes it reads on the
+// device: up to 512 crops, in grids whose rows hold the median parts of the largest
+// crop.
 SplitCfg split_for_device_count(int32_t max_n, const FeatParams &fp);
 
 // Kernel launchers (features.hip). All return hipSuccess or the launch error.

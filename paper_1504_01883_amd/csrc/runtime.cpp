@@ -101,11 +101,13 @@ struct lbpf_pipeline {
     float *d_sx = nullptr;        //   per-tile argmax pairs
     float *d_apart = nullptr;
     size_t apart_elems = 0;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
+    // The same step with the persistent feature kernel, which takes the crops
+    // largest first, and (split.parts > 0) with several workgroups a crop.
+    hipGraph_t graph[2] = {};
+    hipGraphExec_t exec[2] = {};
+    SplitCfg split;
     hipEvent_t done = nullptr;  // end of the last replay (its staging may be reused)
     size_t bytes = 0;           // device bytes charged to the context
-    bool ordered = false;       // the feature kernel takes the crops largest first
     std::vector<CropDesc> crops;
     std::vector<int32_t> order;
 };
@@ -721,8 +723,10 @@ lbpf_status lbpf_score(lbpf_ctx *ctx, const float *hist, int32_t N, const lbpf_w
 void lbpf_pipeline_destroy(lbpf_pipeline *p) {
     if (!p) return;
     (void)hipDeviceSynchronize();
-    if (p->exec) (void)hipGraphExecDestroy(p->exec);
-    if (p->graph) (void)hipGraphDestroy(p->graph);
+    for (hipGraphExec_t e : p->exec)
+        if (e) (void)hipGraphExecDestroy(e);
+    for (hipGraph_t g : p->graph)
+        if (g) (void)hipGraphDestroy(g);
     if (p->done) (void)hipEventDestroy(p->done);
     if (p->h_stage) (void)hipHostFree(p->h_stage);
     for (void *d : {(void *)p->d_stage, (void *)p->d_queue, (void *)p->d_scores, (void *)p->d_xq,
@@ -792,27 +796,24 @@ lbpf_status lbpf_pipeline_create(lbpf_ctx *ctx, const lbpf_weights *w, int32_t m
     const CropDesc *d_crops = reinterpret_cast<const CropDesc *>(p->d_stage);
     const int32_t *d_order = reinterpret_cast<const int32_t *>(p->d_stage + p->off_order);
     const int32_t *d_n = reinterpret_cast<const int32_t *>(p->d_stage + p->off_n);
-    // Up to 512 boxes: several workgroups per crop (256 faces of 48-256 px, whole
-    // replay in BF16: 131 us against 163; 5 faces 77 against 98). More: the
-    // persistent feature kernel (4 workgroups per CU, 2 rows prefetched), which
-    // takes the crops in the order the host wrote: largest first.
-    const SplitCfg split = split_for_device_count(max_boxes, ctx->fp);
-    p->ordered = split.parts == 0;
-    LaunchCfg lc;
-    lc.persistent = p->ordered ? 1 : 0;
-    lc.wg_per_cu = 4;
-    lc.row_prefetch = 2;
-    lc.sorted = 1;
+    p->split = split_for_device_count(max_boxes, ctx->fp);
     hipStream_t cs = nullptr;
     e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
     if (e != hipSuccess) return cleanup(fail_hip(e, "hipStreamCreate"));
-    e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-    if (e == hipSuccess) {
+    for (int g = 0; g < (p->split.parts > 0 ? 2 : 1) && e == hipSuccess; ++g) {
+        // The persistent kernel: 4 workgroups per CU, 2 rows prefetched.
+        LaunchCfg lc;
+        lc.persistent = g == 0;
+        lc.wg_per_cu = 4;
+        lc.row_prefetch = 2;
+        lc.sorted = 1;
+        e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
+        if (e != hipSuccess) break;
         hipError_t el = hipMemcpyAsync(p->d_stage, p->h_stage, p->stage_bytes,
                                        hipMemcpyHostToDevice, cs);
         if (el == hipSuccess)
             el = launch_features(d_crops, max_boxes, ctx->fp, ctx->d_bins, hist, nullptr, cs,
-                                 split, lc, d_order, p->d_queue, ctx->num_cus, d_n);
+                                 p->split, lc, d_order, p->d_queue, ctx->num_cus, d_n);
         if (el == hipSuccess && !lp)
             el = launch_score_f32(hist, max_boxes, w->W, w->b, K, D, S, argmax, cs, 1, nullptr, d_n,
                                   false, 1, w->norm);
@@ -824,17 +825,30 @@ lbpf_status lbpf_pipeline_create(lbpf_ctx *ctx, const lbpf_weights *w, int32_t m
         if (el == hipSuccess && argmax_host_opt)
             el = hipMemcpyAsync(argmax_host_opt, argmax, sizeof(int32_t) * mb,
                                 hipMemcpyDeviceToHost, cs);
-        hipGraph_t graph = nullptr;
-        const hipError_t ee = hipStreamEndCapture(cs, &graph);
-        p->graph = graph;
+        const hipError_t ee = hipStreamEndCapture(cs, &p->graph[g]);
         e = el != hipSuccess ? el : ee;
     }
     (void)hipStreamDestroy(cs);
     if (e != hipSuccess) return cleanup(fail_hip(e, "pipeline capture"));
-    e = hipGraphInstantiate(&p->exec, p->graph, nullptr, nullptr, 0);
+    for (int g = 0; g < 2 && e == hipSuccess; ++g)
+        if (p->graph[g]) e = hipGraphInstantiate(&p->exec[g], p->graph[g], nullptr, nullptr, 0);
     if (e != hipSuccess) return cleanup(fail_hip(e, "hipGraphInstantiate"));
     *out = p;
     return LBPF_OK;
+}
+
+// Whether a batch takes the graph with several workgroups a crop: not where all faces
+// are small and few, whose features one workgroup makes as soon as three launches
+// could. Whole replays in us (64 identities, BF16), persistent / split: up to 64 boxes,
+// 4 of 48 x 48 51 / 57, 64 of 48 x 48 62 / 67, 16 of 96 x 96 60 / 62, 64 of 128 x 128 71 /
+// 69, 5 of 48-256 84 / 62; up to 256 boxes, 16 of 64 x 64 60 / 62, 64 of 64 x 64 69 / 67,
+// 256 of 128 x 128 102 / 79; up to 512, 256 of 48-256 139 / 99.
+static bool pipeline_splits(const lbpf_pipeline *p, size_t n) {
+    if (p->split.parts == 0) return false;
+    int32_t largest = 0;
+    for (size_t i = 0; i < n; ++i)
+        largest = std::max(largest, (int32_t)p->crops[i].w * p->crops[i].h);
+    return largest > 96 * 96 || n > (p->max_boxes <= 128 ? 64u : 16u);
 }
 
 lbpf_status lbpf_pipeline_launch(lbpf_pipeline *p, const lbpf_image *images, int32_t n_images,
@@ -847,7 +861,8 @@ lbpf_status lbpf_pipeline_launch(lbpf_pipeline *p, const lbpf_image *images, int
     // (a no-op when the caller already waited for its results).
     HIP_TRY(hipEventSynchronize(p->done), "hipEventSynchronize");
     const size_t n = (size_t)n_boxes;
-    if (p->ordered) {
+    const bool split = pipeline_splits(p, n);
+    if (!split) {
         for (size_t i = 0; i < n; ++i) p->order[i] = (int32_t)i;
         std::stable_sort(p->order.begin(), p->order.begin() + n, [&](int32_t a, int32_t c) {
             return (int64_t)p->crops[a].w * p->crops[a].h > (int64_t)p->crops[c].w * p->crops[c].h;
@@ -858,7 +873,7 @@ lbpf_status lbpf_pipeline_launch(lbpf_pipeline *p, const lbpf_image *images, int
     const int32_t nb = n_boxes;
     std::memcpy(p->h_stage + p->off_n, &nb, sizeof nb);
     hipStream_t s = (hipStream_t)stream;
-    HIP_TRY(hipGraphLaunch(p->exec, s), "hipGraphLaunch");
+    HIP_TRY(hipGraphLaunch(p->exec[split ? 1 : 0], s), "hipGraphLaunch");
     HIP_TRY(hipEventRecord(p->done, s), "hipEventRecord");
     return LBPF_OK;
 }
