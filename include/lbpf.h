@@ -70,7 +70,7 @@ typedef enum lbpf_status {
 } lbpf_status;
 
 typedef enum lbpf_precision {
-    LBPF_FP32 = 0,       /* FP32 operands, FP32 MFMA accumulation */
+    LBPF_FP32 = 0,       /* FP32 operands and accumulation (see lbpf_score) */
     LBPF_BF16 = 1,       /* BF16 operands (round to nearest even), FP32 accumulation */
     LBPF_FP16 = 2,       /* FP16 operands with per-row power-of-two scales */
     LBPF_FP8_E4M3 = 3,   /* OCP FP8 e4m3 operands with per-row amax/448 scales
